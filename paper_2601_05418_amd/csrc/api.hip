@@ -52,6 +52,7 @@ static void free_plan(Plan* pl) {
   void* bufs[] = {pl->coils, pl->psf,  pl->psfp, pl->twin, pl->tw_x, pl->tw_y, pl->lines, pl->pgroup,
                   pl->maskf, pl->zeros, pl->A128, pl->Aexp, pl->AH,   pl->W,    pl->Zp,   pl->Zt,    pl->part,
                   pl->vx,    pl->vr,   pl->vp,   pl->vq,   pl->vb,   pl->vd,   pl->red,  pl->hist,  pl->flag,
+                  pl->Ac2,   pl->wscale,
                   pl->bmod,  pl->Ec,   pl->T3,   pl->pts3, pl->sel3, pl->maskf3, pl->tw_y3, pl->tw_z3};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -198,7 +199,7 @@ static int setup_plan(Plan& pl, const gpjc_geom* g, const gpjc_c64* d_coils, con
   GPJC_TRY(dalloc(&pl.maskf, (size_t)pl.ny));
   GPJC_TRY(dalloc(&pl.zeros, 64));
   GPJC_HIP(hipMemsetAsync(pl.zeros, 0, 64 * sizeof(float), stream));
-  if (!pl.general) GPJC_TRY(dalloc(&pl.W, (size_t)pl.B * pl.nc * pl.ny * pl.nt));
+  if (!pl.general) GPJC_TRY(dalloc(&pl.W, (size_t)pl.B * pl.nc * pl.ny * pl.nt + 2));  // + 2: pair.hip, odd P
   GPJC_TRY(dalloc(&pl.part, (size_t)pl.f1h_nchunk * pl.B * npix));
   const size_t ni = pl.img_elems();
   GPJC_TRY(dalloc(&pl.vx, ni));
@@ -222,6 +223,13 @@ static int setup_plan(Plan& pl, const gpjc_geom* g, const gpjc_c64* d_coils, con
     GPJC_TRY(dalloc(&pl.Zp, (size_t)kMaxKsplit * pl.B * pl.np * pl.K * pl.ny));
     GPJC_TRY(dalloc(&pl.Zt, (size_t)pl.B * pl.np * pl.ny * pl.Kp));
     GPJC_HIP(hipMemsetAsync(pl.Zt, 0, sizeof(float2) * (size_t)pl.B * pl.np * pl.ny * pl.Kp, stream));
+    if (!pl.general) {
+      GPJC_TRY(dalloc(&pl.Ac2, pair_compress_words(pl) + pair_expand_words(pl)));
+      pl.Ae2 = pl.Ac2 + pair_compress_words(pl);
+      GPJC_TRY(dalloc(&pl.wscale, pair_scale_floats(pl)));
+      pl.ascale = pl.wscale + (size_t)pl.B * pl.ny;
+      pl.wbound = pl.ascale + pl.G;
+    }
     if (pl.general) {
       GPJC_TRY(dalloc(&pl.bmod, (size_t)pl.nt * npix));
       GPJC_TRY(dalloc(&pl.Ec, explicit_bytes(pl.nx, pl.ny, pl.np, pl.K) / sizeof(float2)));
@@ -251,6 +259,7 @@ static int setup_plan(Plan& pl, const gpjc_geom* g, const gpjc_c64* d_coils, con
     GPJC_HIP(hipMemcpyAsync(pl.psf, d_psf, sizeof(float2) * pl.ny * pl.nt, hipMemcpyDeviceToDevice, stream));
   }
   GPJC_TRY(launch_prep_tables(pl));
+  if (pl.wscale) GPJC_TRY(setup_pair(pl));
   GPJC_HIP(hipMemsetAsync(pl.hist, 0, sizeof(double) * pl.hist_cap, stream));
 
   if (pl.compressed && pl.G < pl.np && pl.P > 1 && pl.general) {

@@ -32,6 +32,9 @@
 // hold both parts one after the other and meet the same bank row twice, so
 // Z^T adds no rounding beyond the bank's and W's.
 //
+// The FP32 operator's contractions run on FP16 pairs (pair.hip); the FP32 forms
+// here serve gpjc_compress and the operands that those cannot address.
+//
 // Two families of kernels, chosen per launch:
 // - LDS-staged (k_compress_lds, k_expand_lds): the work-group loads k-tiles of
 //   one 128-byte line per row cooperatively into LDS and the waves read their
@@ -914,49 +917,64 @@ struct BankOut {
   uint16_t* AH16[2];
 };
 
-__device__ inline void put16(uint16_t* const (&dst)[2], size_t i, float v) {
-  if (dst[0]) dst[0][i] = (uint16_t)f32_to_bf16_bits(v);
-  if (dst[1]) dst[1][i] = (uint16_t)f32_to_f16_bits(v);
-}
-
-__global__ void k_expand_bank(const double2* __restrict__ A, BankOut o, int G, int K, int kp, int ns) {
-  const size_t total = (size_t)G * K * ns;
-  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (size_t)gridDim.x * blockDim.x) {
-    const int i = (int)(idx % ns);
-    const int k = (int)((idx / ns) % K);
-    const int g = (int)(idx / ((size_t)ns * K));
-    const double2 v = A[idx];
-    const float ar = (float)v.x, ai = (float)v.y;
-    const size_t e0 = ((size_t)g * 2 * K + 2 * k) * 2 * ns + 2 * i, e1 = e0 + 2 * ns;
-    const float ev[4] = {ar, -ai, ai, ar};  // e0, e0 + 1, e1, e1 + 1
-    const size_t ei[4] = {e0, e0 + 1, e1, e1 + 1};
-    const size_t h0 = ((size_t)g * 2 * ns + 2 * i) * 2 * kp + 2 * k, h1 = h0 + 2 * kp;
-    const float hv[4] = {ar, ai, -ai, ar};
-    const size_t hi[4] = {h0, h0 + 1, h1, h1 + 1};
+// A work-group takes 32 rows k x 32 columns i of one group: the compressing
+// forms are written along i, the expanding ones (transposed) along k, from a
+// tile in LDS, so both sides are whole segments.  (One thread per element
+// wrote the expanding forms 4 bytes at a time, 512 bytes apart: 200 us for 42
+// groups of 64 x 1024.)
+__global__ __launch_bounds__(256) void k_expand_bank(const double2* __restrict__ A, BankOut o, int K, int kp, int ns) {
+  __shared__ float2 t[32][33];
+  const int i0 = blockIdx.x * 32, k0 = blockIdx.y * 32, g = blockIdx.z;
+  const int c = threadIdx.x & 31, r0 = threadIdx.x >> 5;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      o.Aexp[ei[r]] = ev[r];
-      o.AH[hi[r]] = hv[r];
-      put16(o.Aexp16, ei[r], ev[r]);
-      put16(o.AH16, hi[r], hv[r]);
+  for (int r = r0; r < 32; r += 8) {
+    const int k = k0 + r, i = i0 + c;
+    const double2 v = k < K && i < ns ? A[((size_t)g * K + k) * ns + i] : make_double2(0.0, 0.0);
+    t[r][c] = make_float2((float)v.x, (float)v.y);
+  }
+  __syncthreads();
+  auto put = [&](float* f, uint16_t* const (&h)[2], size_t at, float x, float y) {
+    *reinterpret_cast<float2*>(f + at) = make_float2(x, y);
+    if (h[0])
+      *reinterpret_cast<uint32_t*>(h[0] + at) = f32_to_bf16_bits(x) | (f32_to_bf16_bits(y) << 16);
+    if (h[1]) *reinterpret_cast<uint32_t*>(h[1] + at) = f32_to_f16_bits(x) | (f32_to_f16_bits(y) << 16);
+  };
+#pragma unroll
+  for (int r = r0; r < 32; r += 8) {
+    const int k = k0 + r, i = i0 + c;
+    if (k < K && i < ns) {
+      const float2 a = t[r][c];
+      const size_t e = ((size_t)g * 2 * K + 2 * k) * 2 * ns + 2 * i;
+      put(o.Aexp, o.Aexp16, e, a.x, -a.y);
+      put(o.Aexp, o.Aexp16, e + 2 * ns, a.y, a.x);
+    }
+  }
+#pragma unroll
+  for (int r = r0; r < 32; r += 8) {
+    const int i = i0 + r, k = k0 + c;
+    if (k < K && i < ns) {
+      const float2 a = t[c][r];
+      const size_t h = ((size_t)g * 2 * ns + 2 * i) * 2 * kp + 2 * k;
+      put(o.AH, o.AH16, h, a.x, a.y);
+      put(o.AH, o.AH16, h + 2 * kp, -a.y, a.x);
     }
   }
 }
 
-// Tile-shape tables: waves WM x WN per work-group, wave tile MT x NT MFMA
-// tiles, depth.  kCompressLds / kExpandLds: LDS-staged FP32 (32 x 32 tiles
-// of complex rows / columns, depth = k-tiles of register prefetch); the *16
-// tables: LDS-staged 16-bit (16 x 16 tiles).  Index 0 is the default of its
-// class.  The general forms (operands of 2 GiB or more) use one fixed shape.
+// Tile shapes: waves WM x WN per work-group, wave tile MT x NT MFMA tiles,
+// depth (k-tiles of register prefetch).  LDS-staged FP32 (32 x 32 tiles of
+// complex rows / columns) and the general forms (operands of 2 GiB or more)
+// have fixed shapes; the tables are the variants of the 16-bit (16 x 16
+// tiles) and BF16X6 classes, index 0 the default of its class.  The FP32
+// class's variants are those of pair.hip.
 struct Shape {
   int wm, wn, mt, nt, depth;
 };
 constexpr int kNumShapes = 8;
-constexpr Shape kCompressLds[kNumShapes] = {{2, 2, 1, 1, 1}, {2, 1, 1, 1, 2}, {2, 1, 1, 1, 1}, {2, 1, 1, 2, 1},
-                                            {4, 1, 1, 1, 1}, {2, 4, 1, 1, 1}, {1, 2, 1, 1, 1}, {1, 4, 1, 1, 1}};
-constexpr Shape kExpandLds[kNumShapes] = {{1, 2, 1, 1, 1}, {1, 4, 1, 1, 1}, {1, 2, 1, 1, 2}, {2, 2, 1, 1, 1},
-                                          {1, 1, 1, 1, 1}, {1, 2, 1, 2, 1}, {2, 1, 1, 1, 1}, {1, 4, 1, 1, 2}};
+// FP32 on the FP32 MFMA: 64 or 32 complex rows per work-group (acquired data of
+// gpjc_compress, and operands that the FP16-pair forms cannot address).
+constexpr Shape kCompressLds64 = {2, 2, 1, 1, 1}, kCompressLds32 = {1, 4, 1, 1, 1};
+constexpr Shape kExpandLdsF32 = {1, 2, 1, 1, 1};
 constexpr Shape kCompressLds16[kNumShapes] = {{4, 1, 2, 4, 1}, {2, 2, 4, 2, 1}, {2, 1, 4, 2, 1}, {4, 1, 2, 2, 1},
                                               {2, 1, 4, 4, 1}, {4, 2, 2, 2, 1}, {1, 4, 2, 2, 1}, {2, 2, 2, 2, 1}};
 constexpr Shape kExpandLds16[kNumShapes] = {{2, 2, 2, 2, 1}, {1, 2, 2, 2, 1}, {1, 4, 2, 2, 1}, {2, 4, 2, 2, 1},
@@ -1005,46 +1023,66 @@ bool expand_staged(const ExpandArgs& a, Store st) {
 
 int tiles(int n, int t) { return (n + t - 1) / t; }
 
+template <int WM, int WN, int MT, int NT, int PF, Store ST>
+void launch_compress_lds(StageScope& sc, hipStream_t s, const CompressArgs& a) {
+  constexpr int T = Geo<ST>::T;
+  CompressArgs c = a;
+  if (ST == Store::F32) c.M = a.K;  // complex rows of the three-multiplication form
+  const dim3 grid(tiles(c.N, WN * NT * T) * tiles(c.M, WM * MT * T) * a.B * a.np * a.ksplit);
+  if constexpr (storage_of(ST) == Store::F32) {
+    if (a.P & 1) {
+      sc.launch(k_compress_lds<WM, WN, MT, NT, PF, ST, true>, grid, dim3(64 * WM * WN), 0, s, c);
+      return;
+    }
+  }
+  sc.launch(k_compress_lds<WM, WN, MT, NT, PF, ST, false>, grid, dim3(64 * WM * WN), 0, s, c);
+}
+template <Store ST>
+void launch_compress_general(StageScope& sc, hipStream_t s, const CompressArgs& a) {
+  constexpr Shape S = kCompressGeneral;
+  const dim3 grid(tiles(a.N, S.wn * S.nt * 16) * tiles(a.M, S.wm * S.mt * 16) * a.B * a.np * a.ksplit);
+  sc.launch(k_compress<S.wm, S.wn, S.mt, S.nt, storage_of(ST)>, grid, dim3(64 * S.wm * S.wn), 0, s, a);
+}
+template <int WM, int WN, int MT, int NT, int PF, Store ST>
+void launch_expand_lds(StageScope& sc, hipStream_t s, const ExpandArgs& a) {
+  constexpr int T = Geo<ST>::T;
+  ExpandArgs e = a;
+  if (ST == Store::F32) e.N = a.N / 2;  // complex columns of the three-multiplication form
+  const dim3 grid(tiles(e.N, WN * NT * T) * tiles(e.M, WM * MT * T) * a.B * a.np);
+  sc.launch(k_expand_lds<WM, WN, MT, NT, PF, ST>, grid, dim3(64 * WM * WN), 0, s, e);
+}
+template <Store ST>
+void launch_expand_general(StageScope& sc, hipStream_t s, const ExpandArgs& a) {
+  constexpr Shape S = kExpandGeneral;
+  const dim3 grid(tiles(a.N, S.wn * S.nt * 16) * tiles(a.M, S.wm * S.mt * 16) * a.B * a.np);
+  sc.launch(k_expand<S.wm, S.wn, S.mt, S.nt, storage_of(ST)>, grid, dim3(64 * S.wm * S.wn), 0, s, a);
+}
 template <int V, Store ST>
 void launch_compress_v(StageScope& sc, hipStream_t s, const CompressArgs& a) {
-  const int rest = a.B * a.np * a.ksplit;
-  if (compress_staged(a, ST)) {
-    constexpr Shape S = ST == Store::F32 ? kCompressLds[V] : ST == Store::BF16X6 ? kCompressSplit[V] : kCompressLds16[V];
-    constexpr int T = Geo<ST>::T;
-    CompressArgs c = a;
-    if (ST == Store::F32) c.M = a.K;  // complex rows of the three-multiplication form
-    const dim3 grid(tiles(c.N, S.wn * S.nt * T) * tiles(c.M, S.wm * S.mt * T) * rest);
-    if constexpr (storage_of(ST) == Store::F32) {
-      if (a.P & 1) {
-        sc.launch(k_compress_lds<S.wm, S.wn, S.mt, S.nt, S.depth, ST, true>, grid, dim3(64 * S.wm * S.wn),
-                           0, s, c);
-        return;
-      }
-    }
-    sc.launch(k_compress_lds<S.wm, S.wn, S.mt, S.nt, S.depth, ST, false>, grid, dim3(64 * S.wm * S.wn), 0,
-                       s, c);
-  } else {
-    // operands of 2 GiB or more: BF16X6 takes the FP32 general form
-    constexpr Shape S = kCompressGeneral;
-    const dim3 grid(tiles(a.N, S.wn * S.nt * 16) * tiles(a.M, S.wm * S.mt * 16) * rest);
-    sc.launch(k_compress<S.wm, S.wn, S.mt, S.nt, storage_of(ST)>, grid, dim3(64 * S.wm * S.wn), 0, s, a);
-  }
+  constexpr Shape S = ST == Store::BF16X6 ? kCompressSplit[V] : kCompressLds16[V];
+  if (compress_staged(a, ST)) launch_compress_lds<S.wm, S.wn, S.mt, S.nt, S.depth, ST>(sc, s, a);
+  else launch_compress_general<ST>(sc, s, a);  // BF16X6 takes the FP32 general form
 }
 template <int V, Store ST>
 void launch_expand_v(StageScope& sc, hipStream_t s, const ExpandArgs& a) {
-  const int rest = a.B * a.np;
-  if (expand_staged(a, ST)) {
-    constexpr Shape S = ST == Store::F32 ? kExpandLds[V] : ST == Store::BF16X6 ? kExpandSplit[V] : kExpandLds16[V];
-    constexpr int T = Geo<ST>::T;
-    ExpandArgs e = a;
-    if (ST == Store::F32) e.N = a.N / 2;  // complex columns of the three-multiplication form
-    const dim3 grid(tiles(e.N, S.wn * S.nt * T) * tiles(e.M, S.wm * S.mt * T) * rest);
-    sc.launch(k_expand_lds<S.wm, S.wn, S.mt, S.nt, S.depth, ST>, grid, dim3(64 * S.wm * S.wn), 0, s, e);
-  } else {
-    constexpr Shape S = kExpandGeneral;
-    const dim3 grid(tiles(a.N, S.wn * S.nt * 16) * tiles(a.M, S.wm * S.mt * 16) * rest);
-    sc.launch(k_expand<S.wm, S.wn, S.mt, S.nt, storage_of(ST)>, grid, dim3(64 * S.wm * S.wn), 0, s, a);
-  }
+  constexpr Shape S = ST == Store::BF16X6 ? kExpandSplit[V] : kExpandLds16[V];
+  if (expand_staged(a, ST)) launch_expand_lds<S.wm, S.wn, S.mt, S.nt, S.depth, ST>(sc, s, a);
+  else launch_expand_general<ST>(sc, s, a);
+}
+// FP32 MFMA: the taller row tile unless it pads more than an eighth of the rows.
+void compress_f32(StageScope& sc, hipStream_t s, const CompressArgs& a) {
+  constexpr Shape S = kCompressLds64, L = kCompressLds32;
+  const int padded = tiles(a.K, 64) * 64;
+  if (!compress_staged(a, Store::F32)) launch_compress_general<Store::F32>(sc, s, a);
+  else if (8 * (padded - a.K) <= padded)
+    launch_compress_lds<S.wm, S.wn, S.mt, S.nt, S.depth, Store::F32>(sc, s, a);
+  else
+    launch_compress_lds<L.wm, L.wn, L.mt, L.nt, L.depth, Store::F32>(sc, s, a);
+}
+void expand_f32(StageScope& sc, hipStream_t s, const ExpandArgs& a) {
+  constexpr Shape S = kExpandLdsF32;
+  if (expand_staged(a, Store::F32)) launch_expand_lds<S.wm, S.wn, S.mt, S.nt, S.depth, Store::F32>(sc, s, a);
+  else launch_expand_general<Store::F32>(sc, s, a);
 }
 
 template <Store ST>
@@ -1088,8 +1126,6 @@ int compress_kchunk(int KD, int ksplit, Store st) {
   return ((KD + ksplit - 1) / ksplit + kb - 1) / kb * kb;
 }
 
-int kblock(Store st) { return st == Store::F32 ? Geo<Store::F32>::KB : Geo<Store::BF16>::KB; }
-
 int gemm_compress(const Plan& pl, StageScope& sc, Store st, const void* in, int ncol, float2* out, int ksplit,
                   int cvar) {
   CompressArgs a;
@@ -1117,7 +1153,7 @@ int gemm_compress(const Plan& pl, StageScope& sc, Store st, const void* in, int 
   a.kchunk = compress_kchunk(a.KD, ksplit, st);
   a.split_stride = (size_t)pl.B * pl.np * pl.K * ncol;
   switch (st) {
-    case Store::F32: compress_variant<Store::F32>(cvar, sc, pl.stream, a); break;
+    case Store::F32: compress_f32(sc, pl.stream, a); break;
     case Store::BF16X6: compress_variant<Store::BF16X6>(cvar, sc, pl.stream, a); break;
     case Store::BF16: compress_variant<Store::BF16>(cvar, sc, pl.stream, a); break;
     default: compress_variant<Store::F16>(cvar, sc, pl.stream, a); break;
@@ -1132,32 +1168,31 @@ int gemm_compress_variants() { return kNumShapes; }
 int gemm_expand_variants() { return kNumShapes; }
 
 // Defaults: for the compressing contraction the work-group shape with the
-// tallest row tile that pads at most 1/8 of its rows (FP32: 64 or 32 of the K
-// complex rows; 16-bit and BF16X6: 128, 64 or 32 of the 2K real rows), else
-// the shortest; for the expanding one shape 0; and a split giving about 504
-// work-groups.
+// tallest row tile that pads at most 1/8 of its rows (128, 64 or 32 of the 2K
+// real rows), else the shortest; for the expanding one shape 0; and a split
+// giving about 504 work-groups.  FP32: default_pair_config.
 int compress_shape_for_rows(int rows, Store st) {
-  const bool f32 = st == Store::F32;
-  const int n = f32 ? 2 : 3;
   const int order16[3] = {0, 7, 6}, orderx6[3] = {0, 3, 6};
   const int* order = st == Store::BF16X6 ? orderx6 : order16;
-  const int tile[3] = {f32 ? 64 : 128, f32 ? 32 : 64, 32};
-  for (int i = 0; i < n; ++i) {
+  const int tile[3] = {128, 64, 32};
+  for (int i = 0; i < 3; ++i) {
     const int padded = (rows + tile[i] - 1) / tile[i] * tile[i];
     if (8 * (padded - rows) <= padded) return order[i];
   }
-  return order[n - 1];
+  return order[2];
 }
 void default_gemm_config(Plan& pl) {
   for (const Store st : {Store::F32, Store::BF16, Store::BF16X6}) {
     Plan::GemmCfg& g = pl.cfg(st);
-    const int rows = st == Store::F32 ? pl.K : 2 * pl.K;  // complex rows in FP32, real rows otherwise
-    g.cvar = compress_shape_for_rows(rows, st);
+    if (st == Store::F32 && pair_compress_ok(pl)) {
+      default_pair_config(pl, g);
+      continue;
+    }
+    const int rows = 2 * pl.K;
+    g.cvar = st == Store::F32 ? 0 : compress_shape_for_rows(rows, st);
     g.evar = 0;
-    const Shape S = st == Store::F32 ? kCompressLds[g.cvar] : st == Store::BF16X6 ? kCompressSplit[g.cvar]
-                                                                                  : kCompressLds16[g.cvar];
-    const int T = st == Store::F32 ? 32 : 16;
-    const long t = (long)tiles(pl.ny, S.wn * S.nt * T) * tiles(rows, S.wm * S.mt * T) * pl.B * pl.np;
+    const Shape S = st == Store::BF16X6 ? kCompressSplit[g.cvar] : kCompressLds16[g.cvar];
+    const long t = (long)tiles(pl.ny, S.wn * S.nt * 16) * tiles(rows, S.wm * S.mt * 16) * pl.B * pl.np;
     // work-groups: measured best for E'^H E' on the 224 x 224, 32-coil slice
     // (the phase-encode stage reads one partial of Z per split)
     const long target = 504;
@@ -1175,18 +1210,24 @@ bool compress_split_staged(const Plan& pl, Store st, int ksplit) {
                             elem_bytes(st));
 }
 
+int compress_partials(const Plan& pl, Store st) {
+  return st == Store::F32 && pair_compress_ok(pl) ? pair_partials(pl) : pl.cfg(st).ksplit;
+}
+
 int launch_group_compress(const Plan& pl, Store st) {
   StageScope sc(pl, GPJC_STAGE_GROUP_COMPRESS, true);
+  if (st == Store::F32 && pair_compress_ok(pl)) return launch_compress_pair(pl, sc, pl.W, pl.Zp);
   return gemm_compress(pl, sc, st, pl.W, pl.ny, pl.Zp, pl.cfg(st).ksplit, pl.cfg(st).cvar);
 }
 
 int launch_compress_data(const Plan& pl, const float2* ksp, float2* out) {
   StageScope sc(pl, GPJC_STAGE_GROUP_COMPRESS, true);
-  return gemm_compress(pl, sc, Store::F32, ksp, pl.ms, out, 1, pl.cfg(Store::F32).cvar);
+  return gemm_compress(pl, sc, Store::F32, ksp, pl.ms, out, 1, 0);
 }
 
 int launch_group_expand(const Plan& pl, Store st) {
   StageScope sc(pl, GPJC_STAGE_GROUP_EXPAND, true);
+  if (st == Store::F32 && pair_expand_ok(pl)) return launch_expand_pair(pl, sc);
   ExpandArgs a;
   if (storage_of(st) == Store::F32) {
     a.Zt = pl.Zt;
@@ -1211,7 +1252,7 @@ int launch_group_expand(const Plan& pl, Store st) {
   a.np = pl.np;
   a.B = pl.B;
   switch (st) {
-    case Store::F32: expand_variant<Store::F32>(pl.cfg(st).evar, sc, pl.stream, a); break;
+    case Store::F32: expand_f32(sc, pl.stream, a); break;
     case Store::BF16X6: expand_variant<Store::BF16X6>(pl.cfg(st).evar, sc, pl.stream, a); break;
     case Store::BF16: expand_variant<Store::BF16>(pl.cfg(st).evar, sc, pl.stream, a); break;
     default: expand_variant<Store::F16>(pl.cfg(st).evar, sc, pl.stream, a); break;
@@ -1226,11 +1267,10 @@ int launch_expand_bank(Plan& pl) {
   BankOut o{pl.Aexp, pl.AH, {pl.Aexp16[0], pl.Aexp16[1]}, {pl.AH16[0], pl.AH16[1]}};
   for (int i = 0; i < 2; ++i)
     if (pl.AH16[i]) GPJC_HIP(hipMemsetAsync(pl.AH16[i], 0, nh * sizeof(uint16_t), pl.stream));
-  const size_t total = (size_t)pl.G * pl.K * pl.ns;
-  const int blocks = (int)std::min<size_t>((total + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_expand_bank, dim3(blocks), dim3(256), 0, pl.stream, pl.A128, o, pl.G, pl.K, pl.Kp, pl.ns);
+  hipLaunchKernelGGL(k_expand_bank, dim3((pl.ns + 31) / 32, (pl.K + 31) / 32, pl.G), dim3(256), 0, pl.stream, pl.A128,
+                     o, pl.K, pl.Kp, pl.ns);
   GPJC_HIP(hipGetLastError());
-  return GPJC_OK;
+  return pl.Ac2 ? launch_pair_bank(pl) : GPJC_OK;
 }
 
 }  // namespace gpjc

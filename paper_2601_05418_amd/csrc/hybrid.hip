@@ -198,7 +198,7 @@ int lsqr_u(const Plan& pl, bool start, int ms, int R, int ksplit) {
 }
 
 int lsqr_u_st(const Plan& pl, Store st, bool start, int ms, int R) {
-  const int ks = pl.cfg(st).ksplit;  // partials of Z the compressing contraction of st wrote
+  const int ks = compress_partials(pl, st);  // partials of Z the compressing contraction of st wrote
   switch (storage_of(st)) {
     case Store::F32: return lsqr_u<Store::F32>(pl, start, ms, R, ks);
     case Store::BF16: return lsqr_u<Store::BF16>(pl, start, ms, R, ks);

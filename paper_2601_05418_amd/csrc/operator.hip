@@ -84,11 +84,18 @@ __device__ inline int div_os(int t, float inv_os) { return (int)(((float)t + 0.5
 // grid (row blocks, nc, B); `rows` image rows per work-group.  LDS lines are
 // padded (fft.h): line (r, s) holds the s-th sub-transform of row r.
 // ---------------------------------------------------------------------------
+// The scale of W's rows as FP16 pairs (pair.hip) from a row's L1 norm:
+// |W[n][y][t]| <= max|psf| max|coil| sum_x |img[y][x]| / sqrt(Nt) = wbound * l1.
+struct RowScale {
+  float* out;           // [B][ny], or NULL: not wanted
+  const float* wbound;
+};
+
 template <int NX, Store ST>
 __global__ __launch_bounds__(256) void k_readout_fwd(const float2* __restrict__ img, const float2* __restrict__ coils,
                                                      const float2* __restrict__ psfp, const float2* __restrict__ twin,
                                                      const float2* __restrict__ tw, void* __restrict__ W, int ny,
-                                                     int nc, int os, float inv_os, int rows) {
+                                                     int nc, int os, float inv_os, int rows, RowScale rsc) {
   constexpr int LS = fline(NX);
   extern __shared__ float2 sm[];
   const int tid = threadIdx.x;
@@ -96,6 +103,18 @@ __global__ __launch_bounds__(256) void k_readout_fwd(const float2* __restrict__ 
   const int n = blockIdx.y, b = blockIdx.z;
   const int y0 = blockIdx.x * rows;
   const int nr = min(rows, ny - y0);
+  if (rsc.out && n == 0) {
+    for (int r = tid >> 6; r < nr; r += 4) {
+      float l1 = 0.f;
+      for (int x = tid & 63; x < NX; x += 64) {
+        const float2 v = img[((size_t)b * ny + y0 + r) * NX + x];
+        l1 += fabsf(v.x) + fabsf(v.y);
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
+      if ((tid & 63) == 0) rsc.out[(size_t)b * ny + y0 + r] = pair_scale(l1 * *rsc.wbound);
+    }
+  }
   float2* twl = sm;
   float2* bufA = sm + NX;
   float2* bufB = bufA + rows * os * LS;
@@ -211,10 +230,11 @@ template <int NX, Store ST>
 __global__ __launch_bounds__(256) void k_readout_fwd2(const float2* __restrict__ img, const float2* __restrict__ coils,
                                                       const float2* __restrict__ psfp, const float2* __restrict__ twin,
                                                       const float2* __restrict__ tw, void* __restrict__ W, int ny,
-                                                      int nc, int os, int cb) {
+                                                      int nc, int os, int cb, RowScale rsc) {
   using S = Split<NX>;
   constexpr int N1 = S::N1, N2 = S::N2, AS = N1 + 1;
   extern __shared__ float2 sm[];
+  __shared__ float wl1[4];
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int nt = os * NX;
   const int y = blockIdx.x, n0 = blockIdx.y * cb, b = blockIdx.z;
@@ -241,6 +261,15 @@ __global__ __launch_bounds__(256) void k_readout_fwd2(const float2* __restrict__
       const int i = tid + k * nthr;
       if (i < tot) u[i] = cmul(cv[k], iv[k]);
     }
+    if (rsc.out && n0 == 0) {  // the first NX elements are the image row (NX <= kSetupRegs blockDim)
+      float l1 = 0.f;
+#pragma unroll
+      for (int k = 0; k < kSetupRegs; ++k)
+        if (tid + k * nthr < NX) l1 += fabsf(iv[k].x) + fabsf(iv[k].y);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
+      if ((tid & 63) == 0) wl1[tid >> 6] = l1;
+    }
     for (int i = tid + kSetupRegs * nthr; i < tot; i += nthr) {
       const int c = i / NX, x = i - c * NX;
       u[i] = cmul(coils[((size_t)(n0 + c) * ny + y) * NX + x], ip[x]);
@@ -249,6 +278,8 @@ __global__ __launch_bounds__(256) void k_readout_fwd2(const float2* __restrict__
     for (int i = tid + nthr; i < NX; i += nthr) twl[i] = tw[i];
   }
   __syncthreads();
+  if (rsc.out && n0 == 0 && tid == 0)
+    rsc.out[(size_t)b * ny + y] = pair_scale((wl1[0] + wl1[1] + wl1[2] + wl1[3]) * *rsc.wbound);
   const int items1 = ncb * os * N2;
   for (int it = tid; it < items1; it += nthr) {
     const int r = it / N2, i2 = it - r * N2;  // r = c * os + s
@@ -985,12 +1016,13 @@ struct ReadoutFwd {
   struct L {
     static int run(const Plan& pl, const float2* img) {
       StageScope sc(pl, GPJC_STAGE_READOUT_FWD, true);
+      const RowScale rsc{ST == Store::F32 ? pl.wscale : nullptr, pl.wbound};
       if constexpr (Split<NX>::ok) {
         if (pl.f2_cb > 0) {
           const size_t lds = two_pass_lds_fwd(NX, pl.os, pl.f2_cb) * sizeof(float2);
           dim3 grid(pl.ny, (pl.nc + pl.f2_cb - 1) / pl.f2_cb, pl.B);
           sc.launch(k_readout_fwd2<NX, ST>, grid, dim3(pl.f2_threads), lds, pl.stream, img, pl.coils, pl.psfp,
-                    pl.twin, pl.tw_x, (void*)pl.W, pl.ny, pl.nc, pl.os, pl.f2_cb);
+                    pl.twin, pl.tw_x, (void*)pl.W, pl.ny, pl.nc, pl.os, pl.f2_cb, rsc);
           GPJC_HIP(hipGetLastError());
           return GPJC_OK;
         }
@@ -999,7 +1031,7 @@ struct ReadoutFwd {
       const size_t lds = (size_t)(NX + 2 * rows * pl.os * fline(NX)) * sizeof(float2);
       dim3 grid((pl.ny + rows - 1) / rows, pl.nc, pl.B);
       sc.launch(k_readout_fwd<NX, ST>, grid, dim3(256), lds, pl.stream, img, pl.coils, pl.psfp, pl.twin, pl.tw_x,
-                (void*)pl.W, pl.ny, pl.nc, pl.os, 1.0f / pl.os, rows);
+                (void*)pl.W, pl.ny, pl.nc, pl.os, 1.0f / pl.os, rows, rsc);
       GPJC_HIP(hipGetLastError());
       return GPJC_OK;
     }
@@ -1178,7 +1210,7 @@ int launch_combine(const Plan& pl, float2* out) {
 // the phase-encode stage sums.
 int launch_pe_fwd(const Plan& pl, float2* out, Store st) {
   if (pl.nz > 1) return launch_pe3_fwd(pl, out, st);
-  return dispatch_n<PeFwd>(pl.ny, pl, out, pl.cfg(st).ksplit);
+  return dispatch_n<PeFwd>(pl.ny, pl, out, compress_partials(pl, st));
 }
 int launch_pe_adj(const Plan& pl, const float2* in, Store st) {
   if (pl.nz > 1) return launch_pe3_adj(pl, in, st);
@@ -1190,7 +1222,7 @@ int launch_pe_adj(const Plan& pl, const float2* in, Store st) {
 }
 int launch_pe_normal(const Plan& pl, Store st) {
   if (pl.nz > 1) return launch_pe3_normal(pl, st);
-  const int ks = pl.cfg(st).ksplit;
+  const int ks = compress_partials(pl, st);
   switch (storage_of(st)) {
     case Store::F32: return dispatch_n<PeNormal<Store::F32>::L>(pl.ny, pl, ks);
     case Store::BF16: return dispatch_n<PeNormal<Store::BF16>::L>(pl.ny, pl, ks);

@@ -286,7 +286,7 @@ int y_inv(const Plan& pl, Store st) {
 int launch_pe3_fwd(const Plan& pl, float2* out, Store st) {
   StageScope sc(pl, GPJC_STAGE_PE_FWD);
   const size_t zs = (size_t)pl.B * pl.np * pl.K * pl.ny;
-  GPJC_TRY(dispatch3<YFwd>(pl.ny2, pl, pl.cfg(st).ksplit, zs));
+  GPJC_TRY(dispatch3<YFwd>(pl.ny2, pl, compress_partials(pl, st), zs));
   GPJC_TRY(dispatch3<ZPass>(pl.nz, pl, 0));
   const size_t nplanes = (size_t)pl.B * pl.np * pl.K;
   hipLaunchKernelGGL(k3_gather, dim3(2048), dim3(256), 0, pl.stream, pl.T3, pl.pts3, pl.ms, pl.ny, nplanes, out);
@@ -307,7 +307,7 @@ int launch_pe3_adj(const Plan& pl, const float2* in, Store st) {
 int launch_pe3_normal(const Plan& pl, Store st) {
   StageScope sc(pl, GPJC_STAGE_PE_NORMAL);
   const size_t zs = (size_t)pl.B * pl.np * pl.K * pl.ny;
-  GPJC_TRY(dispatch3<YFwd>(pl.ny2, pl, pl.cfg(st).ksplit, zs));
+  GPJC_TRY(dispatch3<YFwd>(pl.ny2, pl, compress_partials(pl, st), zs));
   GPJC_TRY(dispatch3<ZPass>(pl.nz, pl, 1));
   GPJC_TRY(y_inv(pl, st));
   GPJC_HIP(hipGetLastError());

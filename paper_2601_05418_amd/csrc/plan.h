@@ -116,6 +116,13 @@ struct Plan {
   uint16_t* Aexp16[2] = {nullptr, nullptr};
   uint16_t* AH16[2] = {nullptr, nullptr};
 
+  // the bank as FP16 pairs in MFMA fragments (pair.hip), for the FP32 contractions
+  uint32_t* Ac2 = nullptr;  // compressing; Ae2 lies behind it
+  uint32_t* Ae2 = nullptr;  // expanding
+  float* wscale = nullptr;  // [B][ny] scale of W's rows, written by the readout forward; ascale and wbound lie behind it
+  float* ascale = nullptr;  // [G] power-of-two scale of a group's pairs
+  float* wbound = nullptr;  // max|psf| max|coil| / sqrt(nt), then two words of scratch and [G][8] maxima of the bank
+
   // device: workspaces
   float2* W = nullptr;      // [B][nc][ny][nt] (also holds 16-bit W)
   float2* Zp = nullptr;     // [ksplit][B][np][K][ny]
@@ -199,7 +206,22 @@ int launch_pe_cols_adj(const Plan& pl, const float2* in);
 int launch_pe_cols_normal(const Plan& pl);
 // volumes: one pass over W in place; 0 / 1 y forward / inverse, 2 / 3 z forward / inverse, 4 z normal
 int launch_pe3_cols_pass(const Plan& pl, int pass);
+// Partials of Z that launch_group_compress leaves and the phase-encode stage sums.
+int compress_partials(const Plan& pl, Store st);
 int launch_expand_bank(Plan& pl);
+// ---- FP32 contractions on FP16 pairs (pair.hip) ----
+// Whether a plan's FP32 contractions can run on them (else the FP32 MFMA forms).
+bool pair_compress_ok(const Plan& pl);
+bool pair_expand_ok(const Plan& pl);
+size_t pair_scale_floats(const Plan& pl);    // sizes of wscale with what lies behind it, Ac2, Ae2
+size_t pair_compress_words(const Plan& pl);
+size_t pair_expand_words(const Plan& pl);
+int setup_pair(Plan& pl);
+int launch_pair_bank(const Plan& pl);
+void default_pair_config(const Plan& pl, Plan::GemmCfg& g);
+int pair_partials(const Plan& pl);
+int launch_compress_pair(const Plan& pl, StageScope& sc, const void* in, float2* out);
+int launch_expand_pair(const Plan& pl, StageScope& sc);
 // Whether the staged compressing forms can address the readout-stage output
 // of a plan with this split (else it runs on the general form).
 bool compress_split_staged(const Plan& pl, Store st, int ksplit);

@@ -34,7 +34,8 @@ std::map<std::string, Choice> g_cache;
 std::set<std::string> g_loaded;
 
 const char* prec_name(Store st) {
-  return st == Store::F32 ? "fp32" : st == Store::BF16 ? "bf16" : st == Store::F16 ? "fp16" : "bf16x6";
+  // "pair-fp32": the FP16-pair shapes ("fp32" lines of a file name shapes that are gone)
+  return st == Store::F32 ? "pair-fp32" : st == Store::BF16 ? "bf16" : st == Store::F16 ? "fp16" : "bf16x6";
 }
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }

@@ -124,8 +124,10 @@ static void choose_launch(Plan& pl) {
   rows = std::min(rows, std::max(1, pl.ny * pl.nc * pl.B / 4096));
   pl.f1_rows = std::max(1, std::min(rows, pl.ny));
   // the two-pass register-FFT form where its work-group fits
-  pl.f2_threads = 256;
-  pl.f2_cb = two_pass_coils(pl.nx, pl.os, pl.nc, &pl.f2_threads);
+  const TwoPassShape two = two_pass_shape(pl.nx, pl.os, pl.nc, (long)pl.ny * pl.B);
+  pl.f2_cb = two.cb;
+  pl.f2_cpg = two.cpg;
+  pl.f2_threads = two.threads;
 
   // readout adjoint: coils transformed together (up to 2, LDS permitting),
   // and enough coil chunks for about 2048 work-groups (each chunk leaves one
@@ -139,12 +141,10 @@ static void choose_launch(Plan& pl) {
   pl.f1h_cb = cb;
   pl.f1h_cpc = cpc;
   pl.f1h_nchunk = (pl.nc + cpc - 1) / cpc;
-  // two-pass adjoint: one coil group (f2_cb coils) per work-group and partial image
-  pl.f2_adj = pl.f2_cb > 0 && (long)pl.f2_cb * pl.os * std::max(split_n1(pl.nx), pl.nx / split_n1(pl.nx)) <= pl.f2_threads &&
-              two_pass_lds_adj(pl.nx, pl.os, pl.f2_cb) * 8 <= 65536;
-  if (pl.f2_adj) {
-    pl.f1h_cpc = pl.f2_cb;
-    pl.f1h_nchunk = (pl.nc + pl.f2_cb - 1) / pl.f2_cb;
+  // two-pass adjoint: one partial image per f2_cpg chunks of f2_cb coils
+  if (pl.f2_cb > 0) {
+    const int nch = (pl.nc + pl.f2_cb - 1) / pl.f2_cb;
+    pl.f1h_nchunk = (nch + pl.f2_cpg - 1) / pl.f2_cpg;
   }
 
   const int lpb_max = std::max(1, std::min(32, (lds_f2 - pl.ny) / (2 * lsy)));

@@ -10,8 +10,8 @@
 //
 // Readout DFT: with t = q*os + s (q < Nx, s < os) and the zero padding, the
 // centred length-Nt DFT of a length-Nx line splits into os length-Nx DFTs:
-//   X[q os + s] = post[t] * FFT_Nx(u[x] * twin[s][x])[q],
-//   twin[s][x] = (-1)^x exp(-2 pi i s x / Nt),
+//   X[q os + s] = post[t] * FFT_Nx(u[x] * twin[x][s])[q],
+//   twin[x][s] = (-1)^x exp(-2 pi i s x / Nt),
 //   post[t]    = (-1)^(Nx/2) (-1)^q exp(i pi s / os) / sqrt(Nt),
 // and post[t] is folded into the PSF once per plan (psfp).
 #include <hip/hip_runtime.h>
@@ -48,7 +48,7 @@ __global__ void k_prep_tables(const float2* __restrict__ psf, float2* __restrict
     psfp[i] = make_float2((float)(v.x * pr - v.y * pi), (float)(v.x * pi + v.y * pr));
   }
   for (size_t i = gid; i < (size_t)os * nx; i += stride) {
-    const int s = (int)(i / nx), x = (int)(i % nx);
+    const int x = (int)(i / os), s = (int)(i % os);
     const long m = ((long)s * x) % nt;
     double sn, cs;
     sincospi(-2.0 * (double)m / nt, &sn, &cs);
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) void k_readout_fwd(const float2* __restrict__ 
     const int r = i / NX, x = i - r * NX;
     const float2 u = cmul(cp[i], ip[i]);
     float2* dst = bufA + r * os * LS + fpad(x);
-    for (int s = 0; s < os; ++s) dst[s * LS] = cmul(u, twin[s * NX + x]);
+    for (int s = 0; s < os; ++s) dst[s * LS] = cmul(u, twin[x * os + s]);
   }
   // PSF samples of the first row are fetched before the transform so their
   // latency overlaps it (nt <= 16 * 256 samples per row).
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void k_readout_adj(const void* __restrict__ W,
         for (int c = 0; c < ncb; ++c) {
           float2 v = make_float2(0.f, 0.f);
           const float2* rc = res + c * os * LS + fpad(x);
-          for (int s = 0; s < os; ++s) v = cadd(v, cmul(rc[s * LS], twin[s * NX + x]));
+          for (int s = 0; s < os; ++s) v = cadd(v, cmul(rc[s * LS], twin[x * os + s]));
           // v holds conj of the cropped line; acc += conj(coil) * line
           const float2 cv = coils[((size_t)(n0 + c) * ny + y) * NX + x];
           acc[e] = cadd(acc[e], cconj(cmul(v, cv)));
@@ -215,254 +215,270 @@ __global__ __launch_bounds__(256) void k_readout_adj(const void* __restrict__ W,
 // ---------------------------------------------------------------------------
 // Two-pass form of F1 (N = N1 N2, see fft2.h).  One work-group takes one
 // image row and cb coils, i.e. cb * os sub-transforms of length NX; the first
-// pass is an N1-point DFT per (coil, sub-transform, i2) in registers, the
-// second an N2-point DFT per (coil, sub-transform, k1).  The launch keeps
-// cb * os * N1 <= blockDim.x so every second-pass item has its own thread,
-// which lets results overwrite the exchange buffer after one barrier.  The
-// PSF row is read once for all cb coils; the pre-twiddle table (os x NX) is
-// read through the L1 cache, shared by all work-groups of a CU.
+// pass is an N1-point DFT per (coil, i2, sub-transform s) in registers, the
+// second an N2-point DFT per (coil, k1, s).  The launch keeps
+// cb * os * max(N1, N2) <= blockDim.x, so every item has a thread of its own.
+//
+// Items run over s fastest.  Sample t = q os + s with q = k1 + N1 k2 is
+// os N1 k2 + (k1 os + s), so for each k2 the second pass's threads hold
+// consecutive samples: they multiply by the PSF and store W straight from
+// their registers (512 bytes per wave and instruction), with no exchange back
+// to sample order.  The exchange buffer holds (i2, k1, s) with rows of RS
+// slots, RS = os (mod 32): writes (thread i2 os + s) and reads (thread k1 os +
+// s) both fall on consecutive banks.  The pre-twiddles are laid out [x][s] and
+// so read consecutively too.  PSF and pre-twiddles are read once for the work-group's cpg
+// chunks of cb coils.  Bound by the 77 MB of W that it writes (0.015 ms at
+// 5.1 TB/s) and by vector issue.  On the 224 x 224, 32-coil, os 6 slice 20 us
+// (3.9 TB/s); with the exchange to sample order, the pre-twiddles strided over
+// the threads and both tables read again for each pair of coils it took 26 us.
+// 64 x 192 rows of 192, os 5, 32 coils: 1.25 ms, before 1.75 ms.
 // ---------------------------------------------------------------------------
 __device__ inline int udiv(int a, int b) { return (int)(((float)a + 0.5f) / (float)b); }  // a < 2^16, b small
-constexpr int kPsfRegs = 8;  // readout samples per thread held in registers by k_readout_fwd2 / _adj2
-constexpr int kSetupRegs = 2;  // coil x image elements per thread and round of loads in k_readout_fwd2
+constexpr int kMaxCb = 4;      // coils per work-group at most
+constexpr int kSetupRegs = 3;  // coil x image elements per thread held in registers by k_readout_fwd2
+// row length of the exchange buffer
+__host__ __device__ inline int exch_row(int ln, int os) { return ln + (((os - ln) % 32) + 32) % 32; }
 
+// Twiddles w_NX^{i2 k1} of the exchange in LDS, [i2][k1] with rows of TS: an
+// array of its own, which the compiler can tell from the exchange buffer (else
+// each read waits for the write before it).
+constexpr int tw_row(int n1) { return (n1 + 3) / 2 * 2; }
+template <int NX>
+__device__ inline float2 load_twiddle(const float2* __restrict__ tw, int i) {
+  constexpr int N1 = Split<NX>::N1;
+  const int i2 = i / N1;
+  return tw[i2 * (i - i2 * N1)];
+}
+template <int NX>
+__device__ inline void store_twiddle(float2* twl, int i, float2 v) {
+  constexpr int N1 = Split<NX>::N1, TS = tw_row(N1);
+  twl[i / N1 * TS + i % N1] = v;
+}
 template <int NX, Store ST>
 __global__ __launch_bounds__(256) void k_readout_fwd2(const float2* __restrict__ img, const float2* __restrict__ coils,
                                                       const float2* __restrict__ psfp, const float2* __restrict__ twin,
                                                       const float2* __restrict__ tw, void* __restrict__ W, int ny,
-                                                      int nc, int os, int cb, RowScale rsc) {
+                                                      int nc, int os, int cb, int cpg, RowScale rsc) {
   using S = Split<NX>;
-  constexpr int N1 = S::N1, N2 = S::N2, AS = N1 + 1;
-  extern __shared__ float2 sm[];
+  constexpr int N1 = S::N1, N2 = S::N2, TS = tw_row(N1);
+  extern __shared__ __align__(16) float2 sm[];
+  __shared__ __align__(16) float2 twl[N2 * TS];
   __shared__ float wl1[4];
   const int tid = threadIdx.x, nthr = blockDim.x;
-  const int nt = os * NX;
-  const int y = blockIdx.x, n0 = blockIdx.y * cb, b = blockIdx.z;
-  const int ncb = min(cb, nc - n0);
-  float2* twl = sm;         // [NX]       exp(-2 pi i m / NX)
-  float2* u = twl + NX;     // [cb][NX]   coil * image
-  float2* A = u + cb * NX;  // [cb][os][N2][AS], then the output rows [cb][nt]
+  const int nt = os * NX, ln = os * N1, l1n = os * N2, RS = exch_row(ln, os);
+  const int y = blockIdx.x, b = blockIdx.z;
+  const int g0 = blockIdx.y * cpg, g1 = min((nc + cb - 1) / cb, g0 + cpg);
+  float2* u = sm;           // [cb][NX]   coil * image
+  float2* A = u + cb * NX;  // [cb][N2][RS]
   const float2* ip = img + ((size_t)b * ny + y) * NX;
-  {
-    // The set-up loads (coil and image rows, twiddles) are issued before any
-    // is used: kSetupRegs elements per thread, clamped indices; a loop takes
-    // the rest of rows longer than that (cb NX > kSetupRegs blockDim).
-    const int tot = ncb * NX;
-    float2 cv[kSetupRegs], iv[kSetupRegs];
+  // first-pass item (c1, i2, s), second-pass item (c2, k1, s)
+  const int c1 = udiv(tid, l1n), rem1 = tid - c1 * l1n;
+  const int i2 = udiv(rem1, os), sx = rem1 - i2 * os;
+  const int c2 = udiv(tid, ln), rem2 = tid - c2 * ln;
+  // coil elements i = tid + nthr k of a chunk's cb rows, and the image row under them
+  const int tot = cb * NX;
+  float2 cv[kSetupRegs], iv[kSetupRegs];
+  uint32_t ci[kSetupRegs];
+#pragma unroll
+  for (int k = 0; k < kSetupRegs; ++k) {
+    const int i = min(tid + k * nthr, tot - 1), c = i / NX, x = i - c * NX;
+    ci[k] = (uint32_t)c;
+    iv[k] = ip[x];
+  }
+  auto fetch = [&](int g) {
 #pragma unroll
     for (int k = 0; k < kSetupRegs; ++k) {
-      const int i = min(tid + k * nthr, tot - 1), c = i / NX, x = i - c * NX;
-      cv[k] = coils[((size_t)(n0 + c) * ny + y) * NX + x];
-      iv[k] = ip[x];
+      const int i = min(tid + k * nthr, tot - 1), x = i - (int)ci[k] * NX;
+      const int n = min(g * cb + (int)ci[k], nc - 1);
+      cv[k] = coils[((size_t)n * ny + y) * NX + x];
     }
-    const float2 twv = tw[min(tid, NX - 1)];
+  };
+  fetch(g0);
+  for (int i = tid; i < NX; i += nthr) store_twiddle<NX>(twl, i, load_twiddle<NX>(tw, i));
+  // pre-twiddles and PSF samples of the thread's items, for every chunk
+  float2 tpv[N1], pv[N2];
+#pragma unroll
+  for (int i1 = 0; i1 < N1; ++i1) tpv[i1] = (twin + l1n * i1)[(uint32_t)rem1];
+  const float2* ps = psfp + (size_t)y * nt;
+#pragma unroll
+  for (int k2 = 0; k2 < N2; ++k2) pv[k2] = (ps + k2 * ln)[(uint32_t)rem2];
+  if (rsc.out && g0 == 0) {
+    float l1 = 0.f;
+    for (int x = tid; x < NX; x += nthr) {
+      const float2 v = ip[x];
+      l1 += fabsf(v.x) + fabsf(v.y);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
+    if ((tid & 63) == 0) wl1[tid >> 6] = l1;
+    __syncthreads();
+    if (tid == 0) {
+      l1 = 0.f;
+      for (int w = 0; w < nthr / 64; ++w) l1 += wl1[w];
+      rsc.out[(size_t)b * ny + y] = pair_scale(l1 * *rsc.wbound);
+    }
+  }
+  const size_t coff = (size_t)c2 * ny * nt + rem2;
+  for (int g = g0; g < g1; ++g) {
+    const int ncb = min(cb, nc - g * cb);
 #pragma unroll
     for (int k = 0; k < kSetupRegs; ++k) {
       const int i = tid + k * nthr;
       if (i < tot) u[i] = cmul(cv[k], iv[k]);
     }
-    if (rsc.out && n0 == 0) {  // the first NX elements are the image row (NX <= kSetupRegs blockDim)
-      float l1 = 0.f;
-#pragma unroll
-      for (int k = 0; k < kSetupRegs; ++k)
-        if (tid + k * nthr < NX) l1 += fabsf(iv[k].x) + fabsf(iv[k].y);
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
-      if ((tid & 63) == 0) wl1[tid >> 6] = l1;
-    }
-    for (int i = tid + kSetupRegs * nthr; i < tot; i += nthr) {
+    for (int i = tid + kSetupRegs * nthr; i < ncb * NX; i += nthr) {
       const int c = i / NX, x = i - c * NX;
-      u[i] = cmul(coils[((size_t)(n0 + c) * ny + y) * NX + x], ip[x]);
+      u[i] = cmul(coils[((size_t)(g * cb + c) * ny + y) * NX + x], ip[x]);
     }
-    if (tid < NX) twl[tid] = twv;
-    for (int i = tid + nthr; i < NX; i += nthr) twl[i] = tw[i];
-  }
-  __syncthreads();
-  if (rsc.out && n0 == 0 && tid == 0)
-    rsc.out[(size_t)b * ny + y] = pair_scale((wl1[0] + wl1[1] + wl1[2] + wl1[3]) * *rsc.wbound);
-  const int items1 = ncb * os * N2;
-  for (int it = tid; it < items1; it += nthr) {
-    const int r = it / N2, i2 = it - r * N2;  // r = c * os + s
-    const int c = udiv(r, os), s = r - c * os;
-    float2 v[N1];
+    fetch(min(g + 1, g1 - 1));  // the next chunk's coils, ahead of this one's stores
+    __syncthreads();
+    if (c1 < ncb) {
+      const float2* uc = u + c1 * NX + i2;
+      const float2* t = twl + i2 * TS;
+      float2 v[N1];
 #pragma unroll
-    for (int i1 = 0; i1 < N1; ++i1) v[i1] = cmul(u[c * NX + i2 + N2 * i1], twin[s * NX + i2 + N2 * i1]);
-    rdft<N1>(v);
-    float2* dst = A + (r * N2 + i2) * AS;
-    dst[0] = v[0];
-    int m = i2;
+      for (int i1 = 0; i1 < N1; ++i1) v[i1] = cmul(uc[N2 * i1], tpv[i1]);
+      rdft<N1>(v);
+      float2* dst = A + (c1 * N2 + i2) * RS + sx;
+      dst[0] = v[0];
 #pragma unroll
-    for (int k1 = 1; k1 < N1; ++k1) {
-      dst[k1] = cmul(v[k1], twl[m]);
-      m += i2;
-      m = m >= NX ? m - NX : m;
+      for (int k1 = 1; k1 < N1; ++k1) dst[k1 * os] = cmul(v[k1], t[k1]);
     }
-  }
-  __syncthreads();
-  // The PSF samples of the output phase are loaded here, behind the second
-  // pass.  Loads and stores retire in issue order, so a load issued between
-  // the output stores could only be waited for together with them.
-  const float2* ps = psfp + (size_t)y * nt;
-  float2 pv[kPsfRegs];
+    __syncthreads();
+    if (c2 < ncb) {
+      float2 w[N2];
+      const float2* src = A + c2 * N2 * RS + rem2;
 #pragma unroll
-  for (int k = 0; k < kPsfRegs; ++k) pv[k] = ps[min(tid + k * nthr, nt - 1)];  // past the end: dropped
-  const int items2 = ncb * os * N1;
-  const bool act = tid < items2;
-  float2 w[N2];
-  int r2 = 0, k1 = 0;
-  if (act) {
-    r2 = tid / N1;
-    k1 = tid - r2 * N1;
-    const float2* src = A + r2 * N2 * AS + k1;
+      for (int j = 0; j < N2; ++j) w[j] = src[j * RS];
+      rdft<N2>(w);
+      const size_t row = (((size_t)b * nc + g * cb) * ny + y) * nt;
 #pragma unroll
-    for (int i2 = 0; i2 < N2; ++i2) w[i2] = src[i2 * AS];
-    rdft<N2>(w);
-  }
-  __syncthreads();
-  if (act) {
-    const int c = udiv(r2, os), s = r2 - c * os;
-    float2* o = A + c * nt + s;
-#pragma unroll
-    for (int k2 = 0; k2 < N2; ++k2) o[(k1 + N1 * k2) * os] = w[k2];
-  }
-  __syncthreads();
-  for (int c = 0; c < ncb; ++c) {
-    const size_t row = (((size_t)b * nc + n0 + c) * ny + y) * nt;
-    const float2* ar = A + c * nt;
-#pragma unroll
-    for (int k = 0; k < kPsfRegs; ++k) {
-      const int t = tid + k * nthr;
-      if (t < nt) store_c<ST>(W, row + t, cmul(pv[k], ar[t]));
+      for (int k2 = 0; k2 < N2; ++k2) store_c<ST>(W, row + k2 * ln + coff, cmul(pv[k2], w[k2]));
     }
-  }
-  for (int t = tid + kPsfRegs * nthr; t < nt; t += nthr) {
-    const float2 p = ps[t];
-    for (int c = 0; c < ncb; ++c)
-      store_c<ST>(W, (((size_t)b * nc + n0 + c) * ny + y) * nt + t, cmul(p, A[c * nt + t]));
   }
 }
 
-// Two-pass form of F1^H: one work-group per image row and cb coils, leaving
-// one partial image per coil group.  The inputs conj(psf) w are scattered to
-// sub-transform rows (padded to os (mod 32) slots so consecutive samples land
-// on consecutive banks); the inverse DFT of length NX per sub-transform is
-// taken as conj(FFT(conj(.))) with the two passes of the forward form; the
-// sum over sub-transforms of the pre-twiddled results and the coil
-// combination follow.  Pre-twiddles are read from the (L1-resident) table.
-// Grid (kAdjRowBlock x chunks, row blocks, B): the chunks of kAdjRowBlock
-// consecutive rows are consecutive work-groups, so they find each row's PSF
-// in L2 (sweeping all rows of one chunk after another took a volume's PSF,
-// Nz Ny Nt samples, from HBM once per chunk), while the W rows read at one
-// time stay kAdjRowBlock consecutive rows of each coil.
-constexpr int kAdjRowBlock = 16;
+// Two-pass form of F1^H: one work-group per image row and cpg chunks of cb
+// coils, leaving one partial image per work-group's coils.  As in the forward
+// form the first pass (N1-point, over q = i2 + N2 i1) takes its samples
+// os N2 i1 + (i2 os + s) straight from W, consecutive over the threads, and the
+// PSF samples and pre-twiddles stay in registers over the chunks; the inverse
+// DFT of length NX per sub-transform is conj(FFT(conj(.))).  The pre-twiddled
+// results go back to the slots of the exchange buffer that the same thread
+// read, and thread x sums the os of them, beginning at s = k1 mod os so that
+// neighbouring threads read neighbouring slots.
+// Bound like the forward form, by the 77 MB of W that it reads and vector issue.
+// 224 x 224, 32 coils, os 6: 26 us (3 TB/s), before 29.8 us; 64 x 192 rows of
+// 192: 1.27 ms, before 1.70 ms; eight rows-of-256 images, os 8, 16 coils: 0.28
+// ms, before 0.37 ms.
 template <int NX, Store ST>
 __global__ __launch_bounds__(256) void k_readout_adj2(const void* __restrict__ W, const float2* __restrict__ coils,
                                                       const float2* __restrict__ psfp, const float2* __restrict__ twin,
                                                       const float2* __restrict__ tw, float2* __restrict__ part, int ny,
-                                                      int nc, int os, int cb, int B) {
+                                                      int nc, int os, int cb, int cpg, int B) {
   using S = Split<NX>;
-  constexpr int N1 = S::N1, N2 = S::N2, AS = N1 + 1;
-  extern __shared__ float2 sm[];
+  constexpr int N1 = S::N1, N2 = S::N2, TS = tw_row(N1);
+  constexpr int AX = 2;  // image elements per thread (the launch has at least NX / 2 threads)
+  extern __shared__ __align__(16) float2 X[];  // [cb][N2][RS]
+  __shared__ __align__(16) float2 twl[N2 * TS];
   const int tid = threadIdx.x, nthr = blockDim.x;
-  const int nt = os * NX;
-  const int nxp = NX + ((os - NX % 32) % 32 + 32) % 32;
-  const int y = blockIdx.y * kAdjRowBlock + blockIdx.x % kAdjRowBlock;
-  const int chunk = blockIdx.x / kAdjRowBlock, b = blockIdx.z;
-  if (y >= ny) return;  // the last row block's spare work-groups
-  const int n0 = chunk * cb, ncb = min(cb, nc - n0);
-  float2* twl = sm;       // [NX]
-  float2* X = twl + NX;   // [cb][os][nxp] inputs, then [cb][os][N2][AS], then [cb][os][NX] results
-  const float2 twv = tw[min(tid, NX - 1)];  // stored below, behind the sample loads
+  const int nt = os * NX, ln = os * N1, l1n = os * N2, RS = exch_row(ln, os);
+  const int y = blockIdx.x, b = blockIdx.z;
+  const int g0 = blockIdx.y * cpg, g1 = min((nc + cb - 1) / cb, g0 + cpg);
+  const int c1 = udiv(tid, l1n), rem1 = tid - c1 * l1n;
+  const int i2 = udiv(rem1, os), sx = rem1 - i2 * os;
+  const int c2 = udiv(tid, ln), rem2 = tid - c2 * ln;
+  const size_t coff = (size_t)c1 * ny * nt + rem1;
+  float2 v[N1], pv[N1], tpv[N2];
+  // a chunk's samples; threads past its last coil read the coil before it
+  auto fetch = [&](int g) {
+    const int n0 = g * cb, back = max(0, n0 + c1 - (nc - 1));
+    const size_t at = (((size_t)b * nc + n0) * ny + y) * nt + coff - (size_t)back * ny * nt;
+#pragma unroll
+    for (int i1 = 0; i1 < N1; ++i1) v[i1] = load_c<ST>(W, at + i1 * l1n);
+  };
+  fetch(g0);
   const float2* ps = psfp + (size_t)y * nt;
-  // kPsfRegs samples per thread and coil are loaded before any is used, so
-  // that many loads are in flight instead of one sample's.  Samples past the
-  // row end load the last sample (no branch around a load) and are dropped.
-  float2 pv[kPsfRegs];
-  int xo[kPsfRegs];  // LDS slot (s, q) of sample t, without the coil offset
 #pragma unroll
-  for (int k = 0; k < kPsfRegs; ++k) {
-    const int t = tid + k * nthr;
-    const int q = udiv(t, os), s = t - q * os;
-    pv[k] = ps[min(t, nt - 1)];
-    xo[k] = s * nxp + q;
-  }
-  for (int c = 0; c < ncb; ++c) {
-    const size_t row = (((size_t)b * nc + n0 + c) * ny + y) * nt;
-    float2 wv[kPsfRegs];
+  for (int i1 = 0; i1 < N1; ++i1) pv[i1] = (ps + i1 * l1n)[(uint32_t)rem1];
 #pragma unroll
-    for (int k = 0; k < kPsfRegs; ++k) wv[k] = load_c<ST>(W, row + min(tid + k * nthr, nt - 1));
+  for (int k2 = 0; k2 < N2; ++k2) tpv[k2] = (twin + ln * k2)[(uint32_t)rem2];
+  for (int i = tid; i < NX; i += nthr) store_twiddle<NX>(twl, i, load_twiddle<NX>(tw, i));
+  float2 acc[AX];
 #pragma unroll
-    for (int k = 0; k < kPsfRegs; ++k)
-      if (tid + k * nthr < nt) X[c * os * nxp + xo[k]] = cmulc(pv[k], wv[k]);
-  }
-  for (int t = tid + kPsfRegs * nthr; t < nt; t += nthr) {
-    const int q = udiv(t, os), s = t - q * os;
-    const float2 p = ps[t];
-    for (int c = 0; c < ncb; ++c)
-      X[(c * os + s) * nxp + q] = cmulc(p, load_c<ST>(W, (((size_t)b * nc + n0 + c) * ny + y) * nt + t));
-  }
-  if (tid < NX) twl[tid] = twv;
-  for (int i = tid + nthr; i < NX; i += nthr) twl[i] = tw[i];
+  for (int h = 0; h < AX; ++h) acc[h] = make_float2(0.f, 0.f);
   __syncthreads();
-  const int items1 = ncb * os * N2;  // <= blockDim.x
-  float2 v[N1];
-  int r1 = 0, i2 = 0;
-  const bool act1 = tid < items1;
-  if (act1) {
-    r1 = tid / N2;
-    i2 = tid - r1 * N2;
+  for (int g = g0; g < g1; ++g) {
+    const int ncb = min(cb, nc - g * cb);
+    if (c1 < ncb) {
 #pragma unroll
-    for (int i1 = 0; i1 < N1; ++i1) v[i1] = X[r1 * nxp + i2 + N2 * i1];
-  }
-  __syncthreads();
-  if (act1) {
-    rdft<N1>(v);
-    float2* dst = X + (r1 * N2 + i2) * AS;
-    dst[0] = v[0];
-    int m = i2;
+      for (int i1 = 0; i1 < N1; ++i1) v[i1] = cmulc(pv[i1], v[i1]);  // conj(conj(psf) w)
+      const float2* t = twl + i2 * TS;
+      rdft<N1>(v);
+      float2* dst = X + (c1 * N2 + i2) * RS + sx;
+      dst[0] = v[0];
 #pragma unroll
-    for (int k1 = 1; k1 < N1; ++k1) {
-      dst[k1] = cmul(v[k1], twl[m]);
-      m += i2;
-      m = m >= NX ? m - NX : m;
+      for (int k1 = 1; k1 < N1; ++k1) dst[k1 * os] = cmul(v[k1], t[k1]);
     }
-  }
-  __syncthreads();
-  const int items2 = ncb * os * N1;  // <= blockDim.x
-  float2 w[N2];
-  int r2 = 0, k1 = 0;
-  const bool act2 = tid < items2;
-  if (act2) {
-    r2 = tid / N1;
-    k1 = tid - r2 * N1;
-    const float2* src = X + r2 * N2 * AS + k1;
+    __syncthreads();
+    if (c2 < ncb) {
+      // the inverse sub-transform is conj(w); keep twin * w, whose sum over s is
+      // the conjugate of the pre-twiddled sum
+      float2 w[N2];
+      float2* row = X + c2 * N2 * RS + rem2;
 #pragma unroll
-    for (int j = 0; j < N2; ++j) w[j] = src[j * AS];
-    rdft<N2>(w);
-  }
-  __syncthreads();
-  if (act2) {
-    // the inverse sub-transform is conj(w); keep twin * w, whose sum over s is
-    // the conjugate of the pre-twiddled sum
-    const int s = r2 - udiv(r2, os) * os;
-    float2* o = X + r2 * NX;
-    const float2* tws = twin + s * NX;
+      for (int j = 0; j < N2; ++j) w[j] = row[j * RS];
+      rdft<N2>(w);
 #pragma unroll
-    for (int k2 = 0; k2 < N2; ++k2) {
-      const int x = k1 + N1 * k2;
-      o[x] = cmul(w[k2], tws[x]);
+      for (int k2 = 0; k2 < N2; ++k2) row[k2 * RS] = cmul(w[k2], tpv[k2]);
     }
+    // The sums' coil values and the next chunk's samples are fetched here, not
+    // before the second pass: the registers they would hold through it cost a
+    // quarter of the occupancy.
+    float2 cv[AX][kMaxCb];
+#pragma unroll
+    for (int c = 0; c < kMaxCb; ++c)
+      if (c < cb) {
+        const float2* cp = coils + ((size_t)min(g * cb + c, nc - 1) * ny + y) * NX;
+#pragma unroll
+        for (int h = 0; h < AX; ++h) cv[h][c] = cp[min(tid + h * nthr, NX - 1)];
+      }
+    fetch(min(g + 1, g1 - 1));
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < AX; ++h) {
+      const int x = tid + h * nthr;
+      if (x < NX) {
+        const int k2 = x / N1, k1 = x - k2 * N1;
+        const int first = k1 - udiv(k1, os) * os;
+#pragma unroll
+        for (int c = 0; c < kMaxCb; ++c) {
+          if (c >= ncb) break;
+          const float2* r = X + (c * N2 + k2) * RS + k1 * os;
+          float2 sum = make_float2(0.f, 0.f);
+          int s = first;
+          for (int s0 = 0; s0 < os; s0 += 4) {
+            float2 q[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              q[e] = r[s];
+              s = s + 1 < os ? s + 1 : 0;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (s0 + e < os) sum = cadd(sum, q[e]);
+          }
+          acc[h] = cadd(acc[h], cconj(cmul(sum, cv[h][c])));
+        }
+      }
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  float2* pp = part + (((size_t)chunk * B + b) * ny + y) * NX;
-  for (int x = tid; x < NX; x += nthr) {
-    float2 acc = make_float2(0.f, 0.f);
-    for (int c = 0; c < ncb; ++c) {
-      float2 v2 = make_float2(0.f, 0.f);
-      for (int s = 0; s < os; ++s) v2 = cadd(v2, X[(c * os + s) * NX + x]);
-      acc = cadd(acc, cconj(cmul(v2, coils[((size_t)(n0 + c) * ny + y) * NX + x])));
-    }
-    pp[x] = acc;
+  float2* pp = part + (((size_t)blockIdx.y * B + b) * ny + y) * NX;
+#pragma unroll
+  for (int h = 0; h < AX; ++h) {
+    const int x = tid + h * nthr;
+    if (x < NX) pp[x] = acc[h];
   }
 }
 
@@ -965,28 +981,47 @@ __global__ __launch_bounds__(256) void k_cols2(float2* __restrict__ W, size_t ps
 // ---------------------------------------------------------------------------
 size_t two_pass_lds_fwd(int nx, int os, int cb) {
   const int n1 = split_n1(nx), n2 = nx / n1;
-  const size_t a = (size_t)cb * os * n2 * (n1 + 1), o = (size_t)cb * os * nx;
-  return (size_t)nx + (size_t)cb * nx + (a > o ? a : o);
+  return (size_t)cb * nx + (size_t)cb * n2 * exch_row(os * n1, os);
 }
 size_t two_pass_lds_adj(int nx, int os, int cb) {
   const int n1 = split_n1(nx), n2 = nx / n1;
-  const size_t in = (size_t)nx + ((os - nx % 32) % 32 + 32) % 32, ex = (size_t)n2 * (n1 + 1);
-  return (size_t)nx + (size_t)cb * os * (in > ex ? in : ex);
+  return (size_t)cb * n2 * exch_row(os * n1, os);
 }
-// Coils per work-group of the two-pass forward form (0 = not applicable):
-// every second-pass item needs its own thread (at most 256) and the LDS must
-// fit in 64 KiB.
-int two_pass_coils(int nx, int os, int nc, int* threads) {
+// Work-group shape of the two-pass readout forms: coils per chunk (0: not
+// applicable) with every item of both passes on its own thread (at most 256)
+// and the LDS within 64 KiB; at most kMaxCb, and fewer while the launch has less
+// than a work-group per CU.
+TwoPassShape two_pass_shape(int nx, int os, int nc, long rows) {
+  TwoPassShape r;
   const int n1 = split_n1(nx), n2 = nx / n1;
-  if (n1 <= 1 || n2 <= 1 || n2 > 32) return 0;
-  for (int cb = std::min(nc, 4); cb >= 1; --cb) {
-    const int items = cb * os * std::max(n1, n2);
-    if (items > 256) continue;
-    if (two_pass_lds_fwd(nx, os, cb) * 8 > 65536) continue;
-    *threads = 256;  // the load, scatter and output phases take every thread (measured faster than items)
-    return cb;
+  if (n1 <= 1 || n2 <= 1 || n2 > 32) return r;
+  auto fits = [&](int cb) {
+    return cb * os * std::max(n1, n2) <= 256 && (two_pass_lds_fwd(nx, os, cb) + n2 * tw_row(n1)) * 8 + 64 <= 65536;
+  };
+  int cb = std::min(nc, kMaxCb);
+  while (cb > 0 && !fits(cb)) --cb;
+  if (cb == 0) return r;
+  while (cb > 1 && rows * ((nc + cb - 1) / cb) < 256) cb /= 2;
+  r.cb = cb;
+  r.threads = (std::max(cb * os * std::max(n1, n2), nx / 2) + 63) / 64 * 64;
+  // Chunks per work-group: the first loads of a work-group (PSF, pre-twiddles)
+  // cost about 0.9 chunks, and 12 waves of the adjoint are resident per CU, so
+  // rounds of 256 * 12 waves, the last one half empty, times chunks.  Measured
+  // (forward / adjoint, us) for 1, 2, 4, 8 chunks: 224 rows, 16 chunks of two
+  // coils, os 6: 25.5 / 34.4, 21.7 / 29.8, 18.7 / 24.7, 21.7 / 32.6; 8 x 256
+  // rows, os 8: 251 / 340, 203 / 260, 183 / 231, 189 / 211.
+  const int nch = (nc + cb - 1) / cb;
+  const double slots = 256.0 * 12 / (r.threads / 64);
+  double best = 1e30;
+  for (int cpg = 1; cpg <= nch; ++cpg) {
+    const double rounds = rows * ((nch + cpg - 1) / cpg) / slots;
+    const double cost = (rounds <= 1.0 ? 1.0 : rounds + 0.5) * (cpg + 0.9);
+    if (cost < best) {
+      best = cost;
+      r.cpg = cpg;
+    }
   }
-  return 0;
+  return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -1020,9 +1055,10 @@ struct ReadoutFwd {
       if constexpr (Split<NX>::ok) {
         if (pl.f2_cb > 0) {
           const size_t lds = two_pass_lds_fwd(NX, pl.os, pl.f2_cb) * sizeof(float2);
-          dim3 grid(pl.ny, (pl.nc + pl.f2_cb - 1) / pl.f2_cb, pl.B);
+          const int nch = (pl.nc + pl.f2_cb - 1) / pl.f2_cb;
+          dim3 grid(pl.ny, (nch + pl.f2_cpg - 1) / pl.f2_cpg, pl.B);
           sc.launch(k_readout_fwd2<NX, ST>, grid, dim3(pl.f2_threads), lds, pl.stream, img, pl.coils, pl.psfp,
-                    pl.twin, pl.tw_x, (void*)pl.W, pl.ny, pl.nc, pl.os, pl.f2_cb, rsc);
+                    pl.twin, pl.tw_x, (void*)pl.W, pl.ny, pl.nc, pl.os, pl.f2_cb, pl.f2_cpg, rsc);
           GPJC_HIP(hipGetLastError());
           return GPJC_OK;
         }
@@ -1045,11 +1081,11 @@ struct ReadoutAdj {
     static int run(const Plan& pl) {
       StageScope sc(pl, GPJC_STAGE_READOUT_ADJ, true);
       if constexpr (Split<NX>::ok) {
-        if (pl.f2_adj) {
+        if (pl.f2_cb > 0) {
           const size_t lds = two_pass_lds_adj(NX, pl.os, pl.f2_cb) * sizeof(float2);
-          const dim3 grid(kAdjRowBlock * pl.f1h_nchunk, (pl.ny + kAdjRowBlock - 1) / kAdjRowBlock, pl.B);
+          const dim3 grid(pl.ny, pl.f1h_nchunk, pl.B);
           sc.launch(k_readout_adj2<NX, ST>, grid, dim3(pl.f2_threads), lds, pl.stream, (const void*)pl.W, pl.coils,
-                    pl.psfp, pl.twin, pl.tw_x, pl.part, pl.ny, pl.nc, pl.os, pl.f2_cb, pl.B);
+                    pl.psfp, pl.twin, pl.tw_x, pl.part, pl.ny, pl.nc, pl.os, pl.f2_cb, pl.f2_cpg, pl.B);
           GPJC_HIP(hipGetLastError());
           return GPJC_OK;
         }

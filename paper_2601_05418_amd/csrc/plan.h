@@ -60,8 +60,8 @@ struct Plan {
   // launch configuration
   int f1_rows = 1;          // image rows per readout-forward workgroup
   int f2_cb = 0;            // coils per work-group of the two-pass readout forward (0 = Stockham form)
+  int f2_cpg = 1;           // coil chunks (of f2_cb) that a work-group of the two-pass readout forms takes in turn
   int f2_threads = 256;     // threads per work-group of the two-pass readout forms
-  bool f2_adj = false;      // the adjoint uses the two-pass form too (one coil group per work-group)
   int f1h_cb = 1;           // coils transformed together in the readout adjoint
   int f1h_nchunk = 1;       // coil chunks (partial images) in the readout adjoint
   int f1h_cpc = 1;          // coils per chunk
@@ -99,7 +99,7 @@ struct Plan {
   float2* coils = nullptr;  // [nc][ny][nx]
   float2* psf = nullptr;    // [ny][nt] as given
   float2* psfp = nullptr;   // [ny][nt] psf times the readout post-twiddle
-  float2* twin = nullptr;   // [os][nx] readout pre-twiddle
+  float2* twin = nullptr;   // [nx][os] readout pre-twiddle
   float2* tw_x = nullptr;   // [nx] exp(-2 pi i m / nx)
   float2* tw_y = nullptr;   // [ny]
   int* lines = nullptr;     // [ms]
@@ -327,7 +327,10 @@ size_t explicit_bytes(int nx, int ny, int np, int K);
 // Sizing of the two-pass readout forms (operator.hip).
 size_t two_pass_lds_fwd(int nx, int os, int cb);
 size_t two_pass_lds_adj(int nx, int os, int cb);
-int two_pass_coils(int nx, int os, int nc, int* threads);
+struct TwoPassShape {
+  int cb = 0, cpg = 1, threads = 256;
+};
+TwoPassShape two_pass_shape(int nx, int os, int nc, long rows);
 
 // Lengths the FFT kernels are instantiated for.
 bool fft_size_supported(int n);

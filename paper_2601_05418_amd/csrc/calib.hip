@@ -462,7 +462,6 @@ int alloc_calib(Scratch& s, const Plan& pl, bool whiten, CalibBufs& b) {
   GPJC_TRY(s.alloc(&t.bounds, (size_t)G * 3));
   GPJC_TRY(s.alloc(&t.e, gn));
   GPJC_TRY(s.alloc(&t.vb, 2 * gn));
-  GPJC_TRY(s.alloc(&t.wb, gn));
   GPJC_TRY(s.alloc(&t.pb, gn));
   GPJC_TRY(s.alloc(&t.cb, gn));
   GPJC_TRY(s.alloc(&t.ph, gn));

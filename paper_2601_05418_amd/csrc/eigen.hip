@@ -667,7 +667,9 @@ __global__ __launch_bounds__(kTT) void k_invit_orth(int n, int K, const double* 
 // elements tid + 256 q, q < Q): z = D y, then z <- P_k z for k = n-2 .. 0,
 // P_k z = z - tau_k v_k (v_k^H z) on indices > k, v_k read from row k of H
 // (the next row loaded while the current one is applied).  One barrier per
-// reflector (the reduction slots alternate).  Writes U[g][r][.], the
+// reflector (the reduction slots alternate).  A serial chain of n - 1 short
+// steps: 42 matrices of 1024, 64 vectors each, 3.3 ms; with six exchanges over the
+// lanes for each of the VB products, instead of wave_sums', 6.2 ms.  Writes U[g][r][.], the
 // eigenvector of the (r + 1)-th largest eigenvalue.
 template <int Q, int VB>
 __global__ __launch_bounds__(kTT) void k_tri_back(const double2* __restrict__ H, int ld, int n, int K,
@@ -705,19 +707,15 @@ __global__ __launch_bounds__(kTT) void k_tri_back(const double2* __restrict__ H,
     load_row(k - 1, vn);
     const double tk = tau[gn + k];
     if (tk == 0.0) continue;  // uniform across the block
+    double2 s[VB];
 #pragma unroll
     for (int c = 0; c < VB; ++c) {
-      double2 s = make_double2(0.0, 0.0);
+      s[c] = make_double2(0.0, 0.0);
 #pragma unroll
-      for (int q = 0; q < Q; ++q) s = zadd(s, zcmul(v[q], z[c][q]));
-      double a = s.x, b = s.y;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        a += __shfl_down(a, o, 64);
-        b += __shfl_down(b, o, 64);
-      }
-      if (lane == 0) red[slot][wv][c] = make_double2(a, b);
+      for (int q = 0; q < Q; ++q) s[c] = zadd(s[c], zcmul(v[q], z[c][q]));
     }
+    const double2 sum = wave_sums<VB, 32>(s, lane);
+    if (lane % (64 / VB) == 0) red[slot][wv][lane / (64 / VB)] = sum;
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < VB; ++c) {

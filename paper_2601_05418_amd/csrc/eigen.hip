@@ -25,8 +25,8 @@
 // 4. Eigenvectors of the K largest by inverse iteration on the real
 //    tridiagonal (LU with partial pivoting, a fixed pseudo-random start),
 //    each iterate orthogonalised against the earlier vectors of its cluster
-//    (eigenvalues closer than 1e-3 ||T||) in eigenvalue order, as LAPACK's
-//    stein does; the last iterate's residual ||T y - lambda y|| is checked.
+//    (neighbouring eigenvalues closer than 1e-3 ||T||) in eigenvalue order, as
+//    LAPACK's stein does, here by classical Gram-Schmidt applied twice; the last iterate's residual ||T y - lambda y|| is checked.
 // 5. Back-transformation u = P_0 P_1 ... P_{n-2} D y.
 #include <hip/hip_runtime.h>
 
@@ -614,50 +614,97 @@ __global__ __launch_bounds__(64) void k_invit_solve(int n, int K, int G, const d
   }
 }
 
-// One work-group per matrix: in eigenvalue order, orthogonalise vector r
-// against the earlier vectors of its cluster (modified Gram-Schmidt) and
-// normalise it.  last: also check the residual ||T y - lambda y|| <=
-// 1e-9 ||T|| (flag on failure or a non-finite value).
-__global__ __launch_bounds__(kTT) void k_invit_orth(int n, int K, const double* __restrict__ d,
-                                                    const double* __restrict__ f, const double* __restrict__ eig,
-                                                    const double* __restrict__ bounds, double* __restrict__ x,
-                                                    int last, int* __restrict__ flag) {
-  __shared__ double sh[4];
-  const int g = blockIdx.x, tid = threadIdx.x;
+// out[g][c][r] = in[g][r][c], through 32 x 32 tiles in LDS.  The solves want the
+// vectors side by side (a thread per vector), the orthogonalisation one after the
+// other.
+__global__ __launch_bounds__(256) void k_transpose(const double* __restrict__ in, int R, int C,
+                                                   double* __restrict__ out) {
+  __shared__ double t[32][33];
+  const size_t base = (size_t)blockIdx.z * R * C;
+  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+#pragma unroll
+  for (int h = 0; h < 32; h += 8)
+    if (r0 + ty + h < R && c0 + tx < C) t[ty + h][tx] = in[base + (size_t)(r0 + ty + h) * C + c0 + tx];
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 32; h += 8)
+    if (c0 + ty + h < C && r0 + tx < R) out[base + (size_t)(c0 + ty + h) * R + r0 + tx] = t[tx][ty + h];
+}
+
+// One work-group per matrix, vectors x [G][K][n]: in eigenvalue order,
+// orthogonalise vector r against the earlier vectors of its cluster (classical
+// Gram-Schmidt, twice: all products at once, a wave each, then all
+// subtractions, a thread per element) and normalise it.  last: also check the
+// residual ||T y - lambda y|| <= 1e-9 ||T|| (flag on failure or a non-finite
+// value).  A serial chain over the vectors, 2 x 4 accesses of the cluster each:
+// 42 matrices of 1024, 64 vectors, 0.55 ms; product by product with the vectors
+// side by side (strided reads, two barriers per pair) 2.85 ms.
+constexpr int kOrthThreads = 1024;
+__global__ __launch_bounds__(kOrthThreads) void k_invit_orth(int n, int K, const double* __restrict__ d,
+                                                             const double* __restrict__ f,
+                                                             const double* __restrict__ eig,
+                                                             const double* __restrict__ bounds, double* __restrict__ x,
+                                                             int last, int* __restrict__ flag) {
+  constexpr int kWaves = kOrthThreads / 64;
+  __shared__ double xs[kMaxN], pr[kMaxN], sh[2][kWaves];
+  const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const size_t gn = (size_t)g * n;
   const double nrm = fmax(bounds[3 * g + 2], DBL_MIN);
   const double ctol = 1e-3 * nrm;
+  auto total = [&](double v, double* slot) {  // sum over the work-group
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (lane == 0) slot[wv] = v;
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) s += slot[w];
+    return s;
+  };
   int cs = 0;  // first vector of the current cluster
   for (int r = 0; r < K; ++r) {
     if (r > 0 && eig[gn + r - 1] - eig[gn + r] > ctol) cs = r;
-    for (int q = cs; q < r; ++q) {
-      double s = 0.0;
-      for (int i = tid; i < n; i += kTT) s += x[vidx(g, i, q, n, K)] * x[vidx(g, i, r, n, K)];
-      s = bsum(s, sh);
-      for (int i = tid; i < n; i += kTT) x[vidx(g, i, r, n, K)] -= s * x[vidx(g, i, q, n, K)];
+    double* xr = x + ((size_t)g * K + r) * n;
+    const double* xc = x + ((size_t)g * K + cs) * n;
+    for (int i = tid; i < n; i += kOrthThreads) xs[i] = xr[i];
+    __syncthreads();
+    for (int pass = 0; pass < 2 && cs < r; ++pass) {
+      for (int q = wv; q < r - cs; q += kWaves) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int i = lane; i < n; i += 64) s += xc[(size_t)q * n + i] * xs[i];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (lane == 0) pr[q] = s;
+      }
+      __syncthreads();
+      for (int i = tid; i < n; i += kOrthThreads) {
+        double v = xs[i];
+#pragma unroll 8
+        for (int q = 0; q < r - cs; ++q) v -= pr[q] * xc[(size_t)q * n + i];
+        xs[i] = v;
+      }
       __syncthreads();
     }
     double s = 0.0;
-    for (int i = tid; i < n; i += kTT) {
-      const double v = x[vidx(g, i, r, n, K)];
-      s += v * v;
-    }
-    s = bsum(s, sh);
+    for (int i = tid; i < n; i += kOrthThreads) s += xs[i] * xs[i];
+    s = total(s, sh[0]);
     const double inv = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
-    for (int i = tid; i < n; i += kTT) x[vidx(g, i, r, n, K)] *= inv;
-    __syncthreads();
     if (last) {
       const double lam = eig[gn + r];
       double res = 0.0;
-      for (int i = tid; i < n; i += kTT) {
-        double t = (d[gn + i] - lam) * x[vidx(g, i, r, n, K)];
-        if (i >= 1) t += f[gn + i - 1] * x[vidx(g, i - 1, r, n, K)];
-        if (i + 1 < n) t += f[gn + i] * x[vidx(g, i + 1, r, n, K)];
+      for (int i = tid; i < n; i += kOrthThreads) {
+        double t = (d[gn + i] - lam) * xs[i];
+        if (i >= 1) t += f[gn + i - 1] * xs[i - 1];
+        if (i + 1 < n) t += f[gn + i] * xs[i + 1];
+        t *= inv;
         res += t * t;
       }
-      res = bsum(res, sh);
+      res = total(res, sh[1]);
       if (tid == 0 && (!(s > 0.0) || !isfinite(s) || !(sqrt(res) <= 1e-9 * nrm))) *flag = 1;
     }
+    for (int i = tid; i < n; i += kOrthThreads) xr[i] = xs[i] * inv;
+    __syncthreads();
   }
 }
 
@@ -686,7 +733,7 @@ __global__ __launch_bounds__(kTT) void k_tri_back(const double2* __restrict__ H,
     const int i = tid + kTT * q;
     const double2 p = i < n ? ph[gn + i] : make_double2(0.0, 0.0);
 #pragma unroll
-    for (int c = 0; c < VB; ++c) z[c][q] = (i < n && c < nv) ? zscale(p, y[vidx(g, i, r0 + c, n, K)]) : p;
+    for (int c = 0; c < VB; ++c) z[c][q] = (i < n && c < nv) ? zscale(p, y[((size_t)g * K + r0 + c) * n + i]) : p;
   }
   const double2* A = H + (size_t)g * ld * ld;
   const int lane = tid & 63, wv = tid >> 6;
@@ -782,14 +829,19 @@ int tri_eigen(hipStream_t st, double2* H, int ld, int n, int G, int K, const Tri
     const int v = std::atoi(s);
     if (v >= 0 && v <= 8 && s[0] >= '0' && s[0] <= '9') iters = v;
   }
+  // solves on the vectors side by side ([G][n][K], in U), orthogonalisation one
+  // after the other ([G][K][n], in x)
   const dim3 gv((K + 63) / 64, G);
+  double* xs = reinterpret_cast<double*>(b.U);
   hipLaunchKernelGGL(k_invit_factor, gv, dim3(64), 0, st, b.d, b.f, n, K, b.eig, b.bounds, b.lm, b.u0, b.u1, b.u2,
-                     b.sw, b.x);
-  for (int it = 0; it < std::max(iters, 1); ++it) {
-    if (it < iters)
-      hipLaunchKernelGGL(k_invit_solve, gv, dim3(64), 0, st, n, K, G, b.lm, b.u0, b.u1, b.u2, b.sw, b.x);
-    hipLaunchKernelGGL(k_invit_orth, dim3(G), dim3(kTT), 0, st, n, K, b.d, b.f, b.eig, b.bounds, b.x,
-                       it == std::max(iters, 1) - 1 ? 1 : 0, flag);
+                     b.sw, xs);
+  const int tn = (n + 31) / 32, tk = (K + 31) / 32, rounds = std::max(iters, 1);
+  for (int it = 0; it < rounds; ++it) {
+    if (it < iters) hipLaunchKernelGGL(k_invit_solve, gv, dim3(64), 0, st, n, K, G, b.lm, b.u0, b.u1, b.u2, b.sw, xs);
+    hipLaunchKernelGGL(k_transpose, dim3(tk, tn, G), dim3(256), 0, st, xs, n, K, b.x);
+    hipLaunchKernelGGL(k_invit_orth, dim3(G), dim3(kOrthThreads), 0, st, n, K, b.d, b.f, b.eig, b.bounds, b.x,
+                       it == rounds - 1 ? 1 : 0, flag);
+    if (it + 1 < rounds) hipLaunchKernelGGL(k_transpose, dim3(tn, tk, G), dim3(256), 0, st, b.x, K, n, xs);
   }
   GPJC_HIP(hipGetLastError());
   // back-transformation: elements per thread Q = ceil(n / 256), 8 vectors per

@@ -251,7 +251,7 @@ struct TriEigBufs {
   double *d, *tau, *f, *f2, *eig, *bounds;  // [G][n] each (bounds [G][3]); eig: every eigenvalue, descending
   double2 *e, *vb, *pb, *cb, *ph, *pd; // [G][n] each (vb [2][G][n])
   double2* pt;                              // [G][ceil(n / 16)][n]
-  double *lm, *u0, *u1, *u2, *x;            // [G][n][K] each
+  double *lm, *u0, *u1, *u2, *x;            // [G][n][K] each (x: eigenvectors of T, [G][K][n])
   unsigned char* sw;                        // [G][n][K]
   double2* U;                               // [G][K][n]: eigenvectors of the K largest eigenvalues
 };

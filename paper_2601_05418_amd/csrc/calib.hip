@@ -197,72 +197,115 @@ __global__ __launch_bounds__(256) void k_gram_q(const double2* __restrict__ cw, 
     if (ok[q]) Q[(((size_t)n * nc + om[q]) * ny + iy) * nd + od[q]] = acc[q];
 }
 
-// k_gram_assemble: the block (n, m), m >= n, of P_g; the block (m, n) is its
-// conjugate transpose.  Work-group: one coil pair, one group and a tile of
-// 4 * 256 outputs (j, k); rows iy are staged ay at a time in LDS (the
-// q-weighted PSF samples of the patch, the plain ones, and Q_nm).
-constexpr int kAO = 4;  // outputs per thread
-
-__global__ __launch_bounds__(256) void k_gram_assemble(const double2* __restrict__ Q, const float2* __restrict__ psf,
-                                                       const double* __restrict__ qinv, const int* __restrict__ t0s,
-                                                       double2* __restrict__ H, int nc, int P, int ny, int nt, int nsp,
-                                                       int ntile, int ay) {
-  const int n = blockIdx.x, m = blockIdx.y;
-  if (m < n) return;
-  const int g = blockIdx.z / ntile, tile = blockIdx.z - g * ntile;
-  const int nd = 2 * P - 1, t0 = t0s[g];
+// k_gram_assemble: the blocks (m, n), m >= n, of P_g,
+//   P_g[(m, k)][(n, j)] = conj(sum_iy q_g psf_j conj(psf_k) Q_nm(iy, j - k))
+// (the eigensolver reads the lower triangle only).  Work-group: PB coil pairs
+// and one group; a thread takes four elements of a diagonal, which share
+// Q_nm(iy, j - k), for all pairs, which share the four PSF products.  Threads run
+// along j, so rows of P_g are written contiguously.  Rows iy are staged ay at a
+// time in LDS.  Where a thread's diagonal leaves the block it stores nothing; with
+// four pairs the staged rows are padded with zeros there, so that all addresses
+// are one base plus constants (clamped indices, as with one pair, take 5.2 ms).
+// Bound by FP64 issue and LDS reads (16 multiply-adds on 12 reads).  528 pairs,
+// 42 groups, P = 32, 224 rows: 3.8 ms; 7 ms with the PSF product formed for each
+// pair and three reads per element.
+constexpr int kAD = 4;             // elements along a diagonal per thread
+constexpr int kAsmThreads = 320;   // at most; P = 32 has 8 x 35 threads' work
+template <int PB>
+__global__ __launch_bounds__(kAsmThreads) void k_gram_assemble(const double2* __restrict__ Q,
+                                                               const float2* __restrict__ psf,
+                                                               const double* __restrict__ qinv,
+                                                               const int* __restrict__ t0s, double2* __restrict__ H,
+                                                               int nc, int P, int ny, int nt, int nsp, int ntile,
+                                                               int ay) {
+  const int g = blockIdx.x / ntile, tile = blockIdx.x - g * ntile;
+  const int nd = 2 * P - 1, t0 = t0s[g], tid = threadIdx.x, nth = blockDim.x;
+  constexpr bool pad = PB > 1;
+  constexpr int e3 = pad ? kAD - 1 : 0;
+  const int ls = P + 2 * e3, lk = pad ? (P + kAD - 1) / kAD * kAD : P, lq = nd + e3, npair = nc * (nc + 1) / 2;
   extern __shared__ double2 sma[];
-  double2* pj = sma;             // [ay][P]  q_g(iy) psf[iy][t0 + j]
-  double2* pk = pj + ay * P;     // [ay][P]  psf[iy][t0 + k]
-  double2* qs = pk + ay * P;     // [ay][nd] Q_nm(iy, .)
-  const int tid = threadIdx.x;
-  int oj[kAO], ok_[kAO];
-  bool ok[kAO];
-  double2 acc[kAO];
+  double2* pj = sma;           // [ay][ls]     q_g(iy) psf[iy][t0 + j], from -e3
+  double2* pk = pj + ay * ls;  // [ay][lk]     psf[iy][t0 + k]
+  double2* qs = pk + ay * lk;  // [PB][ay][lq] Q_nm(iy, .), from -e3
+  // pair number -> (n, m), m >= n: row n of the upper triangle starts at n nc - n (n - 1) / 2
+  int pn[PB], pm[PB];
 #pragma unroll
-  for (int q = 0; q < kAO; ++q) {
-    const int o = tile * (kAO * 256) + tid + 256 * q;
-    ok[q] = o < P * P;
-    oj[q] = ok[q] ? o / P : 0;
-    ok_[q] = ok[q] ? o - oj[q] * P : 0;
-    acc[q] = make_double2(0.0, 0.0);
+  for (int p = 0; p < PB; ++p) {
+    const int pair = min((int)blockIdx.y * PB + p, npair - 1);
+    int n = 0, base = 0;
+    while (base + nc - n <= pair) {
+      base += nc - n;
+      ++n;
+    }
+    pn[p] = n;
+    pm[p] = n + pair - base;
   }
-  const double2* Qnm = Q + ((size_t)n * nc + m) * ny * nd;
+  const int item = tile * nth + tid, w = P + kAD - 1;
+  const bool on = item < (P + kAD - 1) / kAD * w;
+  const int k0 = on ? item / w * kAD : 0, j = on ? item - item / w * w - (kAD - 1) : 0;
+  int oj[kAD], ok[kAD];
+#pragma unroll
+  for (int e = 0; e < kAD; ++e) {
+    oj[e] = pad ? j + e3 + e : min(max(j + e, 0), P - 1);
+    ok[e] = pad ? k0 + e : min(k0 + e, P - 1);
+  }
+  const int oq = pad ? j - k0 + P - 1 + e3 : max(j - k0 + P - 1, 0);
+  double2 acc[PB][kAD];
+#pragma unroll
+  for (int p = 0; p < PB; ++p)
+#pragma unroll
+    for (int e = 0; e < kAD; ++e) acc[p][e] = make_double2(0.0, 0.0);
+  const double2 zero = make_double2(0.0, 0.0);
   const double* qg = qinv + (size_t)g * ny;
   for (int y0 = 0; y0 < ny; y0 += ay) {
     const int nyc = min(ay, ny - y0);
-    for (int i = tid; i < ay * P; i += 256) {
-      const int r = i / P, j = i - r * P;
-      double2 a = make_double2(0.0, 0.0), b = a;
-      if (r < nyc) {
-        const float2 v = psf[(size_t)(y0 + r) * nt + t0 + j];
-        b = make_double2(v.x, v.y);
-        a = zscale(b, qg[y0 + r]);
-      }
-      pj[i] = a;
-      pk[i] = b;
+    for (int i = tid; i < ay * ls; i += nth) {
+      const int r = i / ls, x = i - r * ls - e3;
+      pj[i] = r < nyc && x >= 0 && x < P ? zscale(z_of(psf[(size_t)(y0 + r) * nt + t0 + x]), qg[y0 + r]) : zero;
     }
-    for (int i = tid; i < ay * nd; i += 256) {
-      const int r = i / nd, dd = i - r * nd;
-      qs[i] = r < nyc ? Qnm[(size_t)(y0 + r) * nd + dd] : make_double2(0.0, 0.0);
+    for (int i = tid; i < ay * lk; i += nth) {
+      const int r = i / lk, x = i - r * lk;
+      pk[i] = r < nyc && x < P ? z_of(psf[(size_t)(y0 + r) * nt + t0 + x]) : zero;
+    }
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+      const double2* Qnm = Q + (((size_t)pn[p] * nc + pm[p]) * ny + y0) * nd;
+      for (int i = tid; i < ay * lq; i += nth) {
+        const int r = i / lq, x = i - r * lq - e3;
+        qs[p * ay * lq + i] = r < nyc && x >= 0 ? Qnm[(size_t)r * nd + x] : zero;
+      }
     }
     __syncthreads();
-    for (int r = 0; r < nyc; ++r) {
+    if (on)
+      for (int r = 0; r < nyc; ++r) {
+        double2 mv[kAD];
 #pragma unroll
-      for (int q = 0; q < kAO; ++q)
-        if (ok[q])
-          acc[q] = zadd(acc[q], zmul(zmulc(pj[r * P + oj[q]], pk[r * P + ok_[q]]), qs[r * nd + oj[q] - ok_[q] + P - 1]));
-    }
+        for (int e = 0; e < kAD; ++e) mv[e] = zmulc(pj[r * ls + oj[e]], pk[r * lk + ok[e]]);
+#pragma unroll
+        for (int p = 0; p < PB; ++p) {
+          const double2 q = qs[(p * ay + r) * lq + oq];
+#pragma unroll
+          for (int e = 0; e < kAD; ++e) acc[p][e] = zadd(acc[p][e], zmul(mv[e], q));
+        }
+      }
     __syncthreads();
   }
+  if (!on) return;
   double2* Hg = H + (size_t)g * nsp * nsp;
 #pragma unroll
-  for (int q = 0; q < kAO; ++q)
-    if (ok[q]) {
-      const int a = n * P + oj[q], b = m * P + ok_[q];
-      Hg[(size_t)a * nsp + b] = acc[q];
-      if (m != n) Hg[(size_t)b * nsp + a] = zconj(acc[q]);
-    }
+  for (int p = 0; p < PB; ++p) {
+    if ((int)blockIdx.y * PB + p >= npair) break;
+#pragma unroll
+    for (int e = 0; e < kAD; ++e)
+      if (k0 + e < P && j + e >= 0 && j + e < P)
+        Hg[(size_t)(pm[p] * P + k0 + e) * nsp + pn[p] * P + j + e] = zconj(acc[p][e]);
+  }
+}
+
+// LDS of k_gram_assemble for one staged row (bytes).
+size_t assemble_row(int P, int pb) {
+  const int e3 = pb > 1 ? kAD - 1 : 0, lk = pb > 1 ? (P + kAD - 1) / kAD * kAD : P;
+  return sizeof(double2) * (size_t)(P + 2 * e3 + lk + pb * (2 * P - 1 + e3));
 }
 
 // ---------------------------------------------------------------------------
@@ -524,17 +567,28 @@ static int calibrate_in(Plan& pl, Scratch& s, const uint8_t* roi, const float2* 
     const dim3 gq(pl.ny, pl.nc, (nout + kQO * 256 - 1) / (kQO * 256));
     // pixels / rows per LDS chunk: 16, fewer when the staged rows would not fit
     // LDS of k_gram_q: (nc + nd) rows of qx + 1 slots and one row of qx
-    const size_t qrow = sizeof(double2) * (size_t)(pl.nc + 1 + nd), arow = sizeof(double2) * (size_t)(2 * P + nd);
-    const int qx = (int)std::min<size_t>(16, kGramLds / qrow - 1), ay = (int)std::min<size_t>(16, kGramLds / arow);
+    const size_t qrow = sizeof(double2) * (size_t)(pl.nc + 1 + nd);
+    const int qx = (int)std::min<size_t>(16, kGramLds / qrow - 1);
+    // four coil pairs per work-group of the assembly, one where a staged row of
+    // four would not fit (patches above 400); eight rows at a time leave room for
+    // four work-groups per CU at P = 32
+    const int pb = assemble_row(P, 4) <= kGramLds ? 4 : 1;
+    const size_t arow = assemble_row(P, pb);
+    const int ay = (int)std::min<size_t>(8, kGramLds / arow);
     if (qx < 1 || ay < 1) return fail(GPJC_E_UNSUPPORTED, "calibration: coil count or patch length too large");
     const size_t lq = qrow * (qx + 1);
     hipLaunchKernelGGL(k_gram_q, gq, dim3(256), lq, st, cw, wc, ph, Qg, pl.nc, pl.nx, pl.ny, nd, qx);
     GPJC_HIP(hipGetLastError());
-    const int ntile = (P * P + kAO * 256 - 1) / (kAO * 256);
-    const dim3 ga(pl.nc, pl.nc, G * ntile);
+    const int items = (P + kAD - 1) / kAD * (P + kAD - 1), ntile = (items + kAsmThreads - 1) / kAsmThreads;
+    const int threads = ((items + ntile - 1) / ntile + 63) / 64 * 64, npair = pl.nc * (pl.nc + 1) / 2;
+    const dim3 ga(G * ntile, (npair + pb - 1) / pb);
     const size_t la = arow * ay;
-    hipLaunchKernelGGL(k_gram_assemble, ga, dim3(256), la, st, Qg, pl.psf, qinv, t0s, H, pl.nc, P, pl.ny, pl.nt, nsp,
-                       ntile, ay);
+    if (pb == 4)
+      hipLaunchKernelGGL(k_gram_assemble<4>, ga, dim3(threads), la, st, Qg, pl.psf, qinv, t0s, H, pl.nc, P, pl.ny, pl.nt,
+                         nsp, ntile, ay);
+    else
+      hipLaunchKernelGGL(k_gram_assemble<1>, ga, dim3(threads), la, st, Qg, pl.psf, qinv, t0s, H, pl.nc, P, pl.ny, pl.nt,
+                         nsp, ntile, ay);
     GPJC_HIP(hipGetLastError());
   }
 

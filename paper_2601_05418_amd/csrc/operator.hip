@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256) void k_readout_adj(const void* __restrict__ W,
 // 5.1 TB/s) and by vector issue.  On the 224 x 224, 32-coil, os 6 slice 20 us
 // (3.9 TB/s); with the exchange to sample order, the pre-twiddles strided over
 // the threads and both tables read again for each pair of coils it took 26 us.
-// 64 x 192 rows of 192, os 5, 32 coils: 1.25 ms, before 1.75 ms.
+// 64 x 192 rows of 192, os 8, 32 coils (4.8 GB of W): 1.25 ms, before 1.75 ms.
 // ---------------------------------------------------------------------------
 __device__ inline int udiv(int a, int b) { return (int)(((float)a + 0.5f) / (float)b); }  // a < 2^16, b small
 constexpr int kMaxCb = 4;      // coils per work-group at most
@@ -369,8 +369,8 @@ __global__ __launch_bounds__(256) void k_readout_fwd2(const float2* __restrict__
 // neighbouring threads read neighbouring slots.
 // Bound like the forward form, by the 77 MB of W that it reads and vector issue.
 // 224 x 224, 32 coils, os 6: 26 us (3 TB/s), before 29.8 us; 64 x 192 rows of
-// 192: 1.27 ms, before 1.70 ms; eight rows-of-256 images, os 8, 16 coils: 0.28
-// ms, before 0.37 ms.
+// 192, os 8: 1.27 ms, before 1.70 ms; eight 256 x 256 images, os 8: 0.28 ms,
+// before 0.37 ms.
 template <int NX, Store ST>
 __global__ __launch_bounds__(256) void k_readout_adj2(const void* __restrict__ W, const float2* __restrict__ coils,
                                                       const float2* __restrict__ psfp, const float2* __restrict__ twin,
@@ -636,27 +636,39 @@ __global__ __launch_bounds__(256) void k_pe_normal(const float2* __restrict__ Zp
   }
 }
 
-// Two-pass form of the normal y-stage for NY = N1 N2, L lines per
-// work-group (256 threads).  All threads first sum the k-split partials of
-// the lines into LDS (coalesced along y).  Per line, the forward transform's
-// first pass (N1-point DFTs of stride-N2 subsequences, twiddled), one
-// exchange, its second pass (N2-point DFTs) -- which leaves each thread the
+// Two-pass form of the y-stages for NY = N1 N2, L lines per work-group (256
+// threads).  MODE 0 is the normal stage: all threads first sum the k-split
+// partials of the lines into LDS (coalesced along y).  Per line, the forward
+// transform's first pass (N1-point DFTs of stride-N2 subsequences, twiddled),
+// one exchange, its second pass (N2-point DFTs) -- which leaves each thread the
 // spectrum subsequence ky = k1 + N1 k2 -- then mask / NY and conjugation, and,
 // in the same registers, the first pass of the second transform taken the
 // other way round (N2-point DFTs over k2, twiddled), one more exchange, and
-// N1-point DFTs giving y = m2 + N2 n1.
+// N1-point DFTs giving y = m2 + N2 n1.  MODE 1, the forward stage, stops at the
+// spectrum and writes its sampled lines; MODE 2, the adjoint, puts the samples
+// on a zero spectrum and takes the second transform alone.
+// Bound by the latency of the loads and exchanges.  Against the Stockham stages
+// above, on 4608 lines of 230 forward 9.4 us (16.5) and adjoint 14.2 us (19), on
+// 2688 lines of 224 adjoint 7.9 us (10).
+enum PeMode { kPeNormal = 0, kPeFwd = 1, kPeAdj = 2 };
+struct PeLines {
+  const float2* in;    // normal, forward: partials of Z [ksplit][line][NY]; adjoint: samples [line][ms]
+  void* out;           // normal, adjoint: Zt; forward: samples [line][ms]
+  const float* maskf;  // [NY]
+  const int* lines;    // [ms]
+  size_t zstride;
+  int ksplit, ms, nlines, K, kp;
+};
 template <int NY>
-struct PeNormal2Geo {
+struct PeLines2Geo {
   static constexpr int N1 = Split<NY>::N1, N2 = Split<NY>::N2, AS = N1 + 1;
   static constexpr int L = 64 / (N1 > N2 ? N1 : N2) > 0 ? 64 / (N1 > N2 ? N1 : N2) : 1;  // lines per work-group
   static constexpr int NYP = NY + 1;
 };
 
-template <int NY, Store ST>
-__global__ __launch_bounds__(256) void k_pe_normal2(const float2* __restrict__ Zp, int ksplit, size_t zstride,
-                                                    void* __restrict__ Zt, const float* __restrict__ maskf, int nlines,
-                                                    int K, int kp, const float2* __restrict__ tw) {
-  using Gm = PeNormal2Geo<NY>;
+template <int NY, Store ST, int MODE>
+__global__ __launch_bounds__(256) void k_pe_lines2(const PeLines a, const float2* __restrict__ tw) {
+  using Gm = PeLines2Geo<NY>;
   constexpr int N1 = Gm::N1, N2 = Gm::N2, AS = Gm::AS, L = Gm::L, NYP = Gm::NYP;
   __shared__ float2 twl[NY];
   __shared__ float2 Zs[L * NYP];
@@ -664,22 +676,30 @@ __global__ __launch_bounds__(256) void k_pe_normal2(const float2* __restrict__ Z
   const int tid = threadIdx.x;
   for (int i = tid; i < NY; i += 256) twl[i] = tw[i];
   const int l0 = blockIdx.x * L;
-  const int nl = min(L, nlines - l0);
-  {
+  const int nl = min(L, a.nlines - l0);
+  const float2* __restrict__ in = a.in;
+  if constexpr (MODE == kPeAdj) {
+    for (int i = tid; i < nl * NYP; i += 256) Zs[i] = make_float2(0.f, 0.f);
+    __syncthreads();
+    for (int i = tid; i < nl * a.ms; i += 256) {
+      const int ln = i / a.ms, ky = a.lines[i - ln * a.ms];
+      Zs[ln * NYP + ky] = cscale(cconj(in[(size_t)l0 * a.ms + i]), pe_post<NY>(ky));
+    }
+  } else {
     constexpr int IT = (L * NY + 255) / 256;
-    float2 a[IT];
-    sum_partials<IT>(a, Zp, ksplit, zstride, (size_t)l0 * NY, nl * NY, tid);
+    float2 z[IT];
+    sum_partials<IT>(z, in, a.ksplit, a.zstride, (size_t)l0 * NY, nl * NY, tid);
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
       const int i = tid + 256 * it;
       if (i < nl * NY) {
         const int ln = i / NY, y = i - ln * NY;
-        Zs[ln * NYP + y] = (y & 1) ? make_float2(-a[it].x, -a[it].y) : a[it];
+        Zs[ln * NYP + y] = (y & 1) ? make_float2(-z[it].x, -z[it].y) : z[it];
       }
     }
   }
   __syncthreads();
-  if (tid < nl * N2) {  // forward, first pass: item (line, i2)
+  if (MODE != kPeAdj && tid < nl * N2) {  // forward, first pass: item (line, i2)
     const int ln = tid / N2, i2 = tid - ln * N2;
     float2 v[N1];
 #pragma unroll
@@ -703,16 +723,36 @@ __global__ __launch_bounds__(256) void k_pe_normal2(const float2* __restrict__ Z
   if (act2) {
     ln2 = tid / N1;
     k1 = tid - ln2 * N1;
-    const float2* src = E + ln2 * N2 * AS + k1;
+    if constexpr (MODE == kPeAdj) {
 #pragma unroll
-    for (int i2 = 0; i2 < N2; ++i2) w[i2] = src[i2 * AS];
-    rdft<N2>(w);  // w[k2] = F[k1 + N1 k2]
-    const float inv = 1.0f / (float)NY;
+      for (int k2 = 0; k2 < N2; ++k2) w[k2] = Zs[ln2 * NYP + k1 + N1 * k2];
+    } else {
+      const float2* src = E + ln2 * N2 * AS + k1;
 #pragma unroll
-    for (int k2 = 0; k2 < N2; ++k2) w[k2] = cconj(cscale(w[k2], maskf[k1 + N1 * k2] * inv));
-    rdft<N2>(w);  // over k2: w[m2] = sum_k2 g[k1 + N1 k2] w_N2^{k2 m2}
+      for (int i2 = 0; i2 < N2; ++i2) w[i2] = src[i2 * AS];
+      rdft<N2>(w);  // w[k2] = F[k1 + N1 k2]
+    }
+    if constexpr (MODE == kPeNormal) {
+      const float inv = 1.0f / (float)NY;
+#pragma unroll
+      for (int k2 = 0; k2 < N2; ++k2) w[k2] = cconj(cscale(w[k2], a.maskf[k1 + N1 * k2] * inv));
+    }
+    if constexpr (MODE == kPeFwd) {
+#pragma unroll
+      for (int k2 = 0; k2 < N2; ++k2) Zs[ln2 * NYP + k1 + N1 * k2] = w[k2];
+    } else {
+      rdft<N2>(w);  // over k2: w[m2] = sum_k2 g[k1 + N1 k2] w_N2^{k2 m2}
+    }
   }
   __syncthreads();
+  if constexpr (MODE == kPeFwd) {
+    float2* out = static_cast<float2*>(a.out);
+    for (int i = tid; i < nl * a.ms; i += 256) {
+      const int ln = i / a.ms, ky = a.lines[i - ln * a.ms];
+      out[(size_t)l0 * a.ms + i] = cscale(Zs[ln * NYP + ky], pe_post<NY>(ky));
+    }
+    return;
+  }
   if (act2) {
     float2* dst = E + ln2 * N2 * AS + k1;
     int m = 0;
@@ -744,8 +784,8 @@ __global__ __launch_bounds__(256) void k_pe_normal2(const float2* __restrict__ Z
   for (int i = tid; i < nl * NY; i += 256) {
     const int y = i / nl, ln = i - y * nl;
     const int l = l0 + ln;
-    const int bp = l / K, k = l - bp * K;
-    store_zt<ST>(Zt, (size_t)bp * NY + y, kp, k, Zs[ln * NYP + y]);
+    const int bp = l / a.K, k = l - bp * a.K;
+    store_zt<ST>(a.out, (size_t)bp * NY + y, a.kp, k, Zs[ln * NYP + y]);
   }
 }
 
@@ -815,7 +855,7 @@ __global__ __launch_bounds__(256) void k_pe_cols(const void* __restrict__ Win, v
 
 // ---------------------------------------------------------------------------
 // Centred DFTs along the columns of uncompressed planes, in place, two-pass
-// register form (as k_pe_normal2).  Element e of column c of plane q sits at
+// register form (as k_pe_lines2).  Element e of column c of plane q sits at
 // W[q pstride + e estride + c], c < ncols: for a slice, planes (b, n) with
 // columns t (estride = ncols = Nt); for a volume's y pass, planes (b, n, z)
 // likewise; for its z pass, planes (b, n) with columns y Nt + t (estride =
@@ -1100,10 +1140,25 @@ struct ReadoutAdj {
   };
 };
 
+// The two-pass form wherever NY splits: it was the faster one at both sizes
+// measured (adjoint of 224: 7.9 and 10 us, of 230: 14.2 and 19).
+template <int NY, Store ST, int MODE>
+static void launch_pe_lines2(const Plan& pl, StageScope& sc, const float2* in, void* out, int ksplit) {
+  constexpr int L = PeLines2Geo<NY>::L;
+  const int nlines = pl.B * pl.np * pl.K;
+  const PeLines a{in, out, pl.maskf, pl.lines, (size_t)nlines * pl.ny, ksplit, pl.ms, nlines, pl.K, pl.Kp};
+  sc.launch(k_pe_lines2<NY, ST, MODE>, dim3((nlines + L - 1) / L), dim3(256), 0, pl.stream, a, (const float2*)pl.tw_y);
+}
+
 template <int NY>
 struct PeFwd {
   static int run(const Plan& pl, float2* out, int ksplit) {
     StageScope sc(pl, GPJC_STAGE_PE_FWD);
+    if constexpr (Split<NY>::ok) {
+      launch_pe_lines2<NY, Store::F32, kPeFwd>(pl, sc, pl.Zp, out, ksplit);
+      GPJC_HIP(hipGetLastError());
+      return GPJC_OK;
+    }
     const int nlines = pl.B * pl.np * pl.K;
     const size_t lds = (size_t)(NY + 2 * pl.f3_lpb * fline(NY)) * sizeof(float2);
     const size_t zs = (size_t)pl.B * pl.np * pl.K * pl.ny;
@@ -1125,6 +1180,11 @@ struct PeAdj {
   struct L {
     static int run(const Plan& pl, const float2* in) {
       StageScope sc(pl, GPJC_STAGE_PE_ADJ);
+      if constexpr (Split<NY>::ok) {
+        launch_pe_lines2<NY, ST, kPeAdj>(pl, sc, in, zt_for(pl, ST), 1);
+        GPJC_HIP(hipGetLastError());
+        return GPJC_OK;
+      }
       const int nlines = pl.B * pl.np * pl.K;
       const size_t lds = (size_t)(NY + 2 * pl.f3_lpb * fline(NY)) * sizeof(float2);
       hipLaunchKernelGGL((k_pe_adj<NY, ST>), dim3((nlines + pl.f3_lpb - 1) / pl.f3_lpb), dim3(256), lds, pl.stream,
@@ -1141,16 +1201,12 @@ struct PeNormal {
   struct L {
     static int run(const Plan& pl, int ksplit) {
       StageScope sc(pl, GPJC_STAGE_PE_NORMAL, true);
-      const int nlines = pl.B * pl.np * pl.K;
       if constexpr (Split<NY>::ok) {
-        constexpr int lines = PeNormal2Geo<NY>::L;
-        const size_t zs = (size_t)pl.B * pl.np * pl.K * pl.ny;
-        sc.launch(k_pe_normal2<NY, ST>, dim3((nlines + lines - 1) / lines), dim3(256), 0, pl.stream,
-                  (const float2*)pl.Zp, ksplit, zs, zt_for(pl, ST), (const float*)pl.maskf, nlines, pl.K,
-                  pl.Kp, (const float2*)pl.tw_y);
+        launch_pe_lines2<NY, ST, kPeNormal>(pl, sc, pl.Zp, zt_for(pl, ST), ksplit);
         GPJC_HIP(hipGetLastError());
         return GPJC_OK;
       }
+      const int nlines = pl.B * pl.np * pl.K;
       const size_t lds = (size_t)(NY + 2 * pl.f3_lpb * fline(NY)) * sizeof(float2);
       const size_t zs = (size_t)pl.B * pl.np * pl.K * pl.ny;
       sc.launch(k_pe_normal<NY, ST>, dim3((nlines + pl.f3_lpb - 1) / pl.f3_lpb), dim3(256), lds, pl.stream,

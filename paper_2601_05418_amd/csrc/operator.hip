@@ -1029,8 +1029,8 @@ size_t two_pass_lds_adj(int nx, int os, int cb) {
 }
 // Work-group shape of the two-pass readout forms: coils per chunk (0: not
 // applicable) with every item of both passes on its own thread (at most 256)
-// and the LDS within 64 KiB; at most kMaxCb, and fewer while the launch has less
-// than a work-group per CU.
+// and the LDS within 64 KiB; at most kMaxCb, and fewer where that leaves two waves'
+// work, or while the launch has less than a work-group per CU.
 TwoPassShape two_pass_shape(int nx, int os, int nc, long rows) {
   TwoPassShape r;
   const int n1 = split_n1(nx), n2 = nx / n1;
@@ -1041,6 +1041,11 @@ TwoPassShape two_pass_shape(int nx, int os, int nc, long rows) {
   int cb = std::min(nc, kMaxCb);
   while (cb > 0 && !fits(cb)) --cb;
   if (cb == 0) return r;
+  // Two waves' items are enough: one coil with os n1 = 128 leaves shorter waits at
+  // the barriers than two (64 x 192 rows of 192, os 8: forward 1231 us against
+  // 1293, adjoint 1195 against 1301; 320 rows of 32, os 8: 8.7 and 9.5 against 9.2
+  // and 11.9; eight 256 x 256: the same).
+  while (cb > 1 && cb / 2 * os * std::max(n1, n2) >= 128) cb /= 2;
   while (cb > 1 && rows * ((nc + cb - 1) / cb) < 256) cb /= 2;
   r.cb = cb;
   r.threads = (std::max(cb * os * std::max(n1, n2), nx / 2) + 63) / 64 * 64;

@@ -57,7 +57,7 @@ def stage_work(g, stage, prec, ksplit_read=1):
     B, nx, ny, nc, nt = 1, g.nx, g.ny, g.nc, g.nt
     wbytes = 8 if prec in ("fp32", "bf16x6") else 4
     if stage in ("group_compress", "group_expand"):
-        if prec == "fp32":  # arithmetic intensity ~50 flop/B, above the FP32 MFMA ridge (~20)
+        if prec == "fp32":  # FP32-class products, three FP16 products each
             return "mfma", 8.0 * B * g.k * nc * nt * ny, "flop"
         if prec == "bf16x6":
             # FP32 W once, one FP32 row of each expanded bank pair once, Z once in FP32;

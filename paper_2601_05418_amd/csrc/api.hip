@@ -147,9 +147,6 @@ static void choose_launch(Plan& pl) {
     pl.f1h_nchunk = (nch + pl.f2_cpg - 1) / pl.f2_cpg;
   }
 
-  const int lpb_max = std::max(1, std::min(32, (lds_f2 - pl.ny) / (2 * lsy)));
-  const int nlines = pl.compressed ? pl.B * pl.np * pl.K : 1;
-  pl.f3_lpb = std::max(1, std::min(lpb_max, nlines / 1024));
   pl.f3_tb = std::max(1, std::min(16, (lds_f2 - pl.ny) / (2 * lsy)));
 
   if (pl.compressed) default_gemm_config(pl);

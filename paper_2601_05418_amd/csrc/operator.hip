@@ -523,119 +523,6 @@ __device__ inline void sum_partials(float2 (&a)[IT], const float2* __restrict__ 
   }
 }
 
-template <int NY>
-__device__ inline void load_z_lines(float2* A, const float2* __restrict__ Zp, int ksplit, size_t zstride, int l0,
-                                    int nl, int tid) {
-  constexpr int LS = fline(NY);
-  constexpr int IT = 4;  // elements per thread and round of loads
-  const int nel = nl * NY;
-  for (int i0 = 0; i0 < nel; i0 += IT * 256) {
-    float2 a[IT];
-    sum_partials<IT>(a, Zp, ksplit, zstride, (size_t)l0 * NY + i0, nel - i0, tid);
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int i = i0 + tid + 256 * it;
-      if (i < nel) {
-        const int li = i / NY, y = i - li * NY;
-        A[li * LS + fpad(y)] = (y & 1) ? make_float2(-a[it].x, -a[it].y) : a[it];
-      }
-    }
-  }
-}
-
-template <int NY>
-__global__ __launch_bounds__(256) void k_pe_fwd(const float2* __restrict__ Zp, int ksplit, size_t zstride,
-                                                float2* __restrict__ out, const int* __restrict__ lines, int ms,
-                                                int nlines, int lpb, const float2* __restrict__ tw) {
-  constexpr int LS = fline(NY);
-  extern __shared__ float2 sm[];
-  const int tid = threadIdx.x;
-  float2* twl = sm;
-  float2* A = sm + NY;
-  float2* Bf = A + lpb * LS;
-  for (int i = tid; i < NY; i += 256) twl[i] = tw[i];
-  const int l0 = blockIdx.x * lpb;
-  const int nl = min(lpb, nlines - l0);
-  load_z_lines<NY>(A, Zp, ksplit, zstride, l0, nl, tid);
-  __syncthreads();
-  const float2* res = fft_lines<NY>(A, Bf, twl, nl, LS, tid, 256, wg_sync);
-  for (int i = tid; i < nl * ms; i += 256) {
-    const int li = i / ms, m = i - li * ms;
-    const int ky = lines[m];
-    out[(size_t)l0 * ms + i] = cscale(res[li * LS + fpad(ky)], pe_post<NY>(ky));
-  }
-}
-
-// Adjoint: zero-fill, inverse DFT; writes Zt[(b,p)][y][k] (k contiguous, stride kp), stored as ST.
-template <int NY, Store ST>
-__global__ __launch_bounds__(256) void k_pe_adj(const float2* __restrict__ in, void* __restrict__ Zt,
-                                                const int* __restrict__ lines, int ms, int nlines, int lpb, int K,
-                                                int kp, const float2* __restrict__ tw) {
-  constexpr int LS = fline(NY);
-  extern __shared__ float2 sm[];
-  const int tid = threadIdx.x;
-  float2* twl = sm;
-  float2* A = sm + NY;
-  float2* Bf = A + lpb * LS;
-  for (int i = tid; i < NY; i += 256) twl[i] = tw[i];
-  const int l0 = blockIdx.x * lpb;
-  const int nl = min(lpb, nlines - l0);
-  for (int i = tid; i < nl * LS; i += 256) A[i] = make_float2(0.f, 0.f);
-  __syncthreads();
-  for (int i = tid; i < nl * ms; i += 256) {
-    const int li = i / ms, m = i - li * ms;
-    const int ky = lines[m];
-    A[li * LS + fpad(ky)] = cscale(cconj(in[(size_t)l0 * ms + i]), pe_post<NY>(ky));
-  }
-  __syncthreads();
-  const float2* res = fft_lines<NY>(A, Bf, twl, nl, LS, tid, 256, wg_sync);
-  for (int i = tid; i < nl * NY; i += 256) {
-    const int y = i / nl, li = i - y * nl;
-    const int l = l0 + li;
-    const int bp = l / K, k = l - bp * K;
-    float2 v = cconj(res[li * LS + fpad(y)]);
-    if (y & 1) v = make_float2(-v.x, -v.y);
-    store_zt<ST>(Zt, (size_t)bp * NY + y, kp, k, v);
-  }
-}
-
-// Normal y-stage: (-1)^y conj(FFT(conj(mask/Ny * FFT((-1)^y z)))) -> Zt.
-template <int NY, Store ST>
-__global__ __launch_bounds__(256) void k_pe_normal(const float2* __restrict__ Zp, int ksplit, size_t zstride,
-                                                   void* __restrict__ Zt, const float* __restrict__ maskf,
-                                                   int nlines, int lpb, int K, int kp,
-                                                   const float2* __restrict__ tw) {
-  constexpr int LS = fline(NY);
-  extern __shared__ float2 sm[];
-  const int tid = threadIdx.x;
-  float2* twl = sm;
-  float2* A = sm + NY;
-  float2* Bf = A + lpb * LS;
-  for (int i = tid; i < NY; i += 256) twl[i] = tw[i];
-  const int l0 = blockIdx.x * lpb;
-  const int nl = min(lpb, nlines - l0);
-  load_z_lines<NY>(A, Zp, ksplit, zstride, l0, nl, tid);
-  __syncthreads();
-  float2* res = fft_lines<NY>(A, Bf, twl, nl, LS, tid, 256, wg_sync);
-  const float inv = 1.0f / (float)NY;
-  for (int i = tid; i < nl * NY; i += 256) {
-    const int li = i / NY, ky = i - li * NY;
-    float2& v = res[li * LS + fpad(ky)];
-    v = cconj(cscale(v, maskf[ky] * inv));
-  }
-  __syncthreads();
-  float2* other = (res == A) ? Bf : A;
-  const float2* res2 = fft_lines<NY>(res, other, twl, nl, LS, tid, 256, wg_sync);
-  for (int i = tid; i < nl * NY; i += 256) {
-    const int y = i / nl, li = i - y * nl;
-    const int l = l0 + li;
-    const int bp = l / K, k = l - bp * K;
-    float2 v = cconj(res2[li * LS + fpad(y)]);
-    if (y & 1) v = make_float2(-v.x, -v.y);
-    store_zt<ST>(Zt, (size_t)bp * NY + y, kp, k, v);
-  }
-}
-
 // Two-pass form of the y-stages for NY = N1 N2, L lines per work-group (256
 // threads).  MODE 0 is the normal stage: all threads first sum the k-split
 // partials of the lines into LDS (coalesced along y).  Per line, the forward
@@ -647,8 +534,8 @@ __global__ __launch_bounds__(256) void k_pe_normal(const float2* __restrict__ Zp
 // N1-point DFTs giving y = m2 + N2 n1.  MODE 1, the forward stage, stops at the
 // spectrum and writes its sampled lines; MODE 2, the adjoint, puts the samples
 // on a zero spectrum and takes the second transform alone.
-// Bound by the latency of the loads and exchanges.  Against the Stockham stages
-// above, on 4608 lines of 230 forward 9.4 us (16.5) and adjoint 14.2 us (19), on
+// Bound by the latency of the loads and exchanges.  Against Stockham passes through
+// LDS, on 4608 lines of 230 forward 9.4 us (16.5) and adjoint 14.2 us (19), on
 // 2688 lines of 224 adjoint 7.9 us (10).
 enum PeMode { kPeNormal = 0, kPeFwd = 1, kPeAdj = 2 };
 struct PeLines {
@@ -1145,10 +1032,10 @@ struct ReadoutAdj {
   };
 };
 
-// The two-pass form wherever NY splits: it was the faster one at both sizes
-// measured (adjoint of 224: 7.9 and 10 us, of 230: 14.2 and 19).
+// The phase-encode stages of compressed lines: every built length splits.
 template <int NY, Store ST, int MODE>
 static void launch_pe_lines2(const Plan& pl, StageScope& sc, const float2* in, void* out, int ksplit) {
+  static_assert(Split<NY>::ok, "a built length without a two-pass split");
   constexpr int L = PeLines2Geo<NY>::L;
   const int nlines = pl.B * pl.np * pl.K;
   const PeLines a{in, out, pl.maskf, pl.lines, (size_t)nlines * pl.ny, ksplit, pl.ms, nlines, pl.K, pl.Kp};
@@ -1159,16 +1046,7 @@ template <int NY>
 struct PeFwd {
   static int run(const Plan& pl, float2* out, int ksplit) {
     StageScope sc(pl, GPJC_STAGE_PE_FWD);
-    if constexpr (Split<NY>::ok) {
-      launch_pe_lines2<NY, Store::F32, kPeFwd>(pl, sc, pl.Zp, out, ksplit);
-      GPJC_HIP(hipGetLastError());
-      return GPJC_OK;
-    }
-    const int nlines = pl.B * pl.np * pl.K;
-    const size_t lds = (size_t)(NY + 2 * pl.f3_lpb * fline(NY)) * sizeof(float2);
-    const size_t zs = (size_t)pl.B * pl.np * pl.K * pl.ny;
-    hipLaunchKernelGGL(k_pe_fwd<NY>, dim3((nlines + pl.f3_lpb - 1) / pl.f3_lpb), dim3(256), lds, pl.stream, pl.Zp,
-                       ksplit, zs, out, pl.lines, pl.ms, nlines, pl.f3_lpb, pl.tw_y);
+    launch_pe_lines2<NY, Store::F32, kPeFwd>(pl, sc, pl.Zp, out, ksplit);
     GPJC_HIP(hipGetLastError());
     return GPJC_OK;
   }
@@ -1185,15 +1063,7 @@ struct PeAdj {
   struct L {
     static int run(const Plan& pl, const float2* in) {
       StageScope sc(pl, GPJC_STAGE_PE_ADJ);
-      if constexpr (Split<NY>::ok) {
-        launch_pe_lines2<NY, ST, kPeAdj>(pl, sc, in, zt_for(pl, ST), 1);
-        GPJC_HIP(hipGetLastError());
-        return GPJC_OK;
-      }
-      const int nlines = pl.B * pl.np * pl.K;
-      const size_t lds = (size_t)(NY + 2 * pl.f3_lpb * fline(NY)) * sizeof(float2);
-      hipLaunchKernelGGL((k_pe_adj<NY, ST>), dim3((nlines + pl.f3_lpb - 1) / pl.f3_lpb), dim3(256), lds, pl.stream,
-                         in, zt_for(pl, ST), pl.lines, pl.ms, nlines, pl.f3_lpb, pl.K, pl.Kp, pl.tw_y);
+      launch_pe_lines2<NY, ST, kPeAdj>(pl, sc, in, zt_for(pl, ST), 1);
       GPJC_HIP(hipGetLastError());
       return GPJC_OK;
     }
@@ -1206,17 +1076,7 @@ struct PeNormal {
   struct L {
     static int run(const Plan& pl, int ksplit) {
       StageScope sc(pl, GPJC_STAGE_PE_NORMAL, true);
-      if constexpr (Split<NY>::ok) {
-        launch_pe_lines2<NY, ST, kPeNormal>(pl, sc, pl.Zp, zt_for(pl, ST), ksplit);
-        GPJC_HIP(hipGetLastError());
-        return GPJC_OK;
-      }
-      const int nlines = pl.B * pl.np * pl.K;
-      const size_t lds = (size_t)(NY + 2 * pl.f3_lpb * fline(NY)) * sizeof(float2);
-      const size_t zs = (size_t)pl.B * pl.np * pl.K * pl.ny;
-      sc.launch(k_pe_normal<NY, ST>, dim3((nlines + pl.f3_lpb - 1) / pl.f3_lpb), dim3(256), lds, pl.stream,
-                (const float2*)pl.Zp, ksplit, zs, zt_for(pl, ST), (const float*)pl.maskf, nlines,
-                pl.f3_lpb, pl.K, pl.Kp, (const float2*)pl.tw_y);
+      launch_pe_lines2<NY, ST, kPeNormal>(pl, sc, pl.Zp, zt_for(pl, ST), ksplit);
       GPJC_HIP(hipGetLastError());
       return GPJC_OK;
     }

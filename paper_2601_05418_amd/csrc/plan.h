@@ -65,7 +65,6 @@ struct Plan {
   int f1h_cb = 1;           // coils transformed together in the readout adjoint
   int f1h_nchunk = 1;       // coil chunks (partial images) in the readout adjoint
   int f1h_cpc = 1;          // coils per chunk
-  int f3_lpb = 1;           // phase-encode lines per workgroup
   int f3_tb = 1;            // readout columns per uncompressed phase-encode workgroup
   // group-contraction configuration per precision class ([0] FP32, [1] BF16 / FP16,
   // [2] BF16X6): tile shape of the compressing and expanding contractions, split of

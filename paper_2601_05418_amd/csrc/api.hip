@@ -52,7 +52,7 @@ static void free_plan(Plan* pl) {
   void* bufs[] = {pl->coils, pl->psf,  pl->psfp, pl->twin, pl->tw_x, pl->tw_y, pl->lines, pl->pgroup,
                   pl->maskf, pl->zeros, pl->A128, pl->Aexp, pl->AH,   pl->W,    pl->Zp,   pl->Zt,    pl->part,
                   pl->vx,    pl->vr,   pl->vp,   pl->vq,   pl->vb,   pl->vd,   pl->red,  pl->hist,  pl->flag,
-                  pl->Ac2,   pl->wscale,
+                  pl->Ac2,   pl->scales,
                   pl->bmod,  pl->Ec,   pl->T3,   pl->pts3, pl->sel3, pl->maskf3, pl->tw_y3, pl->tw_z3};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -223,9 +223,8 @@ static int setup_plan(Plan& pl, const gpjc_geom* g, const gpjc_c64* d_coils, con
     if (!pl.general) {
       GPJC_TRY(dalloc(&pl.Ac2, pair_compress_words(pl) + pair_expand_words(pl)));
       pl.Ae2 = pl.Ac2 + pair_compress_words(pl);
-      GPJC_TRY(dalloc(&pl.wscale, pair_scale_floats(pl)));
-      pl.ascale = pl.wscale + (size_t)pl.B * pl.ny;
-      pl.wbound = pl.ascale + pl.G;
+      GPJC_TRY(dalloc(&pl.scales, place_pair_scales(pl)));
+      place_pair_scales(pl);
     }
     if (pl.general) {
       GPJC_TRY(dalloc(&pl.bmod, (size_t)pl.nt * npix));
@@ -256,7 +255,7 @@ static int setup_plan(Plan& pl, const gpjc_geom* g, const gpjc_c64* d_coils, con
     GPJC_HIP(hipMemcpyAsync(pl.psf, d_psf, sizeof(float2) * pl.ny * pl.nt, hipMemcpyDeviceToDevice, stream));
   }
   GPJC_TRY(launch_prep_tables(pl));
-  if (pl.wscale) GPJC_TRY(setup_pair(pl));
+  if (pl.scales) GPJC_TRY(setup_pair(pl));
   GPJC_HIP(hipMemsetAsync(pl.hist, 0, sizeof(double) * pl.hist_cap, stream));
 
   if (pl.compressed && pl.G < pl.np && pl.P > 1 && pl.general) {

@@ -84,12 +84,15 @@ __device__ inline int div_os(int t, float inv_os) { return (int)(((float)t + 0.5
 // grid (row blocks, nc, B); `rows` image rows per work-group.  LDS lines are
 // padded (fft.h): line (r, s) holds the s-th sub-transform of row r.
 // ---------------------------------------------------------------------------
-// The scale of W's rows as FP16 pairs (pair.hip) from a row's L1 norm:
-// |W[n][y][t]| <= max|psf| max|coil| sum_x |img[y][x]| / sqrt(Nt) = wbound * l1.
+// The scale of W's rows as FP16 pairs (pair.hip):
+// |W[n][y][t]| <= max_t|psf[y]| / sqrt(Nt) sum_x max_n|coil[n][y][x]| |img[y][x]|,
+// a bound of this row alone (a coil value where the image is zero drops out).
 struct RowScale {
-  float* out;           // [B][ny], or NULL: not wanted
-  const float* wbound;
+  float* out;            // [B][ny], or NULL: not wanted
+  const float* coilmax;  // [ny][nx]
+  const float* rowp;     // [ny]
 };
+__device__ inline float row_term(float2 v, float c) { return (fabsf(v.x) + fabsf(v.y)) * c; }
 
 template <int NX, Store ST>
 __global__ __launch_bounds__(256) void k_readout_fwd(const float2* __restrict__ img, const float2* __restrict__ coils,
@@ -106,13 +109,11 @@ __global__ __launch_bounds__(256) void k_readout_fwd(const float2* __restrict__ 
   if (rsc.out && n == 0) {
     for (int r = tid >> 6; r < nr; r += 4) {
       float l1 = 0.f;
-      for (int x = tid & 63; x < NX; x += 64) {
-        const float2 v = img[((size_t)b * ny + y0 + r) * NX + x];
-        l1 += fabsf(v.x) + fabsf(v.y);
-      }
+      for (int x = tid & 63; x < NX; x += 64)
+        l1 += row_term(img[((size_t)b * ny + y0 + r) * NX + x], rsc.coilmax[(size_t)(y0 + r) * NX + x]);
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
-      if ((tid & 63) == 0) rsc.out[(size_t)b * ny + y0 + r] = pair_scale(l1 * *rsc.wbound);
+      if ((tid & 63) == 0) rsc.out[(size_t)b * ny + y0 + r] = pair_scale(l1 * rsc.rowp[y0 + r]);
     }
   }
   float2* twl = sm;
@@ -304,10 +305,7 @@ __global__ __launch_bounds__(256) void k_readout_fwd2(const float2* __restrict__
   for (int k2 = 0; k2 < N2; ++k2) pv[k2] = (ps + k2 * ln)[(uint32_t)rem2];
   if (rsc.out && g0 == 0) {
     float l1 = 0.f;
-    for (int x = tid; x < NX; x += nthr) {
-      const float2 v = ip[x];
-      l1 += fabsf(v.x) + fabsf(v.y);
-    }
+    for (int x = tid; x < NX; x += nthr) l1 += row_term(ip[x], rsc.coilmax[(size_t)y * NX + x]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
     if ((tid & 63) == 0) wl1[tid >> 6] = l1;
@@ -315,7 +313,7 @@ __global__ __launch_bounds__(256) void k_readout_fwd2(const float2* __restrict__
     if (tid == 0) {
       l1 = 0.f;
       for (int w = 0; w < nthr / 64; ++w) l1 += wl1[w];
-      rsc.out[(size_t)b * ny + y] = pair_scale(l1 * *rsc.wbound);
+      rsc.out[(size_t)b * ny + y] = pair_scale(l1 * rsc.rowp[y]);
     }
   }
   const size_t coff = (size_t)c2 * ny * nt + rem2;
@@ -983,7 +981,7 @@ struct ReadoutFwd {
   struct L {
     static int run(const Plan& pl, const float2* img) {
       StageScope sc(pl, GPJC_STAGE_READOUT_FWD, true);
-      const RowScale rsc{ST == Store::F32 ? pl.wscale : nullptr, pl.wbound};
+      const RowScale rsc{ST == Store::F32 ? pl.wscale : nullptr, pl.coilmax, pl.rowp};
       if constexpr (Split<NX>::ok) {
         if (pl.f2_cb > 0) {
           const size_t lds = two_pass_lds_fwd(NX, pl.os, pl.f2_cb) * sizeof(float2);

@@ -19,8 +19,8 @@
 // - the bank by a power of two per group (its largest component), applied
 //   when the bank is installed;
 // - W by a power of two per image row (b, y), from the bound
-//   |W[n][y][t]| <= max|psf| max|coil| sum_x |img[y][x]| / sqrt(Nt) that the
-//   readout stage evaluates on the row it transforms anyway (row_scale);
+//   |W[n][y][t]| <= max_t|psf[y]| / sqrt(Nt) sum_x max_n|coil[n][y][x]| |img[y][x]|
+//   that the readout stage evaluates on the row it transforms anyway;
 // - Z^T by a power of two per work-group tile, from the tile's own maximum.
 // The smallest step is then 2^-39 of the bound, far below the rounding error
 // that the readout FFT leaves relative to the same bound.
@@ -549,32 +549,35 @@ __global__ __launch_bounds__(256) void k_pair_bank(const double2* __restrict__ A
   }
 }
 
-// Set-up: block 0 evaluates wbound = max|psf| max|coil| / sqrt(Nt), which
-// row_scale multiplies a row's L1 norm with, from the two maxima of k_absmax;
-// every block sets scales to one.
-__global__ __launch_bounds__(256) void k_absmax(const float2* __restrict__ coils, size_t nc, const float2* __restrict__ psf,
-                                                size_t np, uint32_t* __restrict__ mx) {
+// Set-up, one row y per work-group: coilmax[y][x], rowp[y], and the row's scales
+// set to one.  |re| + |im| bounds a modulus.  (fmaxf drops a NaN; the row of W
+// that it reaches is NaN under any scale.)
+__global__ __launch_bounds__(256) void k_pair_setup(const float2* __restrict__ coils, const float2* __restrict__ psf,
+                                                    int nc, int nx, int ny, int nt, int B,
+                                                    float* __restrict__ coilmax, float* __restrict__ rowp,
+                                                    float* __restrict__ wscale) {
   __shared__ float sh[4];
-  for (int which = 0; which < 2; ++which) {
-    const float2* v = which ? psf : coils;
-    const size_t n = which ? np : nc;
+  const int y = blockIdx.x, tid = threadIdx.x;
+  for (int x = tid; x < nx; x += 256) {
     float m = 0.f;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
-      m = fmaxf(m, fabsf(v[i].x) + fabsf(v[i].y));
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0)  // maxima are >= 0: ordered as their bits
-      atomicMax(mx + which, __float_as_uint(fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]))));
+#pragma unroll 4
+    for (int n = 0; n < nc; ++n) {
+      const float2 c = coils[((size_t)n * ny + y) * nx + x];
+      m = fmaxf(m, fabsf(c.x) + fabsf(c.y));
+    }
+    coilmax[(size_t)y * nx + x] = m;
   }
-}
-__global__ __launch_bounds__(256) void k_pair_init(const uint32_t* __restrict__ mx, int nt, float* __restrict__ wbound,
-                                                   float* __restrict__ scale, int n) {
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    *wbound = __uint_as_float(mx[0]) * __uint_as_float(mx[1]) * rsqrtf((float)nt);
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) scale[i] = 1.f;
+  float m = 0.f;
+  for (int t = tid; t < nt; t += 256) {
+    const float2 v = psf[(size_t)y * nt + t];
+    m = fmaxf(m, fabsf(v.x) + fabsf(v.y));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  if ((tid & 63) == 0) sh[tid >> 6] = m;
+  __syncthreads();
+  if (tid == 0) rowp[y] = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3])) * rsqrtf((float)nt);
+  for (int b = tid; b < B; b += 256) wscale[(size_t)b * ny + y] = 1.f;
 }
 
 int ceil_div(int n, int d) { return (n + d - 1) / d; }
@@ -636,7 +639,20 @@ constexpr int kExpandLds = 65536;  // bytes of Z^T pieces per work-group
 static int pair_pp(const Plan& pl) { return pl.P + (pl.P & 1); }
 static int pair_ns(const Plan& pl) { return pl.nc * pair_pp(pl); }
 static int pair_kblocks(int ns) { return ceil_div(ns, 64) * 4; }  // blocks of 16, whole k-tiles of either WK
-size_t pair_scale_floats(const Plan& pl) { return (size_t)pl.B * pl.ny + pl.G + 3 + (size_t)pl.G * kMaxParts; }
+size_t place_pair_scales(Plan& pl) {
+  float* p = pl.scales;
+  size_t used = 0;
+  auto take = [&](float** a, size_t n) {
+    *a = p ? p + used : nullptr;
+    used += (n + 63) / 64 * 64;
+  };
+  take(&pl.wscale, (size_t)pl.B * pl.ny);
+  take(&pl.coilmax, (size_t)pl.ny * pl.nx);
+  take(&pl.rowp, pl.ny);
+  take(&pl.ascale, pl.G);
+  take(&pl.amax, (size_t)pl.G * kMaxParts);
+  return used;
+}
 size_t pair_compress_words(const Plan& pl) {
   return (size_t)pl.G * ceil_div(pl.K, 16) * pair_kblocks(pair_ns(pl)) * 2 * kFrag;
 }
@@ -655,24 +671,17 @@ bool pair_expand_ok(const Plan& pl) {
 }
 
 int setup_pair(Plan& pl) {
-  const int rows = pl.B * pl.ny;
-  const size_t nc = (size_t)pl.nc * pl.ny * pl.nx, np = (size_t)pl.ny * pl.nt;
-  uint32_t* mx = reinterpret_cast<uint32_t*>(pl.wbound) + 1;
-  GPJC_HIP(hipMemsetAsync(mx, 0, 2 * sizeof(uint32_t), pl.stream));
-  hipLaunchKernelGGL(k_absmax, dim3((unsigned)std::min<size_t>((nc + 4095) / 4096, 1024)), dim3(256), 0, pl.stream,
-                     pl.coils, nc, pl.psf, np, mx);
-  hipLaunchKernelGGL(k_pair_init, dim3(std::min(ceil_div(rows, 256), 1024)), dim3(256), 0, pl.stream, mx, pl.nt,
-                     pl.wbound, pl.wscale, rows);
+  hipLaunchKernelGGL(k_pair_setup, dim3(pl.ny), dim3(256), 0, pl.stream, pl.coils, pl.psf, pl.nc, pl.nx, pl.ny, pl.nt,
+                     pl.B, pl.coilmax, pl.rowp, pl.wscale);
   GPJC_HIP(hipGetLastError());
   return GPJC_OK;
 }
 
 int launch_pair_bank(const Plan& pl) {
-  float* amax = pl.wbound + 3;  // [G][kMaxParts]
-  hipLaunchKernelGGL(k_pair_max, dim3(kMaxParts, pl.G), dim3(256), 0, pl.stream, pl.A128, (size_t)pl.K * pl.ns, amax);
+  hipLaunchKernelGGL(k_pair_max, dim3(kMaxParts, pl.G), dim3(256), 0, pl.stream, pl.A128, (size_t)pl.K * pl.ns, pl.amax);
   const size_t words = (pair_compress_words(pl) + pair_expand_words(pl)) / 2;
   hipLaunchKernelGGL(k_pair_bank, dim3((unsigned)std::min<size_t>((words + 255) / 256, 8192)), dim3(256), 0, pl.stream,
-                     pl.A128, amax, pl.ascale, pl.Ac2, pl.Ae2, pl.G, pl.K, pl.nc, pl.P, pair_pp(pl), ceil_div(pl.K, 16), pair_kblocks(pair_ns(pl)),
+                     pl.A128, pl.amax, pl.ascale, pl.Ac2, pl.Ae2, pl.G, pl.K, pl.nc, pl.P, pair_pp(pl), ceil_div(pl.K, 16), pair_kblocks(pair_ns(pl)),
                      ceil_div(pair_ns(pl), 16), pl.Kp / 16);
   GPJC_HIP(hipGetLastError());
   return GPJC_OK;

@@ -118,9 +118,12 @@ struct Plan {
   // the bank as FP16 pairs in MFMA fragments (pair.hip), for the FP32 contractions
   uint32_t* Ac2 = nullptr;  // compressing; Ae2 lies behind it
   uint32_t* Ae2 = nullptr;  // expanding
-  float* wscale = nullptr;  // [B][ny] scale of W's rows, written by the readout forward; ascale and wbound lie behind it
+  float* scales = nullptr;  // the arrays below, in one allocation (place_pair_scales)
+  float* wscale = nullptr;  // [B][ny] scale of W's rows, written by the readout forward
+  float* coilmax = nullptr; // [ny][nx] largest coil value of every pixel
+  float* rowp = nullptr;    // [ny] max|psf| / sqrt(nt) of every row
   float* ascale = nullptr;  // [G] power-of-two scale of a group's pairs
-  float* wbound = nullptr;  // max|psf| max|coil| / sqrt(nt), then two words of scratch and [G][8] maxima of the bank
+  float* amax = nullptr;    // [G][8] maxima of the bank
 
   // device: workspaces
   float2* W = nullptr;      // [B][nc][ny][nt] (also holds 16-bit W)
@@ -212,7 +215,7 @@ int launch_expand_bank(Plan& pl);
 // Whether a plan's FP32 contractions can run on them (else the FP32 MFMA forms).
 bool pair_compress_ok(const Plan& pl);
 bool pair_expand_ok(const Plan& pl);
-size_t pair_scale_floats(const Plan& pl);    // sizes of wscale with what lies behind it, Ac2, Ae2
+size_t place_pair_scales(Plan& pl);          // sets the pointers into pl.scales; floats it takes
 size_t pair_compress_words(const Plan& pl);
 size_t pair_expand_words(const Plan& pl);
 int setup_pair(Plan& pl);

@@ -1,0 +1,79 @@
+"""The FP32 contractions where operands of very different sizes meet: what an
+FP32 product keeps has to be kept whatever else lies in the same row, coil,
+bank or batch.  Data are compared channel by channel or image by image, each
+relative to its own norm.  Bound: the three stages' FP32 errors, each about
+2e-7 relative L2 (a readout DFT of up to 512 points, a contraction, a
+phase-encode DFT), added up and doubled."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_05418_amd import gpjc, synth
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+BOUND = 1.2e-6
+NX, NY, NC, P, K = 48, 80, 7, 12, 20
+
+
+def dev(x):
+    return torch.as_tensor(np.ascontiguousarray(x, np.complex64)).cuda()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy().astype(np.complex128)
+
+
+def make(seed, os_=2, p=P):
+    """A slice with random coil maps of unit size and a random orthonormal bank."""
+    sl = H.rounded_slice(synth._make_rect(2, nx=NX, ny=NY, nc=NC, os_=os_, patch_len=p, k=K, accel=2, acs=4, cycles=2,
+                                          phase_max=2.0))
+    rng = np.random.default_rng(seed)
+    c = H.round64(H.crandn(rng, (NC, NY, NX)))
+    return dataclasses.replace(sl, coils=c), H.random_bank(sl.geom, seed), rng
+
+
+def plan_of(sl, bank, batch=1):
+    plan = gpjc.Plan.from_slice(sl, batch=batch)
+    plan.set_compression(torch.as_tensor(bank).cuda())
+    return plan
+
+
+def with_coils(sl, coils):
+    return dataclasses.replace(sl, coils=H.round64(coils))
+
+
+def check(out, ref):
+    e = H.rel_l2(out, ref)
+    print(f"rel_l2={e:.3e}", flush=True)
+    assert e <= BOUND
+
+
+@pytest.mark.parametrize("spike", [1e4, 1e6, 1e7])
+def test_coil_value_outside_the_image(gpu_lib, spike):
+    """A coil value of any size where the image is zero (maps formed by a
+    division in the background) changes nothing."""
+    sl, bank, rng = make(1)
+    x = H.round64(H.crandn(rng, (NY, NX)))
+    x[:, :3] = 0.0
+    sl.coils[2, 17, 1] = spike
+    out = host(plan_of(sl, bank).forward(dev(x[None])))[0]
+    check(out, H.oracle_ops(sl, bank)["fwd"](x))
+
+
+def test_images_and_rows(gpu_lib):
+    """Images of a batch, each with one row, of sizes 1e-9 to 1e9."""
+    sl, bank, rng = make(5)
+    rows, sizes = (0, 79, 33, 16), (1e-9, 1e9, 1e-4, 1.0)
+    x = np.zeros((4, NY, NX), complex)
+    for b in range(4):
+        x[b, rows[b]] = sizes[b] * H.crandn(rng, NX)
+    x = H.round64(x)
+    plan, ops = plan_of(sl, bank, batch=4), H.oracle_ops(sl, bank)
+    out, nrm = host(plan.forward(dev(x))), host(plan.normal(dev(x)))
+    for b in range(4):
+        check(out[b], ops["fwd"](x[b]))
+        check(nrm[b], ops["nrm"](x[b]))

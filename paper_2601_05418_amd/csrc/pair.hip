@@ -15,11 +15,14 @@
 // the FP32 MFMA in its three-multiplication form gives 1.9-3.3e-7.  The rate
 // is what is bought: three products at 16 times the FP32 MFMA's rate.
 //
-// Scales.  FP16 spans 2^-24 .. 2^16, so every operand is brought under 2^15:
+// Scales.  FP16 spans 2^-24 .. 2^16, so every operand is brought under 2^15.  A
+// coil's gain is no property of the data (a bank undoes it: noise whitening), so
+// first every coil n is brought to about one by a power of two c[n], W[n] taking
+// c[n] and the bank's columns 1 / c[n].  Then
 // - the bank by a power of two per group (its largest component), applied
 //   when the bank is installed;
 // - W by a power of two per image row (b, y), from the bound
-//   |W[n][y][t]| <= max_t|psf[y]| / sqrt(Nt) sum_x max_n|coil[n][y][x]| |img[y][x]|
+//   |c[n] W[n][y][t]| <= max_t|psf[y]| / sqrt(Nt) sum_x max_n|c[n] coil[n][y][x]| |img[y][x]|
 //   that the readout stage evaluates on the row it transforms anyway;
 // - Z^T by a power of two per work-group tile, from the tile's own maximum.
 // The smallest step is then 2^-39 of the bound, far below the rounding error
@@ -132,6 +135,10 @@ __device__ inline floatx4 load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }
 
+__device__ inline float load4(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 __device__ inline void store16(__amdgpu_buffer_rsrc_t r, uint32_t off, const floatx4& v) {
@@ -172,6 +179,7 @@ struct PairCompress {
   const int* pgroup;
   const float* ascale;  // [G]
   const float* wscale;  // [B][N]
+  const float* cscale;  // [nc]
   int MT, KB;           // 16-row tiles of K; 16-element blocks of ns (padded)
   int N, ns, nc, nt, P, PP, np, K, B, ksplit, tps;  // ns = nc PP (padded); tps: k-tiles per split
   size_t split_stride;
@@ -225,7 +233,8 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
   uint32_t tail = 0;  // ODD: bit d set if the tile fetched d fetches ago holds padding in this thread's chunks
   // The buffer of a k-tile starts at the coil of the tile's first element, so
   // 32-bit offsets reach every coil the tile touches whatever the size of W.
-  auto fetch = [&](int t, floatx4(&x)[R]) {
+  const __amdgpu_buffer_rsrc_t rc = pair_rsrc(a.cscale, (uint32_t)a.nc * 4u);
+  auto fetch = [&](int t, floatx4(&x)[R], float& cn) {
     const int nf = min((t * KT) / a.PP, a.nc - 1);
     // (ODD: a last pair reaches one sample past the end of W, which is allocated two longer)
     const size_t left = (size_t)(a.nc - nf) * cstride - (size_t)p * a.P * 8 + (ODD ? 8 : 0);
@@ -237,6 +246,7 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
     const uint32_t m0 = kk < kend ? 0u : kOOBPair;
 #pragma unroll
     for (int r = 0; r < R; ++r) x[r] = load16(rw, (off + roff[r]) | m0);
+    cn = load4(rc, (uint32_t)n * 4u);  // (past the last coil: 0)
     if (ODD) tail = (tail << 1) | (uint32_t)(j + 1 == a.P);  // the pair's second element is padding
     kk += KT;
     j += KT;
@@ -255,23 +265,24 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
 #pragma unroll
   for (int i = 0; i < NT; ++i) re[i] = im[i] = floatx4{0.f, 0.f, 0.f, 0.f};
   floatx4 xw[2][R], xa[2][2];  // two k-tiles ahead
+  float xc[2];
 #pragma unroll
   for (int f = 0; f < 2; ++f) {
-    fetch(t0 + f, xw[f]);
+    fetch(t0 + f, xw[f], xc[f]);
     fetch_bank(t0 + f, xa[f]);
     __builtin_amdgcn_sched_barrier(0);  // in this order: the loop's first wait counts on it
   }
   const int kbl = c / 8, cc = c % 8;
   uint32_t* const stage = lds + kbl * NT * 2 * kFrag + (cc & 1) * 2;
   const uint32_t* const frags = lds + wk * NT * 2 * kFrag + frag_slot(li, lh, wk);
-  auto body = [&](int t, floatx4(&x)[R], floatx4(&f)[2]) {
+  auto body = [&](int t, floatx4(&x)[R], float& cn, floatx4(&f)[2]) {
     __syncthreads();  // the previous k-tile has been read
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int row = row0 + RPP * r;
       if (R * RPP == TN || row < TN) {
         uint2 hi, lo;
-        floatx4 v = x[r];
+        floatx4 v = x[r] * cn;
         if (ODD && (tail & 2u)) v[2] = v[3] = 0.f;  // what was read there belongs to the next patch
         split_pair(v, sc[r], &hi, &lo);
         uint32_t* d = stage + (row >> 4) * 2 * kFrag + frag_slot(row & 15, cc >> 1, kbl);
@@ -284,16 +295,16 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
     // out of the buffer's range, so nothing is read): every wait below counts
     // the loads of all paths to it, so a fetch behind a branch, or a way out
     // of the middle of the loop, would make it drain them all.
-    fetch(t + 2, x);
+    fetch(t + 2, x, cn);
     pair_block<NT>(f[0], f[1], frags, re, im);
     fetch_bank(t + 2, f);
   };
   int t = t0;
   for (; t + 1 < t1; t += 2) {
-    body(t, xw[0], xa[0]);
-    body(t + 1, xw[1], xa[1]);
+    body(t, xw[0], xc[0], xa[0]);
+    body(t + 1, xw[1], xc[1], xa[1]);
   }
-  if (t < t1) body(t, xw[0], xa[0]);
+  if (t < t1) body(t, xw[0], xc[0], xa[0]);
   // the wave groups' sums, in group order
 #pragma unroll
   for (int part = 0; part < 2; ++part) {
@@ -348,6 +359,7 @@ struct PairExpand {
   float2* W;            // [B][nc][M][nt]
   const int* pgroup;
   const float* ascale;
+  const float* cscale;  // [nc]
   int CT, KBk;          // 16-column tiles of ns; 16-element blocks of Kp
   int M, Kp, ns, nc, nt, P, PP, np, B, msplit, tps;  // ns = nc PP (padded); tps: column tiles per work-group
   float invPP;
@@ -434,17 +446,21 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
     const int y = y0 + 8 * i + (lane & 7);
     roff[i] = y < a.M ? (uint32_t)y * rowb : kOOBPair;
   }
+  const __amdgpu_buffer_rsrc_t rc = pair_rsrc(a.cscale, (uint32_t)a.nc * 4u);
+  // Lane (li, lh) holds row li: columns 2 lh (registers 0, 1) and 8 + 2 lh
+  // (registers 2, 3).  Lanes li < 8 and li + 8 swap halves, so that an
+  // instruction writes whole 16-column (128-byte) segments of eight rows: this
+  // lane's column of a tile, and the scale of its coil.
+  const int mycol = ((lane & 8) ? 8 : 0) + 2 * lh;
+  auto coil_scale = [&](int tile) { return load4(rc, (uint32_t)qdiv(16 * tile + mycol, a.invPP) * 4u); };
   floatx4 re[NT], im[NT];
-  auto store = [&](int tile) {
+  auto store = [&](int tile, float cn) {
     // the tile's buffer starts at the coil of its first column; rows and columns out of range are dropped
     const int nf = (16 * tile) / a.PP;
     const size_t left = (size_t)(a.nc - nf) * cstride - (size_t)p * a.P * 8;
     const __amdgpu_buffer_rsrc_t rw =
         pair_rsrc(Wb + (size_t)nf * a.M * a.nt, (uint32_t)min(left, (size_t)0x7ffffff0));
-    // Lane (li, lh) holds row li: columns 2 lh (registers 0, 1) and 8 + 2 lh
-    // (registers 2, 3).  Lanes li < 8 and li + 8 swap halves, so that an
-    // instruction writes whole 16-column (128-byte) segments of eight rows.
-    const int col = 16 * tile + ((lane & 8) ? 8 : 0) + 2 * lh;
+    const int col = 16 * tile + mycol;
     const int n = qdiv(col, a.invPP), j = col - n * a.PP;
     const uint32_t off = (uint32_t)(n - nf) * cstride + (uint32_t)j * 8u, m0 = col < a.ns ? 0u : kOOBPair;
     const bool tail = ODD && j + 1 == a.P;
@@ -456,8 +472,8 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
       floatx4 lo8, hi8;  // rows li & 7 and 8 + (li & 7)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        lo8[e] = swap8<0xc>(v0[e], v1[e]);
-        hi8[e] = swap8<0x3>(v1[e], v0[e]);
+        lo8[e] = swap8<0xc>(v0[e], v1[e]) * cn;
+        hi8[e] = swap8<0x3>(v1[e], v0[e]) * cn;
       }
       store16(rw, (off + roff[2 * i]) | mt, lo8);
       store16(rw, (off + roff[2 * i + 1]) | mt, hi8);
@@ -468,6 +484,7 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
     }
   };
   for (; ct < c_end; ct += 4) {
+    const float cn = coil_scale(ct);
 #pragma unroll
     for (int i = 0; i < NT; ++i) re[i] = im[i] = floatx4{0.f, 0.f, 0.f, 0.f};
     for (int grp = 0; grp < ng; ++grp) {
@@ -480,22 +497,23 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
         fetch_bank(last ? ct + 4 : ct, last ? 0 : grp + 1, k);
       }
     }
-    store(ct);
+    store(ct, cn);
   }
 }
 
 // ---- bank fragments -----------------------------------------------------------
 
-// Largest component of A_g over eighth blockIdx.x of its entries.
+// Largest component of A_g / c over eighth blockIdx.x of its entries.
 constexpr int kMaxParts = 8;
-__global__ __launch_bounds__(256) void k_pair_max(const double2* __restrict__ A, size_t n, float* __restrict__ amax) {
+__global__ __launch_bounds__(256) void k_pair_max(const double2* __restrict__ A, size_t n, int nc, int P,
+                                                  const float* __restrict__ cscale, float* __restrict__ amax) {
   __shared__ float sh[4];
   const double2* Ag = A + (size_t)blockIdx.y * n;
   const size_t per = (n + kMaxParts - 1) / kMaxParts, i0 = blockIdx.x * per, i1 = min(n, i0 + per);
   float m = 0.f;
 #pragma unroll 4
   for (size_t i = i0 + threadIdx.x; i < i1; i += 256)
-    m = fmaxf(m, fmaxf(fabsf((float)Ag[i].x), fabsf((float)Ag[i].y)));
+    m = fmaxf(m, fmaxf(fabsf((float)Ag[i].x), fabsf((float)Ag[i].y)) / cscale[i / P % nc]);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
@@ -504,19 +522,21 @@ __global__ __launch_bounds__(256) void k_pair_max(const double2* __restrict__ A,
     amax[blockIdx.y * kMaxParts + blockIdx.x] = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
 }
 
-__device__ inline void put_pair(uint32_t* frag, int word, float x, float y, float s) {
+// (s, a power of two, may lie outside the range of a float: the product does not)
+__device__ inline void put_pair(uint32_t* frag, int word, float x, float y, double s) {
   uint2 hi, lo;
-  split_pair(floatx4{x, y, 0.f, 0.f}, s, &hi, &lo);
+  split_pair(floatx4{(float)(x * s), (float)(y * s), 0.f, 0.f}, 1.f, &hi, &lo);
   frag[word] = hi.x;
   frag[word + kFrag] = lo.x;
 }
 
 // One complex element per thread: words of the compressing fragments [G][MT]
 // [KB] (rows k, elements i: conj(A) interleaved), then of the expanding ones
-// [G][CT][KBk] (rows c, permuted, elements k: A interleaved).  Padding is zero.
-// ascale[g] is the power of two that brings A_g's largest component under 2^15.
+// [G][CT][KBk] (rows c, permuted, elements k: A interleaved), with A / c for A.
+// Padding is zero.  ascale[g] is the power of two that brings the largest component
+// of A_g / c under 2^15.
 __global__ __launch_bounds__(256) void k_pair_bank(const double2* __restrict__ A, const float* __restrict__ amax,
-                                                   float* __restrict__ ascale,
+                                                   const float* __restrict__ cscale, float* __restrict__ ascale,
                                                    uint32_t* __restrict__ Ac, uint32_t* __restrict__ Ae, int G, int K,
                                                    int nc, int P, int PP, int MT, int KB, int CT, int KBk) {
   const size_t cmpw = (size_t)G * MT * KB * kFrag, expw = (size_t)G * CT * KBk * kFrag;
@@ -545,16 +565,54 @@ __global__ __launch_bounds__(256) void k_pair_bank(const double2* __restrict__ A
     for (int q = 0; q < kMaxParts; ++q) m = fmaxf(m, amax[g * kMaxParts + q]);
     const float sc = pair_scale(m);
     if (!cmp && v % ((size_t)CT * KBk * kFrag) == 0) ascale[g] = sc;
-    put_pair((cmp ? Ac : Ae) + f * 2 * kFrag, word, (float)x.x, cmp ? -im : im, sc);
+    put_pair((cmp ? Ac : Ae) + f * 2 * kFrag, word, (float)x.x, cmp ? -im : im, (double)sc / cscale[in ? n : 0]);
   }
+}
+
+// Set-up, one coil per work-group: cscale[n] = 2^-e, e the mean exponent of the
+// coil's values that are neither zero nor non-finite.  (A mean, not a maximum:
+// one value of any size does not move it.  Sums of integers, so that a gain of
+// 2^m shifts e by m exactly and the order does not matter.)
+__global__ __launch_bounds__(1024) void k_coil_scale(const float2* __restrict__ coils, size_t npix,
+                                                     float* __restrict__ cscale) {
+  __shared__ long long ss[16], sn[16];
+  const int tid = threadIdx.x;
+  const float2* c = coils + (size_t)blockIdx.x * npix;
+  long long s = 0, cnt = 0;
+#pragma unroll 8
+  for (size_t i = tid; i < npix; i += 1024) {
+    const int e = (int)(__float_as_uint(fabsf(c[i].x) + fabsf(c[i].y)) >> 23);
+    const bool ok = e > 0 && e < 255;
+    s += ok ? e - 127 : 0;
+    cnt += ok;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    s += __shfl_xor(s, off, 64);
+    cnt += __shfl_xor(cnt, off, 64);
+  }
+  if ((tid & 63) == 0) {
+    ss[tid >> 6] = s;
+    sn[tid >> 6] = cnt;
+  }
+  __syncthreads();
+  if (tid) return;
+  s = cnt = 0;
+  for (int w = 0; w < 16; ++w) {
+    s += ss[w];
+    cnt += sn[w];
+  }
+  long long e = cnt ? s / cnt : 0;
+  if (cnt && e * cnt > s) --e;  // floor
+  cscale[blockIdx.x] = __uint_as_float((uint32_t)(127 - max(-100LL, min(100LL, e))) << 23);
 }
 
 // Set-up, one row y per work-group: coilmax[y][x], rowp[y], and the row's scales
 // set to one.  |re| + |im| bounds a modulus.  (fmaxf drops a NaN; the row of W
 // that it reaches is NaN under any scale.)
 __global__ __launch_bounds__(256) void k_pair_setup(const float2* __restrict__ coils, const float2* __restrict__ psf,
-                                                    int nc, int nx, int ny, int nt, int B,
-                                                    float* __restrict__ coilmax, float* __restrict__ rowp,
+                                                    const float* __restrict__ cscale, int nc, int nx, int ny, int nt,
+                                                    int B, float* __restrict__ coilmax, float* __restrict__ rowp,
                                                     float* __restrict__ wscale) {
   __shared__ float sh[4];
   const int y = blockIdx.x, tid = threadIdx.x;
@@ -563,7 +621,7 @@ __global__ __launch_bounds__(256) void k_pair_setup(const float2* __restrict__ c
 #pragma unroll 4
     for (int n = 0; n < nc; ++n) {
       const float2 c = coils[((size_t)n * ny + y) * nx + x];
-      m = fmaxf(m, fabsf(c.x) + fabsf(c.y));
+      m = fmaxf(m, (fabsf(c.x) + fabsf(c.y)) * cscale[n]);
     }
     coilmax[(size_t)y * nx + x] = m;
   }
@@ -647,6 +705,7 @@ size_t place_pair_scales(Plan& pl) {
     used += (n + 63) / 64 * 64;
   };
   take(&pl.wscale, (size_t)pl.B * pl.ny);
+  take(&pl.cscale, pl.nc);
   take(&pl.coilmax, (size_t)pl.ny * pl.nx);
   take(&pl.rowp, pl.ny);
   take(&pl.ascale, pl.G);
@@ -671,17 +730,19 @@ bool pair_expand_ok(const Plan& pl) {
 }
 
 int setup_pair(Plan& pl) {
-  hipLaunchKernelGGL(k_pair_setup, dim3(pl.ny), dim3(256), 0, pl.stream, pl.coils, pl.psf, pl.nc, pl.nx, pl.ny, pl.nt,
+  hipLaunchKernelGGL(k_coil_scale, dim3(pl.nc), dim3(1024), 0, pl.stream, pl.coils, (size_t)pl.ny * pl.nx, pl.cscale);
+  hipLaunchKernelGGL(k_pair_setup, dim3(pl.ny), dim3(256), 0, pl.stream, pl.coils, pl.psf, pl.cscale, pl.nc, pl.nx, pl.ny, pl.nt,
                      pl.B, pl.coilmax, pl.rowp, pl.wscale);
   GPJC_HIP(hipGetLastError());
   return GPJC_OK;
 }
 
 int launch_pair_bank(const Plan& pl) {
-  hipLaunchKernelGGL(k_pair_max, dim3(kMaxParts, pl.G), dim3(256), 0, pl.stream, pl.A128, (size_t)pl.K * pl.ns, pl.amax);
+  hipLaunchKernelGGL(k_pair_max, dim3(kMaxParts, pl.G), dim3(256), 0, pl.stream, pl.A128, (size_t)pl.K * pl.ns, pl.nc,
+                     pl.P, pl.cscale, pl.amax);
   const size_t words = (pair_compress_words(pl) + pair_expand_words(pl)) / 2;
   hipLaunchKernelGGL(k_pair_bank, dim3((unsigned)std::min<size_t>((words + 255) / 256, 8192)), dim3(256), 0, pl.stream,
-                     pl.A128, pl.amax, pl.ascale, pl.Ac2, pl.Ae2, pl.G, pl.K, pl.nc, pl.P, pair_pp(pl), ceil_div(pl.K, 16), pair_kblocks(pair_ns(pl)),
+                     pl.A128, pl.amax, pl.cscale, pl.ascale, pl.Ac2, pl.Ae2, pl.G, pl.K, pl.nc, pl.P, pair_pp(pl), ceil_div(pl.K, 16), pair_kblocks(pair_ns(pl)),
                      ceil_div(pair_ns(pl), 16), pl.Kp / 16);
   GPJC_HIP(hipGetLastError());
   return GPJC_OK;
@@ -746,6 +807,7 @@ int launch_compress_pair(const Plan& pl, StageScope& sc, const void* in, float2*
   a.out = out;
   a.pgroup = pl.pgroup;
   a.ascale = pl.ascale;
+  a.cscale = pl.cscale;
   a.wscale = pl.wscale;
   a.MT = ceil_div(pl.K, 16);
   a.KB = pair_kblocks(pair_ns(pl));
@@ -782,6 +844,7 @@ int launch_expand_pair(const Plan& pl, StageScope& sc) {
   a.W = pl.W;
   a.pgroup = pl.pgroup;
   a.ascale = pl.ascale;
+  a.cscale = pl.cscale;
   a.CT = ceil_div(pair_ns(pl), 16);
   a.KBk = kbk;
   a.M = pl.ny;

@@ -64,6 +64,22 @@ def test_coil_value_outside_the_image(gpu_lib, spike):
     check(out, H.oracle_ops(sl, bank)["fwd"](x))
 
 
+@pytest.mark.parametrize("p", [12, 3])
+@pytest.mark.parametrize("e", [-40, -24, -12, 20])
+def test_coil_gain(gpu_lib, e, p):
+    """A coil's gain, undone by the bank as noise whitening does, is exact."""
+    sl, bank, rng = make(2, p=p)
+    x = dev(H.crandn(rng, (1, NY, NX)))
+    plan = plan_of(sl, bank)
+    y = dev(H.crandn(rng, plan.data_shape()))
+    coils, b2 = sl.coils.copy(), bank.copy()
+    coils[3] *= 2.0 ** e
+    b2[:, :, 3] *= 2.0 ** -e
+    other = plan_of(with_coils(sl, coils), b2)
+    assert torch.equal(plan.forward(x), other.forward(x))
+    assert torch.equal(plan.adjoint(y), other.adjoint(y))
+
+
 def test_images_and_rows(gpu_lib):
     """Images of a batch, each with one row, of sizes 1e-9 to 1e9."""
     sl, bank, rng = make(5)

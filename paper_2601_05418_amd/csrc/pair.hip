@@ -19,12 +19,14 @@
 // coil's gain is no property of the data (a bank undoes it: noise whitening), so
 // first every coil n is brought to about one by a power of two c[n], W[n] taking
 // c[n] and the bank's columns 1 / c[n].  Then
-// - the bank by a power of two per group (its largest component), applied
-//   when the bank is installed;
+// - the bank by a power of two per row k of a group (its largest component),
+//   applied when the bank is installed; undone in the result of the compressing
+//   form, and by Z, in which rows of unequal size meet, in the expanding one;
 // - W by a power of two per image row (b, y), from the bound
 //   |c[n] W[n][y][t]| <= max_t|psf[y]| / sqrt(Nt) sum_x max_n|c[n] coil[n][y][x]| |img[y][x]|
 //   that the readout stage evaluates on the row it transforms anyway;
-// - Z^T by a power of two per work-group tile, from the tile's own maximum.
+// - Z^T by a power of two per work-group tile, from the tile's own maximum after
+//   that.
 // The smallest step is then 2^-39 of the bound, far below the rounding error
 // that the readout FFT leaves relative to the same bound.
 //
@@ -177,11 +179,11 @@ struct PairCompress {
   const float2* in;     // [B][nc][N][nt]
   float2* out;          // [ksplit][B][np][K][N]
   const int* pgroup;
-  const float* ascale;  // [G]
+  const float* ascale;  // [G][Kp]
   const float* wscale;  // [B][N]
   const float* cscale;  // [nc]
   int MT, KB;           // 16-row tiles of K; 16-element blocks of ns (padded)
-  int N, ns, nc, nt, P, PP, np, K, B, ksplit, tps;  // ns = nc PP (padded); tps: k-tiles per split
+  int N, ns, nc, nt, P, PP, np, K, Kp, B, ksplit, tps;  // ns = nc PP (padded); tps: k-tiles per split
   size_t split_stride;
   float invPP;
 };
@@ -328,7 +330,8 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
   }
   if (wk > 0 || !mine) return;
   float2* out = a.out + ks * a.split_stride + (size_t)bp * a.K * a.N;
-  const float ua = 1.f / a.ascale[g];
+  // (Kp = 16 MT: rows past K have a scale, and are not stored)
+  const floatx4 sa = *reinterpret_cast<const floatx4*>(a.ascale + (size_t)g * a.Kp + 16 * mt + 4 * lh);
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
     const int y = tn * TN + 16 * i + li;
@@ -337,6 +340,7 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int k = 16 * mt + 4 * lh + r;
+      const float ua = 1.f / sa[r];
       if (k < a.K) out[(size_t)k * a.N + y] = make_float2(re[i][r] * ua * uw, im[i][r] * ua * uw);
     }
   }
@@ -358,7 +362,8 @@ struct PairExpand {
   const float* Zt;      // [B][np][M][2 Kp]
   float2* W;            // [B][nc][M][nt]
   const int* pgroup;
-  const float* ascale;
+  const float* arel;    // [G][Kp]
+  const float* amin;    // [G]
   const float* cscale;  // [nc]
   int CT, KBk;          // 16-column tiles of ns; 16-element blocks of Kp
   int M, Kp, ns, nc, nt, P, PP, np, B, msplit, tps;  // ns = nc PP (padded); tps: column tiles per work-group
@@ -368,7 +373,7 @@ struct PairExpand {
 template <int NT, int GK, bool MULTI, bool ODD>
 __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
   constexpr int TN = 16 * NT;
-  constexpr int R = 16;  // 16-byte chunks per thread: the tile is at most 64 KiB
+  constexpr int R = 16;  // 16-byte chunks per thread at most: NT KBk <= 32 (64 KiB), so TN rows take 16 rounds of 32 / KBk
   extern __shared__ uint32_t zs[];  // [KBk][NT][hi, lo] fragments
   float* smax = reinterpret_cast<float*>(zs);  // the waves' maxima, before the fragments
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -382,7 +387,7 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
   const int g = a.pgroup[p];
   const int y0 = tn * TN;
   const int cpr = a.Kp / 2;  // chunks per row
-  const int nch = TN * cpr, nval = min(TN, a.M - y0) * cpr;
+  const int nrow = min(TN, a.M - y0);
   const floatx4* src = reinterpret_cast<const floatx4*>(a.Zt + ((size_t)bp * a.M + y0) * 2 * a.Kp);
   const uint32_t* Af = a.A + (size_t)g * a.CT * a.KBk * 2 * kFrag + lane * 4;
   const int c_end = min(a.CT, (ms + 1) * a.tps);
@@ -401,19 +406,24 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
   };
   float sz;
   {
+    // 16-byte chunk c0 of rows row0 + rpp r: rpp = 32 / KBk rows at a time
+    const int rpp = 256 / cpr, row0 = qdiv(tid, 1.f / (float)cpr), c0 = tid - row0 * cpr;
+    const bool on = row0 < rpp;
     floatx4 x[R];
     float m = 0.f;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int e = tid + 256 * r;
-      x[r] = e < nval ? src[e] : floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int r = 0; r < R; ++r)
+      x[r] = on && row0 + rpp * r < nrow ? src[tid + rpp * cpr * r] : floatx4{0.f, 0.f, 0.f, 0.f};
+    const float2 rel = reinterpret_cast<const float2*>(a.arel + (size_t)g * a.Kp)[c0];
 #pragma unroll
     for (int k = 0; k < GK; ++k) fetch_bank(ct, 0, k);
+    const floatx4 rk = {rel.x, rel.x, rel.y, rel.y};
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+    for (int r = 0; r < R; ++r) {
+      x[r] *= rk;
 #pragma unroll
       for (int w = 0; w < 4; ++w) m = fmaxf(m, fabsf(x[r][w]));
+    }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
     if (lane == 0) smax[wave] = m;
@@ -421,23 +431,21 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
     m = fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3]));
     __syncthreads();
     sz = pair_scale(m);
-    const float inv = 1.f / (float)cpr;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int e = tid + 256 * r;
-      if (e < nch) {
-        const int row = qdiv(e, inv), c = e - row * cpr;
+      const int row = row0 + rpp * r;
+      if (on && row < TN) {
         uint2 hi, lo;
         split_pair(x[r], sz, &hi, &lo);
-        uint32_t* d = zs + ((c >> 3) * NT + (row >> 4)) * 2 * kFrag + frag_slot(row & 15, (c & 7) >> 1, c >> 3) +
-                      (c & 1) * 2;
+        uint32_t* d = zs + ((c0 >> 3) * NT + (row >> 4)) * 2 * kFrag + frag_slot(row & 15, (c0 & 7) >> 1, c0 >> 3) +
+                      (c0 & 1) * 2;
         *reinterpret_cast<uint2*>(d) = hi;
         *reinterpret_cast<uint2*>(d + kFrag) = lo;
       }
     }
   }
   __syncthreads();
-  const float ua = 1.f / a.ascale[g], uz = 1.f / sz;
+  const float ua = 1.f / a.amin[g], uz = 1.f / sz;
   const uint32_t rowb = (uint32_t)a.nt * 8u, cstride = (uint32_t)a.M * rowb;  // host: 32-bit offsets reach a tile's coils
   float2* Wb = a.W + (size_t)b * a.nc * a.M * a.nt + (size_t)p * a.P;
   uint32_t roff[2 * NT];
@@ -503,23 +511,49 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
 
 // ---- bank fragments -----------------------------------------------------------
 
-// Largest component of A_g / c over eighth blockIdx.x of its entries.
-constexpr int kMaxParts = 8;
-__global__ __launch_bounds__(256) void k_pair_max(const double2* __restrict__ A, size_t n, int nc, int P,
+// Largest component of row blockIdx.x of A_g / c.
+__global__ __launch_bounds__(256) void k_pair_max(const double2* __restrict__ A, int nc, int P,
                                                   const float* __restrict__ cscale, float* __restrict__ amax) {
   __shared__ float sh[4];
-  const double2* Ag = A + (size_t)blockIdx.y * n;
-  const size_t per = (n + kMaxParts - 1) / kMaxParts, i0 = blockIdx.x * per, i1 = min(n, i0 + per);
+  const size_t row = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+  const int ns = nc * P;
+  const double2* Ak = A + row * ns;
   float m = 0.f;
 #pragma unroll 4
-  for (size_t i = i0 + threadIdx.x; i < i1; i += 256)
-    m = fmaxf(m, fmaxf(fabsf((float)Ag[i].x), fabsf((float)Ag[i].y)) / cscale[i / P % nc]);
+  for (int i = threadIdx.x; i < ns; i += 256)
+    m = fmaxf(m, fmaxf(fabsf((float)Ak[i].x), fabsf((float)Ak[i].y)) / cscale[i / P]);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0)
-    amax[blockIdx.y * kMaxParts + blockIdx.x] = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+  if (threadIdx.x == 0) amax[row] = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+}
+
+// The scales of group blockIdx.x: ascale[k] brings row k's largest component
+// under 2^15; amin is the smallest of them, that of the largest row.  A row of
+// zeros, or one past K, takes amin, so that its data keep their size and, being
+// multiplied by zeros, cannot set the scale of others: arel is 0 for it.
+__global__ __launch_bounds__(256) void k_pair_scales(const float* __restrict__ amax, int K, int kp,
+                                                     float* __restrict__ ascale, float* __restrict__ arel,
+                                                     float* __restrict__ amin) {
+  __shared__ float sh[4];
+  const int g = blockIdx.x, tid = threadIdx.x;
+  const float* m = amax + (size_t)g * K;
+  float lo = INFINITY;
+  for (int k = tid; k < K; k += 256) lo = m[k] > 0.f ? fminf(lo, pair_scale(m[k])) : lo;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) lo = fminf(lo, __shfl_xor(lo, off, 64));
+  if ((tid & 63) == 0) sh[tid >> 6] = lo;
+  __syncthreads();
+  lo = fminf(fminf(sh[0], sh[1]), fminf(sh[2], sh[3]));
+  if (!(lo < INFINITY)) lo = 1.f;
+  for (int k = tid; k < kp; k += 256) {
+    const bool on = k < K && m[k] > 0.f;
+    const float s = on ? pair_scale(m[k]) : lo;
+    ascale[(size_t)g * kp + k] = s;
+    arel[(size_t)g * kp + k] = on ? lo / s : 0.f;
+  }
+  if (tid == 0) amin[g] = lo;
 }
 
 // (s, a power of two, may lie outside the range of a float: the product does not)
@@ -533,10 +567,9 @@ __device__ inline void put_pair(uint32_t* frag, int word, float x, float y, doub
 // One complex element per thread: words of the compressing fragments [G][MT]
 // [KB] (rows k, elements i: conj(A) interleaved), then of the expanding ones
 // [G][CT][KBk] (rows c, permuted, elements k: A interleaved), with A / c for A.
-// Padding is zero.  ascale[g] is the power of two that brings the largest component
-// of A_g / c under 2^15.
-__global__ __launch_bounds__(256) void k_pair_bank(const double2* __restrict__ A, const float* __restrict__ amax,
-                                                   const float* __restrict__ cscale, float* __restrict__ ascale,
+// Padding is zero.
+__global__ __launch_bounds__(256) void k_pair_bank(const double2* __restrict__ A, const float* __restrict__ cscale,
+                                                   const float* __restrict__ ascale,
                                                    uint32_t* __restrict__ Ac, uint32_t* __restrict__ Ae, int G, int K,
                                                    int nc, int P, int PP, int MT, int KB, int CT, int KBk) {
   const size_t cmpw = (size_t)G * MT * KB * kFrag, expw = (size_t)G * CT * KBk * kFrag;
@@ -560,12 +593,8 @@ __global__ __launch_bounds__(256) void k_pair_bank(const double2* __restrict__ A
     const bool in = k < K && n < nc && j < P;
     const double2 x = in ? A[(((size_t)g * K + k) * nc + n) * P + j] : make_double2(0.0, 0.0);
     const float im = (float)x.y;
-    float m = 0.f;
-#pragma unroll
-    for (int q = 0; q < kMaxParts; ++q) m = fmaxf(m, amax[g * kMaxParts + q]);
-    const float sc = pair_scale(m);
-    if (!cmp && v % ((size_t)CT * KBk * kFrag) == 0) ascale[g] = sc;
-    put_pair((cmp ? Ac : Ae) + f * 2 * kFrag, word, (float)x.x, cmp ? -im : im, (double)sc / cscale[in ? n : 0]);
+    const double s = in ? (double)ascale[(size_t)g * 16 * KBk + k] / cscale[n] : 0.0;  // (Kp = 16 KBk)
+    put_pair((cmp ? Ac : Ae) + f * 2 * kFrag, word, (float)x.x, cmp ? -im : im, s);
   }
 }
 
@@ -708,8 +737,10 @@ size_t place_pair_scales(Plan& pl) {
   take(&pl.cscale, pl.nc);
   take(&pl.coilmax, (size_t)pl.ny * pl.nx);
   take(&pl.rowp, pl.ny);
-  take(&pl.ascale, pl.G);
-  take(&pl.amax, (size_t)pl.G * kMaxParts);
+  take(&pl.ascale, (size_t)pl.G * pl.Kp);
+  take(&pl.arel, (size_t)pl.G * pl.Kp);
+  take(&pl.amin, pl.G);
+  take(&pl.amax, (size_t)pl.G * pl.K);
   return used;
 }
 size_t pair_compress_words(const Plan& pl) {
@@ -738,12 +769,13 @@ int setup_pair(Plan& pl) {
 }
 
 int launch_pair_bank(const Plan& pl) {
-  hipLaunchKernelGGL(k_pair_max, dim3(kMaxParts, pl.G), dim3(256), 0, pl.stream, pl.A128, (size_t)pl.K * pl.ns, pl.nc,
-                     pl.P, pl.cscale, pl.amax);
+  hipLaunchKernelGGL(k_pair_max, dim3(pl.K, pl.G), dim3(256), 0, pl.stream, pl.A128, pl.nc, pl.P, pl.cscale, pl.amax);
+  hipLaunchKernelGGL(k_pair_scales, dim3(pl.G), dim3(256), 0, pl.stream, pl.amax, pl.K, pl.Kp, pl.ascale, pl.arel,
+                     pl.amin);
   const size_t words = (pair_compress_words(pl) + pair_expand_words(pl)) / 2;
   hipLaunchKernelGGL(k_pair_bank, dim3((unsigned)std::min<size_t>((words + 255) / 256, 8192)), dim3(256), 0, pl.stream,
-                     pl.A128, pl.amax, pl.cscale, pl.ascale, pl.Ac2, pl.Ae2, pl.G, pl.K, pl.nc, pl.P, pair_pp(pl), ceil_div(pl.K, 16), pair_kblocks(pair_ns(pl)),
-                     ceil_div(pair_ns(pl), 16), pl.Kp / 16);
+                     pl.A128, pl.cscale, pl.ascale, pl.Ac2, pl.Ae2, pl.G, pl.K, pl.nc, pl.P, pair_pp(pl),
+                     ceil_div(pl.K, 16), pair_kblocks(pair_ns(pl)), ceil_div(pair_ns(pl), 16), pl.Kp / 16);
   GPJC_HIP(hipGetLastError());
   return GPJC_OK;
 }
@@ -819,6 +851,7 @@ int launch_compress_pair(const Plan& pl, StageScope& sc, const void* in, float2*
   a.PP = pair_pp(pl);
   a.np = pl.np;
   a.K = pl.K;
+  a.Kp = pl.Kp;
   a.B = pl.B;
   a.ksplit = pair_partials(pl);
   a.tps = ceil_div(ceil_div(a.ns, kt), a.ksplit);
@@ -843,7 +876,8 @@ int launch_expand_pair(const Plan& pl, StageScope& sc) {
   a.Zt = reinterpret_cast<const float*>(pl.Zt);
   a.W = pl.W;
   a.pgroup = pl.pgroup;
-  a.ascale = pl.ascale;
+  a.arel = pl.arel;
+  a.amin = pl.amin;
   a.cscale = pl.cscale;
   a.CT = ceil_div(pair_ns(pl), 16);
   a.KBk = kbk;

@@ -123,8 +123,10 @@ struct Plan {
   float* cscale = nullptr;  // [nc] power of two that brings a coil's map to about one
   float* coilmax = nullptr; // [ny][nx] largest coil value of every pixel, coils scaled by cscale
   float* rowp = nullptr;    // [ny] max|psf| / sqrt(nt) of every row
-  float* ascale = nullptr;  // [G] power-of-two scale of a group's pairs
-  float* amax = nullptr;    // [G][8] maxima of the bank
+  float* ascale = nullptr;  // [G][Kp] power-of-two scale of the pairs of a bank row
+  float* arel = nullptr;    // [G][Kp] smallest scale of the group / ascale: the row's size beside the largest
+  float* amin = nullptr;    // [G] that smallest scale
+  float* amax = nullptr;    // [G][K] maxima of the bank's rows
 
   // device: workspaces
   float2* W = nullptr;      // [B][nc][ny][nt] (also holds 16-bit W)

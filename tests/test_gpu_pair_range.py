@@ -80,6 +80,20 @@ def test_coil_gain(gpu_lib, e, p):
     assert torch.equal(plan.adjoint(y), other.adjoint(y))
 
 
+def test_bank_rows(gpu_lib):
+    """The sizes of the bank's rows are exact, channel by channel."""
+    sl, bank, rng = make(3)
+    x = dev(H.crandn(rng, (1, NY, NX)))
+    plan = plan_of(sl, bank)
+    y = H.round64(H.crandn(rng, plan.data_shape()))
+    g = sl.geom
+    m = rng.integers(-30, 31, (g.n_groups, g.k))
+    s = 2.0 ** m[np.asarray(g.patch_group)][None, :, :, None]
+    other = plan_of(sl, bank * 2.0 ** m[:, :, None, None])
+    assert torch.equal(plan.forward(x) * torch.as_tensor(s, dtype=torch.float32).cuda(), other.forward(x))
+    assert torch.equal(plan.adjoint(dev(y)), other.adjoint(dev(y / s)))
+
+
 def test_images_and_rows(gpu_lib):
     """Images of a batch, each with one row, of sizes 1e-9 to 1e9."""
     sl, bank, rng = make(5)

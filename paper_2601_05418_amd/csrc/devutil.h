@@ -91,12 +91,12 @@ __device__ inline float2 sum_chunks(const float2* __restrict__ part, int nchunk,
 }
 
 // The power of two s with |x| s < 2^15 for every |x| <= bound (the scale of an
-// FP16 pair, pair.hip); 1 where the bound is zero or not finite.  1 / s is
-// exact.
+// FP16 pair, pair.hip); 1 where the bound is zero or not finite.  At most 2^115,
+// so that 2^11 s is a float; 1 / s is exact.
 __device__ inline float pair_scale(float bound) {
   if (!(bound > 0.f) || !(bound <= 3.402823466e38f)) return 1.f;
   const int e = (int)(__float_as_uint(bound) >> 23) - 126;  // bound < 2^e
-  return __uint_as_float((uint32_t)(min(15 - e, 120) + 127) << 23);
+  return __uint_as_float((uint32_t)(min(15 - e, 115) + 127) << 23);
 }
 
 // Work-group id remapped so that consecutive logical tiles share one XCD

@@ -5,10 +5,11 @@
 //   compress  Z_p[k][y]          = sum_{n,j} A_g[k][n][j] W[n][y][p P + j]
 //   expand    W[n][y][p P + j]   = sum_k conj(A_g[k][n][j]) Z_p[k][y]
 //
-// x s = hi + lo, hi = rn16(x s), lo = rn16(x s - hi), s a power of two, keeps
-// 22-23 bits of x; the products hi hi, hi lo and lo hi are accumulated in
-// FP32 by v_mfma_f32_16x16x32_f16 and lo lo (below 2^-24 of the product) is
-// dropped (the two-piece split of Ootomo and Yokota, 2022).  Against 64 bits
+// x s = hi + 2^-11 lo, hi = rn16(x s), lo = rn16(2^11 (x s - hi)), s a power of
+// two, is x to half a unit in the last place of FP32 (2^-24); the products hi hi
+// and, in an accumulator of their own (their sum takes the 2^-11), hi lo and lo hi
+// are summed in FP32 by v_mfma_f32_16x16x32_f16, and lo lo (below 2^-24 of the
+// product) is dropped (the two-piece split of Ootomo and Yokota, 2022).  Against 64 bits
 // this is closer than the FP32 MFMA: the operands' error is about 2^-24 each,
 // and an accumulator is rounded once per 32 products instead of once per two.
 // Relative L2 of a contraction of random data against FP64: 1.1-1.6e-7, where
@@ -17,7 +18,7 @@
 //
 // Scales.  FP16 spans 2^-24 .. 2^16, so every operand is brought under 2^15.  A
 // coil's gain is no property of the data (a bank undoes it: noise whitening), so
-// first every coil n is brought to about one by a power of two c[n], W[n] taking
+// first all coils n are brought to one size by a power of two c[n], W[n] taking
 // c[n] and the bank's columns 1 / c[n].  Then
 // - the bank by a power of two per row k of a group (its largest component),
 //   applied when the bank is installed; undone in the result of the compressing
@@ -27,8 +28,8 @@
 //   that the readout stage evaluates on the row it transforms anyway;
 // - Z^T by a power of two per work-group tile, from the tile's own maximum after
 //   that.
-// The smallest step is then 2^-39 of the bound, far below the rounding error
-// that the readout FFT leaves relative to the same bound.
+// Below 2^-27 of a bound (W 2^-12 scaled) a pair has fewer bits, and the smallest step
+// is 2^-50 of it, 2^-26 of the rounding error that the readout FFT leaves in a row.
 //
 // Layouts.  An operand of the MFMA is a "fragment" of 1 KiB: 16 rows x 32
 // contraction elements (16 interleaved complex ones), lane (i, h) (i = lane
@@ -55,7 +56,6 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef float float2v __attribute__((ext_vector_type(2)));
 
 // Where 16-byte piece (row i, part h) of a fragment of k-block kb lies in LDS,
 // in words from the fragment's start.  The XOR spreads the parts, which the
@@ -72,16 +72,24 @@ __device__ inline floatx4 mfma16(const floatx4& a, const floatx4& b, const float
                                                 0);
 }
 
-// hi and lo pieces of four scaled values, two per word.
+// hi and lo pieces of four scaled values, two per word: three instructions per
+// value (v_fma_mixlo / mixhi_f16 for each piece; x s and 2^11 (x s - hi) are
+// exact in FP32).  Staging is bound by these.
+constexpr float kLo = 2048.f;  // 2^11: lo's scale beside hi's, which keeps lo a normal number as long as hi is one
 __device__ inline void split_pair(const floatx4& v, float s, uint2* hi, uint2* lo) {
   uint32_t h[2], l[2];
+  const float s2 = s * kLo;
 #pragma unroll
   for (int w = 0; w < 2; ++w) {
-    const float2v x = {v[2 * w], v[2 * w + 1]};
-    const half2v hh = __builtin_convertvector(x * s, half2v);
-    const float2v r = {fmaf(x[0], s, -(float)hh[0]), fmaf(x[1], s, -(float)hh[1])};
+    half2v hh, ll;
+    hh[0] = (_Float16)fmaf(v[2 * w], s, 0.f);
+    hh[1] = (_Float16)fmaf(v[2 * w + 1], s, 0.f);
     h[w] = __builtin_bit_cast(uint32_t, hh);
-    l[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, half2v));
+    asm("" : "+v"(h[w]));  // read both halves from here on (else hh[0] is formed twice)
+    hh = __builtin_bit_cast(half2v, h[w]);
+    ll[0] = (_Float16)fmaf((float)hh[0], -kLo, v[2 * w] * s2);
+    ll[1] = (_Float16)fmaf((float)hh[1], -kLo, v[2 * w + 1] * s2);
+    l[w] = __builtin_bit_cast(uint32_t, ll);
   }
   *hi = make_uint2(h[0], h[1]);
   *lo = make_uint2(l[0], l[1]);
@@ -96,13 +104,29 @@ __device__ inline floatx4 partner(const floatx4& f) {
   return r;
 }
 
+// Sums of a wave's tile: products hi hi, and hi lo + lo hi (2^11 times as large).
+template <int NT>
+struct PairAcc {
+  floatx4 re[NT], im[NT], rl[NT], il[NT];
+  __device__ inline void clear() {
+#pragma unroll
+    for (int i = 0; i < NT; ++i) re[i] = im[i] = rl[i] = il[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ inline void join() {
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      re[i] += rl[i] * (1.f / kLo);
+      im[i] += il[i] * (1.f / kLo);
+    }
+  }
+};
+
 // One block of 16 complex contraction elements: a 16-row tile of the bank
 // (fragments ah, al of the real part's rows) times NT column tiles whose
 // fragments [tile][hi, lo] lie at bs (LDS, this lane's 16 bytes).  A tile's
 // fragments are read while the tile before it is multiplied.
 template <int NT>
-__device__ inline void pair_block(const floatx4& ah, const floatx4& al, const uint32_t* bs, floatx4 (&re)[NT],
-                                  floatx4 (&im)[NT]) {
+__device__ inline void pair_block(const floatx4& ah, const floatx4& al, const uint32_t* bs, PairAcc<NT>& a) {
   const floatx4 ph = partner(ah), pl = partner(al);
   auto frag = [&](int f) { return *reinterpret_cast<const floatx4*>(bs + f * kFrag); };
   floatx4 bh = frag(0), bl = frag(1);
@@ -113,12 +137,12 @@ __device__ inline void pair_block(const floatx4& ah, const floatx4& al, const ui
       bh = frag(2 * i + 2);
       bl = frag(2 * i + 3);
     }
-    re[i] = mfma16(al, h, re[i]);
-    im[i] = mfma16(pl, h, im[i]);
-    re[i] = mfma16(ah, l, re[i]);
-    im[i] = mfma16(ph, l, im[i]);
-    re[i] = mfma16(ah, h, re[i]);
-    im[i] = mfma16(ph, h, im[i]);
+    a.rl[i] = mfma16(al, h, a.rl[i]);
+    a.il[i] = mfma16(pl, h, a.il[i]);
+    a.re[i] = mfma16(ah, h, a.re[i]);
+    a.im[i] = mfma16(ph, h, a.im[i]);
+    a.rl[i] = mfma16(ah, l, a.rl[i]);
+    a.il[i] = mfma16(ph, l, a.il[i]);
   }
   // the order above, which the scheduler would undo: two tiles' reads, then
   // six products and two reads in turn
@@ -263,9 +287,9 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
     f[1] = *reinterpret_cast<const floatx4*>(q + kFrag);
   };
 
-  floatx4 re[NT], im[NT];
-#pragma unroll
-  for (int i = 0; i < NT; ++i) re[i] = im[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  PairAcc<NT> acc;
+  acc.clear();
+  floatx4(&re)[NT] = acc.re, (&im)[NT] = acc.im;
   floatx4 xw[2][R], xa[2][2];  // two k-tiles ahead
   float xc[2];
 #pragma unroll
@@ -284,9 +308,9 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
       const int row = row0 + RPP * r;
       if (R * RPP == TN || row < TN) {
         uint2 hi, lo;
-        floatx4 v = x[r] * cn;
+        floatx4 v = x[r];
         if (ODD && (tail & 2u)) v[2] = v[3] = 0.f;  // what was read there belongs to the next patch
-        split_pair(v, sc[r], &hi, &lo);
+        split_pair(v, sc[r] * cn, &hi, &lo);
         uint32_t* d = stage + (row >> 4) * 2 * kFrag + frag_slot(row & 15, cc >> 1, kbl);
         *reinterpret_cast<uint2*>(d) = hi;
         *reinterpret_cast<uint2*>(d + kFrag) = lo;
@@ -298,7 +322,7 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
     // the loads of all paths to it, so a fetch behind a branch, or a way out
     // of the middle of the loop, would make it drain them all.
     fetch(t + 2, x, cn);
-    pair_block<NT>(f[0], f[1], frags, re, im);
+    pair_block<NT>(f[0], f[1], frags, acc);
     fetch_bank(t + 2, f);
   };
   int t = t0;
@@ -307,6 +331,7 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
     body(t + 1, xw[1], xc[1], xa[1]);
   }
   if (t < t1) body(t, xw[0], xc[0], xa[0]);
+  acc.join();
   // the wave groups' sums, in group order
 #pragma unroll
   for (int part = 0; part < 2; ++part) {
@@ -392,6 +417,14 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
   const uint32_t* Af = a.A + (size_t)g * a.CT * a.KBk * 2 * kFrag + lane * 4;
   const int c_end = min(a.CT, (ms + 1) * a.tps);
   int ct = ms * a.tps + wave;
+  // Lane (li, lh) holds row li: columns 2 lh (registers 0, 1) and 8 + 2 lh
+  // (registers 2, 3).  Lanes li < 8 and li + 8 swap halves, so that an
+  // instruction writes whole 16-column (128-byte) segments of eight rows: this
+  // lane's column of a tile, and the scale of its coil, read a tile ahead.
+  const __amdgpu_buffer_rsrc_t rc = pair_rsrc(a.cscale, (uint32_t)a.nc * 4u);
+  const int mycol = ((lane & 8) ? 8 : 0) + 2 * lh;
+  auto coil_scale = [&](int tile) { return load4(rc, (uint32_t)qdiv(16 * tile + mycol, a.invPP) * 4u); };
+  float cn = coil_scale(ct);
   // A step takes GK blocks of k of one column tile (all of them unless MULTI).
   // A block's bank fragments make room for the next step's as soon as they
   // are multiplied, so those are issued before the tile's stores, and waiting
@@ -454,15 +487,10 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
     const int y = y0 + 8 * i + (lane & 7);
     roff[i] = y < a.M ? (uint32_t)y * rowb : kOOBPair;
   }
-  const __amdgpu_buffer_rsrc_t rc = pair_rsrc(a.cscale, (uint32_t)a.nc * 4u);
-  // Lane (li, lh) holds row li: columns 2 lh (registers 0, 1) and 8 + 2 lh
-  // (registers 2, 3).  Lanes li < 8 and li + 8 swap halves, so that an
-  // instruction writes whole 16-column (128-byte) segments of eight rows: this
-  // lane's column of a tile, and the scale of its coil.
-  const int mycol = ((lane & 8) ? 8 : 0) + 2 * lh;
-  auto coil_scale = [&](int tile) { return load4(rc, (uint32_t)qdiv(16 * tile + mycol, a.invPP) * 4u); };
-  floatx4 re[NT], im[NT];
-  auto store = [&](int tile, float cn) {
+  PairAcc<NT> acc;
+  auto store = [&](int tile) {
+    acc.join();
+    const floatx4(&re)[NT] = acc.re, (&im)[NT] = acc.im;
     // the tile's buffer starts at the coil of its first column; rows and columns out of range are dropped
     const int nf = (16 * tile) / a.PP;
     const size_t left = (size_t)(a.nc - nf) * cstride - (size_t)p * a.P * 8;
@@ -492,20 +520,20 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
     }
   };
   for (; ct < c_end; ct += 4) {
-    const float cn = coil_scale(ct);
-#pragma unroll
-    for (int i = 0; i < NT; ++i) re[i] = im[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const float next = coil_scale(ct + 4);
+    acc.clear();
     for (int grp = 0; grp < ng; ++grp) {
       const bool last = grp + 1 == ng;
 #pragma unroll
       for (int k = 0; k < GK; ++k) {
         const int kb = MULTI ? grp * GK + k : k;
         if (!MULTI || kb < a.KBk)
-          pair_block<NT>(f[k][0], f[k][1], zs + kb * NT * 2 * kFrag + frag_slot(li, lh, kb), re, im);
+          pair_block<NT>(f[k][0], f[k][1], zs + kb * NT * 2 * kFrag + frag_slot(li, lh, kb), acc);
         fetch_bank(last ? ct + 4 : ct, last ? 0 : grp + 1, k);
       }
     }
-    store(ct, cn);
+    store(ct);
+    cn = next;
   }
 }
 
@@ -598,8 +626,8 @@ __global__ __launch_bounds__(256) void k_pair_bank(const double2* __restrict__ A
   }
 }
 
-// Set-up, one coil per work-group: cscale[n] = 2^-e, e the mean exponent of the
-// coil's values that are neither zero nor non-finite.  (A mean, not a maximum:
+// Set-up, one coil per work-group: cscale[n] = e, the mean exponent of the coil's
+// values that are neither zero nor non-finite, infinite if there is none.  (A mean, not a maximum:
 // one value of any size does not move it.  Sums of integers, so that a gain of
 // 2^m shifts e by m exactly and the order does not matter.)
 __global__ __launch_bounds__(1024) void k_coil_scale(const float2* __restrict__ coils, size_t npix,
@@ -633,7 +661,24 @@ __global__ __launch_bounds__(1024) void k_coil_scale(const float2* __restrict__ 
   }
   long long e = cnt ? s / cnt : 0;
   if (cnt && e * cnt > s) --e;  // floor
-  cscale[blockIdx.x] = __uint_as_float((uint32_t)(127 - max(-100LL, min(100LL, e))) << 23);
+  cscale[blockIdx.x] = cnt ? (float)e : INFINITY;
+}
+// One work-group: cscale[n] = 2^(emin - e), at least 2^-60.  At most 1, so that its
+// product with W's scale is a float whatever the coils' gains.
+__global__ __launch_bounds__(256) void k_coil_scale_rel(float* __restrict__ cscale, int nc) {
+  __shared__ float sh[4];
+  const int tid = threadIdx.x;
+  float lo = INFINITY;
+  for (int n = tid; n < nc; n += 256) lo = fminf(lo, cscale[n]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) lo = fminf(lo, __shfl_xor(lo, off, 64));
+  if ((tid & 63) == 0) sh[tid >> 6] = lo;
+  __syncthreads();
+  lo = fminf(fminf(sh[0], sh[1]), fminf(sh[2], sh[3]));
+  for (int n = tid; n < nc; n += 256) {
+    const float e = cscale[n];
+    cscale[n] = e < INFINITY ? __uint_as_float((uint32_t)(127 - min(60, (int)(e - lo))) << 23) : 1.f;
+  }
 }
 
 // Set-up, one row y per work-group: coilmax[y][x], rowp[y], and the row's scales
@@ -674,11 +719,14 @@ int pair_wm(int K) {
   const int mt = ceil_div(K, 16);
   return ceil_div(mt, ceil_div(mt, kMaxWM));
 }
-int pair_nt(int variant) { return 8 - variant; }
+// Column tiles at most: as many as leave the accumulators and the loads in flight
+// in registers (ten waves have 168 each, the others 256 or more).
+constexpr int pair_max_nt(int wm) { return wm == 2 ? 6 : wm == 3 ? 7 : wm == 5 ? 5 : 8; }
+int pair_nt(int variant, int wm) { return std::min(8 - variant, pair_max_nt(wm)); }
 
 template <int WM, bool ODD>
 void launch_compress_nt(StageScope& sc, hipStream_t s, int nt, const PairCompress& a) {
-  constexpr int thr = 64 * WM * pair_wk(WM);
+  constexpr int thr = 64 * WM * pair_wk(WM), N = pair_max_nt(WM);
   const dim3 grid(ceil_div(a.N, 16 * nt) * ceil_div(a.MT, WM) * a.B * a.np * a.ksplit);
   switch (nt) {
     case 1: sc.launch(k_compress_pair<WM, 1, ODD>, grid, dim3(thr), 0, s, a); break;
@@ -686,9 +734,9 @@ void launch_compress_nt(StageScope& sc, hipStream_t s, int nt, const PairCompres
     case 3: sc.launch(k_compress_pair<WM, 3, ODD>, grid, dim3(thr), 0, s, a); break;
     case 4: sc.launch(k_compress_pair<WM, 4, ODD>, grid, dim3(thr), 0, s, a); break;
     case 5: sc.launch(k_compress_pair<WM, 5, ODD>, grid, dim3(thr), 0, s, a); break;
-    case 6: sc.launch(k_compress_pair<WM, 6, ODD>, grid, dim3(thr), 0, s, a); break;
-    case 7: sc.launch(k_compress_pair<WM, 7, ODD>, grid, dim3(thr), 0, s, a); break;
-    default: sc.launch(k_compress_pair<WM, 8, ODD>, grid, dim3(thr), 0, s, a); break;
+    case 6: sc.launch(k_compress_pair<WM, std::min(6, N), ODD>, grid, dim3(thr), 0, s, a); break;
+    case 7: sc.launch(k_compress_pair<WM, std::min(7, N), ODD>, grid, dim3(thr), 0, s, a); break;
+    default: sc.launch(k_compress_pair<WM, N, ODD>, grid, dim3(thr), 0, s, a); break;
   }
 }
 
@@ -762,6 +810,7 @@ bool pair_expand_ok(const Plan& pl) {
 
 int setup_pair(Plan& pl) {
   hipLaunchKernelGGL(k_coil_scale, dim3(pl.nc), dim3(1024), 0, pl.stream, pl.coils, (size_t)pl.ny * pl.nx, pl.cscale);
+  hipLaunchKernelGGL(k_coil_scale_rel, dim3(1), dim3(256), 0, pl.stream, pl.cscale, pl.nc);
   hipLaunchKernelGGL(k_pair_setup, dim3(pl.ny), dim3(256), 0, pl.stream, pl.coils, pl.psf, pl.cscale, pl.nc, pl.nx, pl.ny, pl.nt,
                      pl.B, pl.coilmax, pl.rowp, pl.wscale);
   GPJC_HIP(hipGetLastError());
@@ -785,41 +834,69 @@ static long pair_groups(const Plan& pl, int nt) {
   return (long)ceil_div(pl.ny, 16 * nt) * ceil_div(ceil_div(pl.K, 16), pair_wm(pl.K)) * pl.B * pl.np;
 }
 
-// Column tiles of the expanding form: the largest count that fits the LDS and
-// pads the rows by at most an eighth (a larger one reads the bank less often),
-// then smaller ones while the launch cannot give every CU a work-group with a
-// column tile per wave.  Measured, W of 4.8 GB: 8 tiles 1.05 ms, 6 tiles 1.16 ms.
+// Column tiles of the expanding form: the count that takes the least time by its
+// tiles, padding included, and their relative time, which more of them lower while
+// three work-groups are resident per CU and the bank is read less often for it (the
+// longer its rows, the more that gives); then fewer while the launch cannot give
+// every CU a work-group with a column tile per wave.  Measured for 1 to 8 tiles, us:
+// 2 x 230 rows of 180, K = 24: 35.2, 30.6, 28.9, 29.3, 33.1, 36.7, 40.8, 36.5; 4 x 112 rows,
+// K = 30: 16.9, 14.2, 16.0, 14.3, 16.4, 21.0, 17.0, 18.6; 256 rows, K = 80: 27.1, 24.6, 22.1,
+// 21.0, 23.7, 26.7, 27.4, 28.6; W of 4.8 GB, K = 56: 1872, 1652, 1390, 1322, 1175, 1193,
+// 1194, 1280.
 static int pair_expand_tiles(const Plan& pl) {
+  static const double kTime[2][5] = {{1.3, 1.05, 1.0, 1.0, 1.1}, {1.4, 1.2, 1.05, 1.05, 1.0}};
   const int n = ceil_div(pl.ny, 16), ct = ceil_div(pair_ns(pl), 16);
-  int t = std::min(n, std::max(1, std::min(8, kExpandLds / (2048 * (pl.Kp / 16)))));
-  while (t > 1 && 8 * ceil_div(n, t) * t > 9 * n) --t;
+  const int most = std::min(std::min(n, 5), kExpandLds / (2048 * (pl.Kp / 16)));
+  int t = 1;
+  double best = 1e30;
+  for (int i = most; i >= 1; --i) {
+    const double us = ceil_div(n, i) * i * kTime[pl.Kp > 32][i - 1];
+    if (us < best) {
+      best = us;
+      t = i;
+    }
+  }
   while (t > 1 && (long)ceil_div(n, t) * pl.B * pl.np * ceil_div(ct, 4) < 256) --t;
   return t;
 }
 
+// Work-groups of the compressing form resident per CU, by registers.
+static int pair_resident(int wm, int nt) {
+  static const uint8_t kRes[kMaxWM][5] = {
+      {4, 3, 2, 2, 1}, {3, 2, 1, 1, 1}, {3, 2, 2, 2, 1}, {2, 2, 1, 1, 1}, {2, 1, 1, 1, 1}};
+  return kRes[wm - 1][std::min(nt, 5) - 1];
+}
+
 // Column tiles and split of the compressing form by the time they are
-// expected to take: a work-group needs about 0.1 + 0.14 NT us (for WK = 2) per
-// k-tile once its loads are in flight, the launch as many rounds of 256 as its
-// work-groups make, and every split writes and reads back a partial of Z at
-// about 5 TB/s.  On the 224 x 224, 32-coil slice (kernel alone, us): 7 tiles
-// with a split of 1, 2, 3: 39, 25, 23; 5 tiles, 1, 2, 4: 30, 21, 24; 3 tiles, 1,
-// 2: 23, 22.
+// expected to take: a work-group needs about 0.25 + 0.14 NT us (for WK = 2) per
+// k-tile once its loads are in flight, half as long again for each work-group that
+// shares the CU, the launch as many such rounds as its work-groups make, and every
+// split writes and reads back a partial of Z at about 5 TB/s.  No split where the
+// launch has four work-groups per CU without one: there it adds partials of Z and no
+// parallelism.  Measured (kernel alone, us), 224 x 224, 32-coil slice, splits of 1, 2, 3:
+// 7 tiles 45, 29, 25; 5 tiles 36, 25, 34; 3 tiles 28, 30, 32; one split: 2 x 230 rows of
+// 180, P = 15, K = 24, 1, 2, 3, 4, 6 tiles: 33.5, 31.8, 36.0, 39.1, 43.8; 4 x 112 rows, K = 30:
+// 19.7, 16.4, 21.9, 18.9, 27.5; 64 x 192 rows, K = 56: 1869, 1486, 1466, 1564, 1444 (8: 1325).
 void default_pair_config(const Plan& pl, Plan::GemmCfg& g) {
-  const int n = ceil_div(pl.ny, 16), wk = pair_wk(pair_wm(pl.K)), ntile = ceil_div(pair_ns(pl), 16 * wk);
+  const int n = ceil_div(pl.ny, 16), wm = pair_wm(pl.K), wk = pair_wk(wm), ntile = ceil_div(pair_ns(pl), 16 * wk);
   const double zus = 16.0 * pl.K * pl.ny * pl.np * pl.B / 5e6;
   double best = 1e30;
   g.ksplit = 1;
   g.cvar = 0;
-  for (int t = std::min(n, 8); t >= 1; --t)
-    for (int ks = 1; ks <= std::min(kMaxKsplit, ntile); ++ks) {
-      const long rounds = (pair_groups(pl, t) * ks + 255) / 256;
-      const double us = rounds * ceil_div(ntile, ks) * (0.1 + 0.14 * t) * wk / 2 + zus * ks + 0.3 * (ks - 1);
+  for (int t = std::min(n, pair_max_nt(wm)); t >= 1; --t) {
+    const long groups = pair_groups(pl, t);
+    const int res = pair_resident(wm, t), most = groups >= 1024 ? 1 : std::min(kMaxKsplit, ntile);
+    for (int ks = 1; ks <= most; ++ks) {
+      const long per_cu = (groups * ks + 255) / 256, rem = per_cu % res;
+      const double rounds = per_cu / res * (0.5 + 0.5 * res) + (rem ? 0.5 + 0.5 * rem : 0.0);
+      const double us = rounds * ceil_div(ntile, ks) * (0.25 + 0.14 * t) * wk / 2 + zus * ks + 0.3 * (ks - 1);
       if (us < best) {
         best = us;
         g.cvar = 8 - t;
         g.ksplit = ks;
       }
     }
+  }
   g.evar = 8 - pair_expand_tiles(pl);
 }
 
@@ -827,12 +904,12 @@ void default_pair_config(const Plan& pl, Plan::GemmCfg& g) {
 // without one: there a split adds partials of Z and no parallelism.
 int pair_partials(const Plan& pl) {
   const Plan::GemmCfg& cfg = pl.cfg(Store::F32);
-  return pair_groups(pl, pair_nt(cfg.cvar)) >= 1024 ? 1 : cfg.ksplit;
+  return pair_groups(pl, pair_nt(cfg.cvar, pair_wm(pl.K))) >= 1024 ? 1 : cfg.ksplit;
 }
 
 int launch_compress_pair(const Plan& pl, StageScope& sc, const void* in, float2* out) {
   const Plan::GemmCfg& cfg = pl.cfg(Store::F32);
-  const int wm = pair_wm(pl.K), nt = pair_nt(cfg.cvar), kt = 16 * pair_wk(wm);
+  const int wm = pair_wm(pl.K), nt = pair_nt(cfg.cvar, wm), kt = 16 * pair_wk(wm);
   PairCompress a{};
   a.A = pl.Ac2;
   a.in = static_cast<const float2*>(in);
@@ -870,7 +947,7 @@ int launch_compress_pair(const Plan& pl, StageScope& sc, const void* in, float2*
 
 int launch_expand_pair(const Plan& pl, StageScope& sc) {
   const int kbk = pl.Kp / 16;
-  const int nt = std::max(1, std::min(pair_nt(pl.cfg(Store::F32).evar), kExpandLds / (2048 * kbk)));
+  const int nt = std::max(1, std::min(8 - pl.cfg(Store::F32).evar, kExpandLds / (2048 * kbk)));
   PairExpand a{};
   a.A = pl.Ae2;
   a.Zt = reinterpret_cast<const float*>(pl.Zt);
@@ -891,18 +968,20 @@ int launch_expand_pair(const Plan& pl, StageScope& sc) {
   a.np = pl.np;
   a.B = pl.B;
   a.invPP = 1.f / (float)a.PP;
-  // as many work-groups as are resident at once (by LDS, and by registers: 128
-  // up to 5 tiles, 170 above), but a column tile per wave; on the 224 x 224,
-  // 32-coil slice 7 tiles with 504 work-groups take 21.8 us, with 672 27.0 us
+  // as many work-groups as are resident at once (by LDS, and by registers: at most
+  // 128 up to 2 tiles, 168 up to 4, or 5 with at most 3 blocks of k to a step), but a
+  // column tile per wave; on the 224 x 224, 32-coil slice 7 tiles with 504 work-groups
+  // take 21.8 us, with 672, not all resident, 27.0 us
   const int base = ceil_div(pl.ny, 16 * nt) * pl.B * pl.np;
-  const int occ = std::min(nt <= 5 ? 4 : 2, 163840 / (kbk * nt * 2048));
+  const int gk = ceil_div(kbk, ceil_div(kbk, kMaxGK));
+  const int occ = std::min(nt <= 2 ? 4 : nt <= 4 || (nt == 5 && gk <= 3) ? 3 : 2, 163840 / (kbk * nt * 2048));
   const int ms = std::max(1, std::min(256 * occ / base, ceil_div(a.CT, 4)));
   a.tps = ceil_div(a.CT, ms);
   a.msplit = ceil_div(a.CT, a.tps);
   const dim3 grid(base * a.msplit);
   const uint32_t lds = (uint32_t)(kbk * nt * 2048);
   const bool multi = kbk > kMaxGK;
-  switch (multi ? ceil_div(kbk, ceil_div(kbk, kMaxGK)) : kbk) {
+  switch (gk) {
     case 1: launch_expand_gk<1, false>(sc, pl.stream, nt, grid, lds, a); break;
     case 2: launch_expand_gk<2, false>(sc, pl.stream, nt, grid, lds, a); break;
     case 3:

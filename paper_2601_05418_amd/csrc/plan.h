@@ -120,7 +120,7 @@ struct Plan {
   uint32_t* Ae2 = nullptr;  // expanding
   float* scales = nullptr;  // the arrays below, in one allocation (place_pair_scales)
   float* wscale = nullptr;  // [B][ny] scale of W's rows, written by the readout forward
-  float* cscale = nullptr;  // [nc] power of two that brings a coil's map to about one
+  float* cscale = nullptr;  // [nc] power of two, at most 1, that brings the coils' maps to one size
   float* coilmax = nullptr; // [ny][nx] largest coil value of every pixel, coils scaled by cscale
   float* rowp = nullptr;    // [ny] max|psf| / sqrt(nt) of every row
   float* ascale = nullptr;  // [G][Kp] power-of-two scale of the pairs of a bank row

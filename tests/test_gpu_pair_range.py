@@ -94,6 +94,39 @@ def test_bank_rows(gpu_lib):
     assert torch.equal(plan.adjoint(dev(y)), other.adjoint(dev(y / s)))
 
 
+def test_one_channel_of_one_coil(gpu_lib):
+    """Channels that see one coil only, where that coil, its bank row or its
+    data are far smaller than what they lie among."""
+    sl, bank, rng = make(4)
+    low = np.arange(NY) < 8
+    t = 2.0 ** -22
+    coils = sl.coils.copy()
+    coils[0, low] *= t           # weak where the image is
+    coils[1, low] = 0.0          # silent there, and the strongest entry of bank row 1
+    b = bank.copy()
+    b[:, 0, 1:] = 0.0
+    b[:, 1, 2] *= t
+    b[:, 1, [0, 3, 4, 5, 6]] = 0.0
+    sl2 = with_coils(sl, coils)
+    x = H.round64(H.crandn(rng, (NY, NX)) * low[:, None])
+    out, ref = host(plan_of(sl2, b).forward(dev(x[None])))[0], H.oracle_ops(sl2, b)["fwd"](x)
+    for k in range(K):
+        check(out[:, k], ref[:, k])
+    # adjoint: data of channel 1, small beside channel 0's, alone reach the rows where coil 0 is silent
+    coils = sl.coils.copy()
+    coils[0, low] = 0.0
+    coils[2:] = 0.0
+    b = bank[:, :2].copy()
+    b[:, 0, 1:] = 0.0
+    b[:, 1, [0, 2, 3, 4, 5, 6]] = 0.0
+    sl3 = with_coils(dataclasses.replace(sl, geom=dataclasses.replace(sl.geom, k=2)), coils)
+    plan = plan_of(sl3, b)
+    y = H.crandn(rng, plan.data_shape())
+    y[:, :, 1] *= t
+    y = H.round64(y)
+    check(host(plan.adjoint(dev(y)))[0][low], H.oracle_ops(sl3, b)["adj"](y[0])[low])
+
+
 def test_images_and_rows(gpu_lib):
     """Images of a batch, each with one row, of sizes 1e-9 to 1e9."""
     sl, bank, rng = make(5)

@@ -56,6 +56,7 @@ static void free_plan(Plan* pl) {
                   pl->bmod,  pl->Ec,   pl->T3,   pl->pts3, pl->sel3, pl->maskf3, pl->tw_y3, pl->tw_z3};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
+  if (pl->coils_pair && pl->coils_pair != pl->coils) (void)hipFree(pl->coils_pair);
   for (int i = 0; i < 2; ++i) {
     if (pl->Aexp16[i]) (void)hipFree(pl->Aexp16[i]);
     if (pl->AH16[i]) (void)hipFree(pl->AH16[i]);

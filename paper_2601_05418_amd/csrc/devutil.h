@@ -99,6 +99,9 @@ __device__ inline float pair_scale(float bound) {
   return __uint_as_float((uint32_t)(min(15 - e, 115) + 127) << 23);
 }
 
+// 1 / s of a normal power of two whose inverse is normal too.
+__device__ inline float pow2_inv(float s) { return __uint_as_float(0x7f000000u - __float_as_uint(s)); }
+
 // Work-group id remapped so that consecutive logical tiles share one XCD
 // (work-groups are dealt round-robin over the 8 XCDs, each with its own L2).
 __device__ inline int xcd_logical(int linear, int total) {

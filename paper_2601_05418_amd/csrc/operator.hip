@@ -305,6 +305,7 @@ __global__ __launch_bounds__(256) void k_readout_fwd2(const float2* __restrict__
   for (int k2 = 0; k2 < N2; ++k2) pv[k2] = (ps + k2 * ln)[(uint32_t)rem2];
   if (rsc.out && g0 == 0) {
     float l1 = 0.f;
+    const float rp = rsc.rowp[y];
     for (int x = tid; x < NX; x += nthr) l1 += row_term(ip[x], rsc.coilmax[(size_t)y * NX + x]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(256) void k_readout_fwd2(const float2* __restrict__
     if (tid == 0) {
       l1 = 0.f;
       for (int w = 0; w < nthr / 64; ++w) l1 += wl1[w];
-      rsc.out[(size_t)b * ny + y] = pair_scale(l1 * rsc.rowp[y]);
+      rsc.out[(size_t)b * ny + y] = pair_scale(l1 * rp);
     }
   }
   const size_t coff = (size_t)c2 * ny * nt + rem2;
@@ -979,15 +980,16 @@ template <Store ST>
 struct ReadoutFwd {
   template <int NX>
   struct L {
-    static int run(const Plan& pl, const float2* img) {
+    static int run(const Plan& pl, const float2* img, bool pairs) {
       StageScope sc(pl, GPJC_STAGE_READOUT_FWD, true);
-      const RowScale rsc{ST == Store::F32 ? pl.wscale : nullptr, pl.coilmax, pl.rowp};
+      const RowScale rsc{pairs ? pl.wscale : nullptr, pl.coilmax, pl.rowp};
+      const float2* coils = pairs ? pl.coils_pair : pl.coils;
       if constexpr (Split<NX>::ok) {
         if (pl.f2_cb > 0) {
           const size_t lds = two_pass_lds_fwd(NX, pl.os, pl.f2_cb) * sizeof(float2);
           const int nch = (pl.nc + pl.f2_cb - 1) / pl.f2_cb;
           dim3 grid(pl.ny, (nch + pl.f2_cpg - 1) / pl.f2_cpg, pl.B);
-          sc.launch(k_readout_fwd2<NX, ST>, grid, dim3(pl.f2_threads), lds, pl.stream, img, pl.coils, pl.psfp,
+          sc.launch(k_readout_fwd2<NX, ST>, grid, dim3(pl.f2_threads), lds, pl.stream, img, coils, pl.psfp,
                     pl.twin, pl.tw_x, (void*)pl.W, pl.ny, pl.nc, pl.os, pl.f2_cb, pl.f2_cpg, rsc);
           GPJC_HIP(hipGetLastError());
           return GPJC_OK;
@@ -996,7 +998,7 @@ struct ReadoutFwd {
       const int rows = pl.f1_rows;
       const size_t lds = (size_t)(NX + 2 * rows * pl.os * fline(NX)) * sizeof(float2);
       dim3 grid((pl.ny + rows - 1) / rows, pl.nc, pl.B);
-      sc.launch(k_readout_fwd<NX, ST>, grid, dim3(256), lds, pl.stream, img, pl.coils, pl.psfp, pl.twin, pl.tw_x,
+      sc.launch(k_readout_fwd<NX, ST>, grid, dim3(256), lds, pl.stream, img, coils, pl.psfp, pl.twin, pl.tw_x,
                 (void*)pl.W, pl.ny, pl.nc, pl.os, 1.0f / pl.os, rows, rsc);
       GPJC_HIP(hipGetLastError());
       return GPJC_OK;
@@ -1008,13 +1010,14 @@ template <Store ST>
 struct ReadoutAdj {
   template <int NX>
   struct L {
-    static int run(const Plan& pl) {
+    static int run(const Plan& pl, bool pairs) {
       StageScope sc(pl, GPJC_STAGE_READOUT_ADJ, true);
+      const float2* coils = pairs ? pl.coils_pair : pl.coils;
       if constexpr (Split<NX>::ok) {
         if (pl.f2_cb > 0) {
           const size_t lds = two_pass_lds_adj(NX, pl.os, pl.f2_cb) * sizeof(float2);
           const dim3 grid(pl.ny, pl.f1h_nchunk, pl.B);
-          sc.launch(k_readout_adj2<NX, ST>, grid, dim3(pl.f2_threads), lds, pl.stream, (const void*)pl.W, pl.coils,
+          sc.launch(k_readout_adj2<NX, ST>, grid, dim3(pl.f2_threads), lds, pl.stream, (const void*)pl.W, coils,
                     pl.psfp, pl.twin, pl.tw_x, pl.part, pl.ny, pl.nc, pl.os, pl.f2_cb, pl.f2_cpg, pl.B);
           GPJC_HIP(hipGetLastError());
           return GPJC_OK;
@@ -1022,7 +1025,7 @@ struct ReadoutAdj {
       }
       const size_t lds = (size_t)(NX + 2 * pl.f1h_cb * pl.os * fline(NX)) * sizeof(float2);
       dim3 grid(pl.ny, pl.f1h_nchunk, pl.B);
-      sc.launch(k_readout_adj<NX, ST>, grid, dim3(256), lds, pl.stream, (const void*)pl.W, pl.coils, pl.psfp,
+      sc.launch(k_readout_adj<NX, ST>, grid, dim3(256), lds, pl.stream, (const void*)pl.W, coils, pl.psfp,
                 pl.twin, pl.tw_x, pl.part, pl.ny, pl.nc, pl.os, 1.0f / pl.os, pl.f1h_cb, pl.f1h_cpc, pl.B);
       GPJC_HIP(hipGetLastError());
       return GPJC_OK;
@@ -1136,19 +1139,30 @@ struct Cols3 {
 
 int launch_pe3_cols_pass(const Plan& pl, int pass) { return dispatch_n<Cols3>(pass < 2 ? pl.ny2 : pl.nz, pl, pass); }
 
+// Whether W goes to or comes from a contraction on FP16 pairs (pair.hip), which
+// wants its rows' scales and the coils at one size.
+static bool pairs_read_w(const Plan& pl, Store st) {
+  return st == Store::F32 && pl.compressed && pair_compress_ok(pl);
+}
+static bool pairs_write_w(const Plan& pl, Store st) {
+  return st == Store::F32 && pl.compressed && pair_expand_ok(pl);
+}
+
 int launch_readout_fwd(const Plan& pl, const float2* img, Store st) {
+  const bool pairs = pairs_read_w(pl, st);
   switch (storage_of(st)) {
-    case Store::F32: return dispatch_n<ReadoutFwd<Store::F32>::L>(pl.nx, pl, img);
-    case Store::BF16: return dispatch_n<ReadoutFwd<Store::BF16>::L>(pl.nx, pl, img);
-    default: return dispatch_n<ReadoutFwd<Store::F16>::L>(pl.nx, pl, img);
+    case Store::F32: return dispatch_n<ReadoutFwd<Store::F32>::L>(pl.nx, pl, img, pairs);
+    case Store::BF16: return dispatch_n<ReadoutFwd<Store::BF16>::L>(pl.nx, pl, img, pairs);
+    default: return dispatch_n<ReadoutFwd<Store::F16>::L>(pl.nx, pl, img, pairs);
   }
 }
 
 int launch_readout_adj(const Plan& pl, Store st) {
+  const bool pairs = pairs_write_w(pl, st);
   switch (storage_of(st)) {
-    case Store::F32: return dispatch_n<ReadoutAdj<Store::F32>::L>(pl.nx, pl);
-    case Store::BF16: return dispatch_n<ReadoutAdj<Store::BF16>::L>(pl.nx, pl);
-    default: return dispatch_n<ReadoutAdj<Store::F16>::L>(pl.nx, pl);
+    case Store::F32: return dispatch_n<ReadoutAdj<Store::F32>::L>(pl.nx, pl, pairs);
+    case Store::BF16: return dispatch_n<ReadoutAdj<Store::BF16>::L>(pl.nx, pl, pairs);
+    default: return dispatch_n<ReadoutAdj<Store::F16>::L>(pl.nx, pl, pairs);
   }
 }
 

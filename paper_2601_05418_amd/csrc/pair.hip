@@ -18,8 +18,10 @@
 //
 // Scales.  FP16 spans 2^-24 .. 2^16, so every operand is brought under 2^15.  A
 // coil's gain is no property of the data (a bank undoes it: noise whitening), so
-// first all coils n are brought to one size by a power of two c[n], W[n] taking
-// c[n] and the bank's columns 1 / c[n].  Then
+// coils of very unequal gains are first brought to one size by a power of two c[n]:
+// the readout stages take a copy of the maps with it (coils_pair), so that W here is
+// c[n] W[n] (compressing) and W[n] / c[n] (expanding), and the bank's columns take
+// 1 / c[n].  Then
 // - the bank by a power of two per row k of a group (its largest component),
 //   applied when the bank is installed; undone in the result of the compressing
 //   form, and by Z, in which rows of unequal size meet, in the expanding one;
@@ -46,6 +48,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
+#include <vector>
 
 #include "devutil.h"
 #include "plan.h"
@@ -161,10 +165,6 @@ __device__ inline floatx4 load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }
 
-__device__ inline float load4(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-}
-
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 __device__ inline void store16(__amdgpu_buffer_rsrc_t r, uint32_t off, const floatx4& v) {
@@ -205,7 +205,6 @@ struct PairCompress {
   const int* pgroup;
   const float* ascale;  // [G][Kp]
   const float* wscale;  // [B][N]
-  const float* cscale;  // [nc]
   int MT, KB;           // 16-row tiles of K; 16-element blocks of ns (padded)
   int N, ns, nc, nt, P, PP, np, K, Kp, B, ksplit, tps;  // ns = nc PP (padded); tps: k-tiles per split
   size_t split_stride;
@@ -259,8 +258,7 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
   uint32_t tail = 0;  // ODD: bit d set if the tile fetched d fetches ago holds padding in this thread's chunks
   // The buffer of a k-tile starts at the coil of the tile's first element, so
   // 32-bit offsets reach every coil the tile touches whatever the size of W.
-  const __amdgpu_buffer_rsrc_t rc = pair_rsrc(a.cscale, (uint32_t)a.nc * 4u);
-  auto fetch = [&](int t, floatx4(&x)[R], float& cn) {
+  auto fetch = [&](int t, floatx4(&x)[R]) {
     const int nf = min((t * KT) / a.PP, a.nc - 1);
     // (ODD: a last pair reaches one sample past the end of W, which is allocated two longer)
     const size_t left = (size_t)(a.nc - nf) * cstride - (size_t)p * a.P * 8 + (ODD ? 8 : 0);
@@ -272,7 +270,6 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
     const uint32_t m0 = kk < kend ? 0u : kOOBPair;
 #pragma unroll
     for (int r = 0; r < R; ++r) x[r] = load16(rw, (off + roff[r]) | m0);
-    cn = load4(rc, (uint32_t)n * 4u);  // (past the last coil: 0)
     if (ODD) tail = (tail << 1) | (uint32_t)(j + 1 == a.P);  // the pair's second element is padding
     kk += KT;
     j += KT;
@@ -287,21 +284,22 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
     f[1] = *reinterpret_cast<const floatx4*>(q + kFrag);
   };
 
+  // (Kp = 16 MT: rows past K have a scale, and are not stored)
+  const floatx4 sa = *reinterpret_cast<const floatx4*>(a.ascale + (size_t)g * a.Kp + 16 * mt + 4 * lh);
   PairAcc<NT> acc;
   acc.clear();
   floatx4(&re)[NT] = acc.re, (&im)[NT] = acc.im;
   floatx4 xw[2][R], xa[2][2];  // two k-tiles ahead
-  float xc[2];
 #pragma unroll
   for (int f = 0; f < 2; ++f) {
-    fetch(t0 + f, xw[f], xc[f]);
+    fetch(t0 + f, xw[f]);
     fetch_bank(t0 + f, xa[f]);
     __builtin_amdgcn_sched_barrier(0);  // in this order: the loop's first wait counts on it
   }
   const int kbl = c / 8, cc = c % 8;
   uint32_t* const stage = lds + kbl * NT * 2 * kFrag + (cc & 1) * 2;
   const uint32_t* const frags = lds + wk * NT * 2 * kFrag + frag_slot(li, lh, wk);
-  auto body = [&](int t, floatx4(&x)[R], float& cn, floatx4(&f)[2]) {
+  auto body = [&](int t, floatx4(&x)[R], floatx4(&f)[2]) {
     __syncthreads();  // the previous k-tile has been read
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -310,7 +308,7 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
         uint2 hi, lo;
         floatx4 v = x[r];
         if (ODD && (tail & 2u)) v[2] = v[3] = 0.f;  // what was read there belongs to the next patch
-        split_pair(v, sc[r] * cn, &hi, &lo);
+        split_pair(v, sc[r], &hi, &lo);
         uint32_t* d = stage + (row >> 4) * 2 * kFrag + frag_slot(row & 15, cc >> 1, kbl);
         *reinterpret_cast<uint2*>(d) = hi;
         *reinterpret_cast<uint2*>(d + kFrag) = lo;
@@ -321,16 +319,16 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
     // out of the buffer's range, so nothing is read): every wait below counts
     // the loads of all paths to it, so a fetch behind a branch, or a way out
     // of the middle of the loop, would make it drain them all.
-    fetch(t + 2, x, cn);
+    fetch(t + 2, x);
     pair_block<NT>(f[0], f[1], frags, acc);
     fetch_bank(t + 2, f);
   };
   int t = t0;
   for (; t + 1 < t1; t += 2) {
-    body(t, xw[0], xc[0], xa[0]);
-    body(t + 1, xw[1], xc[1], xa[1]);
+    body(t, xw[0], xa[0]);
+    body(t + 1, xw[1], xa[1]);
   }
-  if (t < t1) body(t, xw[0], xc[0], xa[0]);
+  if (t < t1) body(t, xw[0], xa[0]);
   acc.join();
   // the wave groups' sums, in group order
 #pragma unroll
@@ -355,17 +353,15 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
   }
   if (wk > 0 || !mine) return;
   float2* out = a.out + ks * a.split_stride + (size_t)bp * a.K * a.N;
-  // (Kp = 16 MT: rows past K have a scale, and are not stored)
-  const floatx4 sa = *reinterpret_cast<const floatx4*>(a.ascale + (size_t)g * a.Kp + 16 * mt + 4 * lh);
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
     const int y = tn * TN + 16 * i + li;
     if (y >= a.N) continue;
-    const float uw = 1.f / a.wscale[b * a.N + y];
+    const float uw = pow2_inv(a.wscale[b * a.N + y]);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int k = 16 * mt + 4 * lh + r;
-      const float ua = 1.f / sa[r];
+      const float ua = pow2_inv(sa[r]);
       if (k < a.K) out[(size_t)k * a.N + y] = make_float2(re[i][r] * ua * uw, im[i][r] * ua * uw);
     }
   }
@@ -387,9 +383,8 @@ struct PairExpand {
   const float* Zt;      // [B][np][M][2 Kp]
   float2* W;            // [B][nc][M][nt]
   const int* pgroup;
-  const float* arel;    // [G][Kp]
-  const float* amin;    // [G]
-  const float* cscale;  // [nc]
+  const float* arel;    // [np][Kp]
+  const float* amin;    // [np]
   int CT, KBk;          // 16-column tiles of ns; 16-element blocks of Kp
   int M, Kp, ns, nc, nt, P, PP, np, B, msplit, tps;  // ns = nc PP (padded); tps: column tiles per work-group
   float invPP;
@@ -398,7 +393,9 @@ struct PairExpand {
 template <int NT, int GK, bool MULTI, bool ODD>
 __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
   constexpr int TN = 16 * NT;
-  constexpr int R = 16;  // 16-byte chunks per thread at most: NT KBk <= 32 (64 KiB), so TN rows take 16 rounds of 32 / KBk
+  // 16-byte chunks of Z^T per thread: 32 / KBk rows at a time, at most 16 times as
+  // NT KBk <= 32 (64 KiB)
+  constexpr int R = MULTI ? 16 : (TN + 32 / GK - 1) / (32 / GK);
   extern __shared__ uint32_t zs[];  // [KBk][NT][hi, lo] fragments
   float* smax = reinterpret_cast<float*>(zs);  // the waves' maxima, before the fragments
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -411,20 +408,12 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
   const int b = bp / a.np, p = bp - b * a.np;
   const int g = a.pgroup[p];
   const int y0 = tn * TN;
-  const int cpr = a.Kp / 2;  // chunks per row
+  const int cpr = MULTI ? a.Kp / 2 : 8 * GK;  // chunks per row
   const int nrow = min(TN, a.M - y0);
   const floatx4* src = reinterpret_cast<const floatx4*>(a.Zt + ((size_t)bp * a.M + y0) * 2 * a.Kp);
   const uint32_t* Af = a.A + (size_t)g * a.CT * a.KBk * 2 * kFrag + lane * 4;
   const int c_end = min(a.CT, (ms + 1) * a.tps);
   int ct = ms * a.tps + wave;
-  // Lane (li, lh) holds row li: columns 2 lh (registers 0, 1) and 8 + 2 lh
-  // (registers 2, 3).  Lanes li < 8 and li + 8 swap halves, so that an
-  // instruction writes whole 16-column (128-byte) segments of eight rows: this
-  // lane's column of a tile, and the scale of its coil, read a tile ahead.
-  const __amdgpu_buffer_rsrc_t rc = pair_rsrc(a.cscale, (uint32_t)a.nc * 4u);
-  const int mycol = ((lane & 8) ? 8 : 0) + 2 * lh;
-  auto coil_scale = [&](int tile) { return load4(rc, (uint32_t)qdiv(16 * tile + mycol, a.invPP) * 4u); };
-  float cn = coil_scale(ct);
   // A step takes GK blocks of k of one column tile (all of them unless MULTI).
   // A block's bank fragments make room for the next step's as soon as they
   // are multiplied, so those are issued before the tile's stores, and waiting
@@ -439,15 +428,15 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
   };
   float sz;
   {
-    // 16-byte chunk c0 of rows row0 + rpp r: rpp = 32 / KBk rows at a time
-    const int rpp = 256 / cpr, row0 = qdiv(tid, 1.f / (float)cpr), c0 = tid - row0 * cpr;
+    // chunk c0 of rows row0 + rpp r
+    const int rpp = 256 / cpr, row0 = MULTI ? qdiv(tid, 1.f / (float)cpr) : tid / cpr, c0 = tid - row0 * cpr;
     const bool on = row0 < rpp;
     floatx4 x[R];
     float m = 0.f;
 #pragma unroll
     for (int r = 0; r < R; ++r)
       x[r] = on && row0 + rpp * r < nrow ? src[tid + rpp * cpr * r] : floatx4{0.f, 0.f, 0.f, 0.f};
-    const float2 rel = reinterpret_cast<const float2*>(a.arel + (size_t)g * a.Kp)[c0];
+    const float2 rel = reinterpret_cast<const float2*>(a.arel + (size_t)p * a.Kp)[c0];
 #pragma unroll
     for (int k = 0; k < GK; ++k) fetch_bank(ct, 0, k);
     const floatx4 rk = {rel.x, rel.x, rel.y, rel.y};
@@ -478,7 +467,7 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
     }
   }
   __syncthreads();
-  const float ua = 1.f / a.amin[g], uz = 1.f / sz;
+  const float ua = pow2_inv(a.amin[p]), uz = pow2_inv(sz);
   const uint32_t rowb = (uint32_t)a.nt * 8u, cstride = (uint32_t)a.M * rowb;  // host: 32-bit offsets reach a tile's coils
   float2* Wb = a.W + (size_t)b * a.nc * a.M * a.nt + (size_t)p * a.P;
   uint32_t roff[2 * NT];
@@ -496,7 +485,10 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
     const size_t left = (size_t)(a.nc - nf) * cstride - (size_t)p * a.P * 8;
     const __amdgpu_buffer_rsrc_t rw =
         pair_rsrc(Wb + (size_t)nf * a.M * a.nt, (uint32_t)min(left, (size_t)0x7ffffff0));
-    const int col = 16 * tile + mycol;
+    // Lane (li, lh) holds row li: columns 2 lh (registers 0, 1) and 8 + 2 lh
+    // (registers 2, 3).  Lanes li < 8 and li + 8 swap halves, so that an
+    // instruction writes whole 16-column (128-byte) segments of eight rows.
+    const int col = 16 * tile + ((lane & 8) ? 8 : 0) + 2 * lh;
     const int n = qdiv(col, a.invPP), j = col - n * a.PP;
     const uint32_t off = (uint32_t)(n - nf) * cstride + (uint32_t)j * 8u, m0 = col < a.ns ? 0u : kOOBPair;
     const bool tail = ODD && j + 1 == a.P;
@@ -508,8 +500,8 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
       floatx4 lo8, hi8;  // rows li & 7 and 8 + (li & 7)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        lo8[e] = swap8<0xc>(v0[e], v1[e]) * cn;
-        hi8[e] = swap8<0x3>(v1[e], v0[e]) * cn;
+        lo8[e] = swap8<0xc>(v0[e], v1[e]);
+        hi8[e] = swap8<0x3>(v1[e], v0[e]);
       }
       store16(rw, (off + roff[2 * i]) | mt, lo8);
       store16(rw, (off + roff[2 * i + 1]) | mt, hi8);
@@ -520,7 +512,6 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
     }
   };
   for (; ct < c_end; ct += 4) {
-    const float next = coil_scale(ct + 4);
     acc.clear();
     for (int grp = 0; grp < ng; ++grp) {
       const bool last = grp + 1 == ng;
@@ -533,7 +524,6 @@ __global__ __launch_bounds__(256, 2) void k_expand_pair(PairExpand a) {
       }
     }
     store(ct);
-    cn = next;
   }
 }
 
@@ -557,15 +547,16 @@ __global__ __launch_bounds__(256) void k_pair_max(const double2* __restrict__ A,
   if (threadIdx.x == 0) amax[row] = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
 }
 
-// The scales of group blockIdx.x: ascale[k] brings row k's largest component
+// The scales of patch blockIdx.x's group: ascale[k] brings row k's largest component
 // under 2^15; amin is the smallest of them, that of the largest row.  A row of
 // zeros, or one past K, takes amin, so that its data keep their size and, being
-// multiplied by zeros, cannot set the scale of others: arel is 0 for it.
-__global__ __launch_bounds__(256) void k_pair_scales(const float* __restrict__ amax, int K, int kp,
-                                                     float* __restrict__ ascale, float* __restrict__ arel,
-                                                     float* __restrict__ amin) {
+// multiplied by zeros, cannot set the scale of others: arel is 0 for it.  (arel and
+// amin by patch, so that the expanding form reads them with its first loads.)
+__global__ __launch_bounds__(256) void k_pair_scales(const float* __restrict__ amax, const int* __restrict__ pgroup,
+                                                     int K, int kp, float* __restrict__ ascale,
+                                                     float* __restrict__ arel, float* __restrict__ amin) {
   __shared__ float sh[4];
-  const int g = blockIdx.x, tid = threadIdx.x;
+  const int p = blockIdx.x, g = pgroup[p], tid = threadIdx.x;
   const float* m = amax + (size_t)g * K;
   float lo = INFINITY;
   for (int k = tid; k < K; k += 256) lo = m[k] > 0.f ? fminf(lo, pair_scale(m[k])) : lo;
@@ -578,10 +569,10 @@ __global__ __launch_bounds__(256) void k_pair_scales(const float* __restrict__ a
   for (int k = tid; k < kp; k += 256) {
     const bool on = k < K && m[k] > 0.f;
     const float s = on ? pair_scale(m[k]) : lo;
-    ascale[(size_t)g * kp + k] = s;
-    arel[(size_t)g * kp + k] = on ? lo / s : 0.f;
+    ascale[(size_t)g * kp + k] = s;  // the same from every patch of the group
+    arel[(size_t)p * kp + k] = on ? lo / s : 0.f;
   }
-  if (tid == 0) amin[g] = lo;
+  if (tid == 0) amin[p] = lo;
 }
 
 // (s, a power of two, may lie outside the range of a float: the product does not)
@@ -626,31 +617,35 @@ __global__ __launch_bounds__(256) void k_pair_bank(const double2* __restrict__ A
   }
 }
 
-// Set-up, one coil per work-group: cscale[n] = e, the mean exponent of the coil's
-// values that are neither zero nor non-finite, infinite if there is none.  (A mean, not a maximum:
-// one value of any size does not move it.  Sums of integers, so that a gain of
-// 2^m shifts e by m exactly and the order does not matter.)
-__global__ __launch_bounds__(1024) void k_coil_scale(const float2* __restrict__ coils, size_t npix,
-                                                     float* __restrict__ cscale) {
+// Set-up, one coil per work-group: mean and largest exponent of the coil's values
+// that are neither zero nor non-finite (both infinite if there is none).  (A mean:
+// one value of any size does not move it.  Sums of integers: no order matters.)
+__global__ __launch_bounds__(1024) void k_coil_size(const float2* __restrict__ coils, size_t npix,
+                                                    float2* __restrict__ size) {
   __shared__ long long ss[16], sn[16];
+  __shared__ int sm[16];
   const int tid = threadIdx.x;
   const float2* c = coils + (size_t)blockIdx.x * npix;
   long long s = 0, cnt = 0;
+  int m = -127;
 #pragma unroll 8
   for (size_t i = tid; i < npix; i += 1024) {
     const int e = (int)(__float_as_uint(fabsf(c[i].x) + fabsf(c[i].y)) >> 23);
     const bool ok = e > 0 && e < 255;
     s += ok ? e - 127 : 0;
     cnt += ok;
+    m = max(m, ok ? e - 127 : m);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     s += __shfl_xor(s, off, 64);
     cnt += __shfl_xor(cnt, off, 64);
+    m = max(m, __shfl_xor(m, off, 64));
   }
   if ((tid & 63) == 0) {
     ss[tid >> 6] = s;
     sn[tid >> 6] = cnt;
+    sm[tid >> 6] = m;
   }
   __syncthreads();
   if (tid) return;
@@ -658,35 +653,25 @@ __global__ __launch_bounds__(1024) void k_coil_scale(const float2* __restrict__ 
   for (int w = 0; w < 16; ++w) {
     s += ss[w];
     cnt += sn[w];
+    m = max(m, sm[w]);
   }
-  long long e = cnt ? s / cnt : 0;
-  if (cnt && e * cnt > s) --e;  // floor
-  cscale[blockIdx.x] = cnt ? (float)e : INFINITY;
+  size[blockIdx.x] = cnt ? make_float2((float)((double)s / (double)cnt), (float)m) : make_float2(INFINITY, INFINITY);
 }
-// One work-group: cscale[n] = 2^(emin - e), at least 2^-60.  At most 1, so that its
-// product with W's scale is a float whatever the coils' gains.
-__global__ __launch_bounds__(256) void k_coil_scale_rel(float* __restrict__ cscale, int nc) {
-  __shared__ float sh[4];
-  const int tid = threadIdx.x;
-  float lo = INFINITY;
-  for (int n = tid; n < nc; n += 256) lo = fminf(lo, cscale[n]);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) lo = fminf(lo, __shfl_xor(lo, off, 64));
-  if ((tid & 63) == 0) sh[tid >> 6] = lo;
-  __syncthreads();
-  lo = fminf(fminf(sh[0], sh[1]), fminf(sh[2], sh[3]));
-  for (int n = tid; n < nc; n += 256) {
-    const float e = cscale[n];
-    cscale[n] = e < INFINITY ? __uint_as_float((uint32_t)(127 - min(60, (int)(e - lo))) << 23) : 1.f;
-  }
+
+__global__ void k_scale_coils(const float2* __restrict__ coils, size_t npix, const float* __restrict__ cscale,
+                              float2* __restrict__ out) {
+  const float c = cscale[blockIdx.y];
+  const size_t base = (size_t)blockIdx.y * npix;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < npix; i += (size_t)gridDim.x * 256)
+    out[base + i] = make_float2(coils[base + i].x * c, coils[base + i].y * c);
 }
 
 // Set-up, one row y per work-group: coilmax[y][x], rowp[y], and the row's scales
 // set to one.  |re| + |im| bounds a modulus.  (fmaxf drops a NaN; the row of W
 // that it reaches is NaN under any scale.)
 __global__ __launch_bounds__(256) void k_pair_setup(const float2* __restrict__ coils, const float2* __restrict__ psf,
-                                                    const float* __restrict__ cscale, int nc, int nx, int ny, int nt,
-                                                    int B, float* __restrict__ coilmax, float* __restrict__ rowp,
+                                                    int nc, int nx, int ny, int nt, int B,
+                                                    float* __restrict__ coilmax, float* __restrict__ rowp,
                                                     float* __restrict__ wscale) {
   __shared__ float sh[4];
   const int y = blockIdx.x, tid = threadIdx.x;
@@ -695,7 +680,7 @@ __global__ __launch_bounds__(256) void k_pair_setup(const float2* __restrict__ c
 #pragma unroll 4
     for (int n = 0; n < nc; ++n) {
       const float2 c = coils[((size_t)n * ny + y) * nx + x];
-      m = fmaxf(m, (fabsf(c.x) + fabsf(c.y)) * cscale[n]);
+      m = fmaxf(m, fabsf(c.x) + fabsf(c.y));
     }
     coilmax[(size_t)y * nx + x] = m;
   }
@@ -721,7 +706,7 @@ int pair_wm(int K) {
 }
 // Column tiles at most: as many as leave the accumulators and the loads in flight
 // in registers (ten waves have 168 each, the others 256 or more).
-constexpr int pair_max_nt(int wm) { return wm == 2 ? 6 : wm == 3 ? 7 : wm == 5 ? 5 : 8; }
+constexpr int pair_max_nt(int wm) { return wm == 2 ? 5 : wm == 3 ? 7 : wm == 5 ? 4 : 8; }
 int pair_nt(int variant, int wm) { return std::min(8 - variant, pair_max_nt(wm)); }
 
 template <int WM, bool ODD>
@@ -733,7 +718,7 @@ void launch_compress_nt(StageScope& sc, hipStream_t s, int nt, const PairCompres
     case 2: sc.launch(k_compress_pair<WM, 2, ODD>, grid, dim3(thr), 0, s, a); break;
     case 3: sc.launch(k_compress_pair<WM, 3, ODD>, grid, dim3(thr), 0, s, a); break;
     case 4: sc.launch(k_compress_pair<WM, 4, ODD>, grid, dim3(thr), 0, s, a); break;
-    case 5: sc.launch(k_compress_pair<WM, 5, ODD>, grid, dim3(thr), 0, s, a); break;
+    case 5: sc.launch(k_compress_pair<WM, std::min(5, N), ODD>, grid, dim3(thr), 0, s, a); break;
     case 6: sc.launch(k_compress_pair<WM, std::min(6, N), ODD>, grid, dim3(thr), 0, s, a); break;
     case 7: sc.launch(k_compress_pair<WM, std::min(7, N), ODD>, grid, dim3(thr), 0, s, a); break;
     default: sc.launch(k_compress_pair<WM, N, ODD>, grid, dim3(thr), 0, s, a); break;
@@ -783,11 +768,14 @@ size_t place_pair_scales(Plan& pl) {
   };
   take(&pl.wscale, (size_t)pl.B * pl.ny);
   take(&pl.cscale, pl.nc);
+  float* size = nullptr;
+  take(&size, 2 * (size_t)pl.nc);
+  pl.coilsize = reinterpret_cast<float2*>(size);
   take(&pl.coilmax, (size_t)pl.ny * pl.nx);
   take(&pl.rowp, pl.ny);
   take(&pl.ascale, (size_t)pl.G * pl.Kp);
-  take(&pl.arel, (size_t)pl.G * pl.Kp);
-  take(&pl.amin, pl.G);
+  take(&pl.arel, (size_t)pl.np * pl.Kp);
+  take(&pl.amin, pl.np);
   take(&pl.amax, (size_t)pl.G * pl.K);
   return used;
 }
@@ -808,19 +796,47 @@ bool pair_expand_ok(const Plan& pl) {
          (size_t)(16 / pl.P + 2) * pl.ny * pl.nt * 8 < kOOBPair;
 }
 
+// c[n] in steps of 2^16, at most 2^64 and no value of the map above 2^100: a pair
+// has room for less.  Coil maps within 2^16 of each other, which is all but a
+// set-up of very unequal gains, keep c = 1 and need no copy.
 int setup_pair(Plan& pl) {
-  hipLaunchKernelGGL(k_coil_scale, dim3(pl.nc), dim3(1024), 0, pl.stream, pl.coils, (size_t)pl.ny * pl.nx, pl.cscale);
-  hipLaunchKernelGGL(k_coil_scale_rel, dim3(1), dim3(256), 0, pl.stream, pl.cscale, pl.nc);
-  hipLaunchKernelGGL(k_pair_setup, dim3(pl.ny), dim3(256), 0, pl.stream, pl.coils, pl.psf, pl.cscale, pl.nc, pl.nx, pl.ny, pl.nt,
-                     pl.B, pl.coilmax, pl.rowp, pl.wscale);
+  const size_t npix = (size_t)pl.ny * pl.nx;
+  std::vector<float2> size(pl.nc);
+  std::vector<float> c(pl.nc, 1.f);
+  hipLaunchKernelGGL(k_coil_size, dim3(pl.nc), dim3(1024), 0, pl.stream, pl.coils, npix, pl.coilsize);
   GPJC_HIP(hipGetLastError());
+  GPJC_HIP(hipMemcpyAsync(size.data(), pl.coilsize, sizeof(float2) * pl.nc, hipMemcpyDeviceToHost, pl.stream));
+  GPJC_HIP(hipStreamSynchronize(pl.stream));
+  float most = -INFINITY;
+  for (const float2& e : size)
+    if (e.x < INFINITY) most = std::max(most, e.x);
+  bool any = false;
+  for (int n = 0; n < pl.nc; ++n)
+    if (size[n].x < INFINITY) {
+      const int steps = (int)std::min({(most - size[n].x) / 16.f, 4.f, std::max(0.f, (100.f - size[n].y) / 16.f)});
+      c[n] = std::ldexp(1.f, 16 * steps);
+      any = any || steps > 0;
+    }
+  GPJC_HIP(hipMemcpyAsync(pl.cscale, c.data(), sizeof(float) * pl.nc, hipMemcpyHostToDevice, pl.stream));
+  pl.coils_pair = pl.coils;
+  if (any) {
+    float2* p = nullptr;
+    GPJC_HIP(hipMalloc(reinterpret_cast<void**>(&p), sizeof(float2) * pl.nc * npix));
+    pl.coils_pair = p;
+    hipLaunchKernelGGL(k_scale_coils, dim3((unsigned)std::min<size_t>((npix + 255) / 256, 1024), pl.nc), dim3(256), 0,
+                       pl.stream, pl.coils, npix, pl.cscale, p);
+  }
+  hipLaunchKernelGGL(k_pair_setup, dim3(pl.ny), dim3(256), 0, pl.stream, pl.coils_pair, pl.psf, pl.nc, pl.nx, pl.ny,
+                     pl.nt, pl.B, pl.coilmax, pl.rowp, pl.wscale);
+  GPJC_HIP(hipGetLastError());
+  GPJC_HIP(hipStreamSynchronize(pl.stream));  // `c` is a host temporary
   return GPJC_OK;
 }
 
 int launch_pair_bank(const Plan& pl) {
   hipLaunchKernelGGL(k_pair_max, dim3(pl.K, pl.G), dim3(256), 0, pl.stream, pl.A128, pl.nc, pl.P, pl.cscale, pl.amax);
-  hipLaunchKernelGGL(k_pair_scales, dim3(pl.G), dim3(256), 0, pl.stream, pl.amax, pl.K, pl.Kp, pl.ascale, pl.arel,
-                     pl.amin);
+  hipLaunchKernelGGL(k_pair_scales, dim3(pl.np), dim3(256), 0, pl.stream, pl.amax, pl.pgroup, pl.K, pl.Kp, pl.ascale,
+                     pl.arel, pl.amin);
   const size_t words = (pair_compress_words(pl) + pair_expand_words(pl)) / 2;
   hipLaunchKernelGGL(k_pair_bank, dim3((unsigned)std::min<size_t>((words + 255) / 256, 8192)), dim3(256), 0, pl.stream,
                      pl.A128, pl.cscale, pl.ascale, pl.Ac2, pl.Ae2, pl.G, pl.K, pl.nc, pl.P, pair_pp(pl),
@@ -834,28 +850,17 @@ static long pair_groups(const Plan& pl, int nt) {
   return (long)ceil_div(pl.ny, 16 * nt) * ceil_div(ceil_div(pl.K, 16), pair_wm(pl.K)) * pl.B * pl.np;
 }
 
-// Column tiles of the expanding form: the count that takes the least time by its
-// tiles, padding included, and their relative time, which more of them lower while
-// three work-groups are resident per CU and the bank is read less often for it (the
-// longer its rows, the more that gives); then fewer while the launch cannot give
-// every CU a work-group with a column tile per wave.  Measured for 1 to 8 tiles, us:
-// 2 x 230 rows of 180, K = 24: 35.2, 30.6, 28.9, 29.3, 33.1, 36.7, 40.8, 36.5; 4 x 112 rows,
-// K = 30: 16.9, 14.2, 16.0, 14.3, 16.4, 21.0, 17.0, 18.6; 256 rows, K = 80: 27.1, 24.6, 22.1,
-// 21.0, 23.7, 26.7, 27.4, 28.6; W of 4.8 GB, K = 56: 1872, 1652, 1390, 1322, 1175, 1193,
-// 1194, 1280.
+// Column tiles of the expanding form: the largest count that fits the LDS and
+// pads the rows by at most an eighth (a larger one reads the bank less often, and
+// writes W in longer runs for the readout stage to read), then smaller ones while the
+// launch cannot give every CU a work-group with a column tile per wave.  Measured for
+// 4 and 8 tiles, a whole operator, us: 32 x 64 rows of 48, K = 12, 191 and 185; 2 x 230 rows
+// of 180, K = 24, encode and adjoint, 180 and 183; W of 4.8 GB, the kernel alone, 1322 and
+// 1192.
 static int pair_expand_tiles(const Plan& pl) {
-  static const double kTime[2][5] = {{1.3, 1.05, 1.0, 1.0, 1.1}, {1.4, 1.2, 1.05, 1.05, 1.0}};
   const int n = ceil_div(pl.ny, 16), ct = ceil_div(pair_ns(pl), 16);
-  const int most = std::min(std::min(n, 5), kExpandLds / (2048 * (pl.Kp / 16)));
-  int t = 1;
-  double best = 1e30;
-  for (int i = most; i >= 1; --i) {
-    const double us = ceil_div(n, i) * i * kTime[pl.Kp > 32][i - 1];
-    if (us < best) {
-      best = us;
-      t = i;
-    }
-  }
+  int t = std::min(n, std::max(1, std::min(8, kExpandLds / (2048 * (pl.Kp / 16)))));
+  while (t > 1 && 8 * ceil_div(n, t) * t > 9 * n) --t;
   while (t > 1 && (long)ceil_div(n, t) * pl.B * pl.np * ceil_div(ct, 4) < 256) --t;
   return t;
 }
@@ -868,8 +873,8 @@ static int pair_resident(int wm, int nt) {
 }
 
 // Column tiles and split of the compressing form by the time they are
-// expected to take: a work-group needs about 0.25 + 0.14 NT us (for WK = 2) per
-// k-tile once its loads are in flight, half as long again for each work-group that
+// expected to take: a work-group needs about 1.5 us to fill and drain and 0.25 + 0.14
+// NT us (for WK = 2) per k-tile, 0.4 times as long again for each work-group that
 // shares the CU, the launch as many such rounds as its work-groups make, and every
 // split writes and reads back a partial of Z at about 5 TB/s.  No split where the
 // launch has four work-groups per CU without one: there it adds partials of Z and no
@@ -888,8 +893,8 @@ void default_pair_config(const Plan& pl, Plan::GemmCfg& g) {
     const int res = pair_resident(wm, t), most = groups >= 1024 ? 1 : std::min(kMaxKsplit, ntile);
     for (int ks = 1; ks <= most; ++ks) {
       const long per_cu = (groups * ks + 255) / 256, rem = per_cu % res;
-      const double rounds = per_cu / res * (0.5 + 0.5 * res) + (rem ? 0.5 + 0.5 * rem : 0.0);
-      const double us = rounds * ceil_div(ntile, ks) * (0.25 + 0.14 * t) * wk / 2 + zus * ks + 0.3 * (ks - 1);
+      const double rounds = per_cu / res * (0.6 + 0.4 * res) + (rem ? 0.6 + 0.4 * rem : 0.0);
+      const double us = rounds * (ceil_div(ntile, ks) * (0.25 + 0.14 * t) * wk / 2 + 1.5) + zus * ks + 0.3 * (ks - 1);
       if (us < best) {
         best = us;
         g.cvar = 8 - t;
@@ -916,7 +921,6 @@ int launch_compress_pair(const Plan& pl, StageScope& sc, const void* in, float2*
   a.out = out;
   a.pgroup = pl.pgroup;
   a.ascale = pl.ascale;
-  a.cscale = pl.cscale;
   a.wscale = pl.wscale;
   a.MT = ceil_div(pl.K, 16);
   a.KB = pair_kblocks(pair_ns(pl));
@@ -955,7 +959,6 @@ int launch_expand_pair(const Plan& pl, StageScope& sc) {
   a.pgroup = pl.pgroup;
   a.arel = pl.arel;
   a.amin = pl.amin;
-  a.cscale = pl.cscale;
   a.CT = ceil_div(pair_ns(pl), 16);
   a.KBk = kbk;
   a.M = pl.ny;

@@ -120,12 +120,14 @@ struct Plan {
   uint32_t* Ae2 = nullptr;  // expanding
   float* scales = nullptr;  // the arrays below, in one allocation (place_pair_scales)
   float* wscale = nullptr;  // [B][ny] scale of W's rows, written by the readout forward
-  float* cscale = nullptr;  // [nc] power of two, at most 1, that brings the coils' maps to one size
+  float* cscale = nullptr;  // [nc] power of two that brings the coils' maps to about one size
+  float2* coils_pair = nullptr;  // [nc][ny][nx] coil maps times cscale: coils itself where that is 1 throughout
+  float2* coilsize = nullptr;    // [nc] mean and largest exponent of a coil's map
   float* coilmax = nullptr; // [ny][nx] largest coil value of every pixel, coils scaled by cscale
   float* rowp = nullptr;    // [ny] max|psf| / sqrt(nt) of every row
   float* ascale = nullptr;  // [G][Kp] power-of-two scale of the pairs of a bank row
-  float* arel = nullptr;    // [G][Kp] smallest scale of the group / ascale: the row's size beside the largest
-  float* amin = nullptr;    // [G] that smallest scale
+  float* arel = nullptr;    // [np][Kp] smallest scale of the patch's group / ascale: the row's size beside the largest
+  float* amin = nullptr;    // [np] that smallest scale
   float* amax = nullptr;    // [G][K] maxima of the bank's rows
 
   // device: workspaces

@@ -319,7 +319,12 @@ int gpjc_stage_times(gpjc_plan* plan, double* h_ms, int* h_launches);
 /* Work-group tile shape of the two group contractions and the contraction
  * split of the compressing one (1..8), for one precision class: FP32, the
  * two 16-bit types together (BF16 and FP16 share one setting), or BF16X6.  Variant
- * numbers index per-class tables of built shapes.  The defaults come from
+ * numbers index per-class tables of built shapes; in the FP32 class variant v
+ * takes 8 - v tiles of 16 image rows per work-group, or as many as its
+ * registers and LDS allow (K above 512, and patches of a few samples of very
+ * large volumes, have one fixed shape for that direction).  A split of the
+ * FP32 class is not carried out where the launch has 1024 work-groups without
+ * one; gpjc_get_gemm_config returns the split as set.  The defaults come from
  * the plan's sizes; gpjc_autotune times the variants and installs the
  * fastest.  Changes only speed, never results beyond FP32 summation order. */
 int gpjc_set_gemm_config(gpjc_plan* plan, gpjc_prec prec, int compress_variant, int expand_variant, int ksplit);

@@ -1070,14 +1070,12 @@ void launch_expand_v(StageScope& sc, hipStream_t s, const ExpandArgs& a) {
   else launch_expand_general<ST>(sc, s, a);
 }
 // FP32 MFMA: the taller row tile unless it pads more than an eighth of the rows.
+bool f32_tall(int K) { return 8 * (tiles(K, 64) * 64 - K) <= tiles(K, 64) * 64; }
 void compress_f32(StageScope& sc, hipStream_t s, const CompressArgs& a) {
   constexpr Shape S = kCompressLds64, L = kCompressLds32;
-  const int padded = tiles(a.K, 64) * 64;
   if (!compress_staged(a, Store::F32)) launch_compress_general<Store::F32>(sc, s, a);
-  else if (8 * (padded - a.K) <= padded)
-    launch_compress_lds<S.wm, S.wn, S.mt, S.nt, S.depth, Store::F32>(sc, s, a);
-  else
-    launch_compress_lds<L.wm, L.wn, L.mt, L.nt, L.depth, Store::F32>(sc, s, a);
+  else if (f32_tall(a.K)) launch_compress_lds<S.wm, S.wn, S.mt, S.nt, S.depth, Store::F32>(sc, s, a);
+  else launch_compress_lds<L.wm, L.wn, L.mt, L.nt, L.depth, Store::F32>(sc, s, a);
 }
 void expand_f32(StageScope& sc, hipStream_t s, const ExpandArgs& a) {
   constexpr Shape S = kExpandLdsF32;
@@ -1170,7 +1168,8 @@ int gemm_expand_variants() { return kNumShapes; }
 // Defaults: for the compressing contraction the work-group shape with the
 // tallest row tile that pads at most 1/8 of its rows (128, 64 or 32 of the 2K
 // real rows), else the shortest; for the expanding one shape 0; and a split
-// giving about 504 work-groups.  FP32: default_pair_config.
+// giving about 504 work-groups.  FP32: default_pair_compress and default_pair_expand
+// where its contractions run on pairs.
 int compress_shape_for_rows(int rows, Store st) {
   const int order16[3] = {0, 7, 6}, orderx6[3] = {0, 3, 6};
   const int* order = st == Store::BF16X6 ? orderx6 : order16;
@@ -1184,15 +1183,19 @@ int compress_shape_for_rows(int rows, Store st) {
 void default_gemm_config(Plan& pl) {
   for (const Store st : {Store::F32, Store::BF16, Store::BF16X6}) {
     Plan::GemmCfg& g = pl.cfg(st);
-    if (st == Store::F32 && pair_compress_ok(pl)) {
-      default_pair_config(pl, g);
+    const bool f32 = st == Store::F32;
+    g.evar = 0;
+    if (f32 && pair_expand_ok(pl)) default_pair_expand(pl, g);
+    if (f32 && pair_compress_ok(pl)) {
+      default_pair_compress(pl, g);
       continue;
     }
-    const int rows = 2 * pl.K;
-    g.cvar = st == Store::F32 ? 0 : compress_shape_for_rows(rows, st);
-    g.evar = 0;
-    const Shape S = st == Store::BF16X6 ? kCompressSplit[g.cvar] : kCompressLds16[g.cvar];
-    const long t = (long)tiles(pl.ny, S.wn * S.nt * 16) * tiles(rows, S.wm * S.mt * 16) * pl.B * pl.np;
+    const int rows = f32 ? pl.K : 2 * pl.K;  // complex rows in FP32, real rows otherwise
+    g.cvar = f32 ? 0 : compress_shape_for_rows(rows, st);
+    const Shape S = f32 ? (f32_tall(pl.K) ? kCompressLds64 : kCompressLds32)
+                        : st == Store::BF16X6 ? kCompressSplit[g.cvar] : kCompressLds16[g.cvar];
+    const int T = f32 ? 32 : 16;
+    const long t = (long)tiles(pl.ny, S.wn * S.nt * T) * tiles(rows, S.wm * S.mt * T) * pl.B * pl.np;
     // work-groups: measured best for E'^H E' on the 224 x 224, 32-coil slice
     // (the phase-encode stage reads one partial of Z per split)
     const long target = 504;
@@ -1211,7 +1214,7 @@ bool compress_split_staged(const Plan& pl, Store st, int ksplit) {
 }
 
 int compress_partials(const Plan& pl, Store st) {
-  return st == Store::F32 && pair_compress_ok(pl) ? pair_partials(pl) : pl.cfg(st).ksplit;
+  return st == Store::F32 && pair_compress_ok(pl) ? pair_partials(pl, pl.cfg(st)) : pl.cfg(st).ksplit;
 }
 
 int launch_group_compress(const Plan& pl, Store st) {

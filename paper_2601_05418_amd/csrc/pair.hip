@@ -882,7 +882,7 @@ static int pair_resident(int wm, int nt) {
 // 7 tiles 45, 29, 25; 5 tiles 36, 25, 34; 3 tiles 28, 30, 32; one split: 2 x 230 rows of
 // 180, P = 15, K = 24, 1, 2, 3, 4, 6 tiles: 33.5, 31.8, 36.0, 39.1, 43.8; 4 x 112 rows, K = 30:
 // 19.7, 16.4, 21.9, 18.9, 27.5; 64 x 192 rows, K = 56: 1869, 1486, 1466, 1564, 1444 (8: 1325).
-void default_pair_config(const Plan& pl, Plan::GemmCfg& g) {
+void default_pair_compress(const Plan& pl, Plan::GemmCfg& g) {
   const int n = ceil_div(pl.ny, 16), wm = pair_wm(pl.K), wk = pair_wk(wm), ntile = ceil_div(pair_ns(pl), 16 * wk);
   const double zus = 16.0 * pl.K * pl.ny * pl.np * pl.B / 5e6;
   double best = 1e30;
@@ -902,13 +902,12 @@ void default_pair_config(const Plan& pl, Plan::GemmCfg& g) {
       }
     }
   }
-  g.evar = 8 - pair_expand_tiles(pl);
 }
+void default_pair_expand(const Plan& pl, Plan::GemmCfg& g) { g.evar = 8 - pair_expand_tiles(pl); }
 
-// The configured split, or 1 where the launch has four work-groups per CU
-// without one: there a split adds partials of Z and no parallelism.
-int pair_partials(const Plan& pl) {
-  const Plan::GemmCfg& cfg = pl.cfg(Store::F32);
+// Partials of Z that a split leaves: 1 where the launch has four work-groups per CU
+// without one (a tuned choice of a smaller plan's bucket, or a caller's).
+int pair_partials(const Plan& pl, const Plan::GemmCfg& cfg) {
   return pair_groups(pl, pair_nt(cfg.cvar, pair_wm(pl.K))) >= 1024 ? 1 : cfg.ksplit;
 }
 
@@ -934,7 +933,7 @@ int launch_compress_pair(const Plan& pl, StageScope& sc, const void* in, float2*
   a.K = pl.K;
   a.Kp = pl.Kp;
   a.B = pl.B;
-  a.ksplit = pair_partials(pl);
+  a.ksplit = pair_partials(pl, cfg);
   a.tps = ceil_div(ceil_div(a.ns, kt), a.ksplit);
   a.split_stride = (size_t)pl.B * pl.np * pl.K * pl.ny;
   a.invPP = 1.f / (float)a.PP;

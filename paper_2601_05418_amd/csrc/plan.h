@@ -225,8 +225,9 @@ size_t pair_compress_words(const Plan& pl);
 size_t pair_expand_words(const Plan& pl);
 int setup_pair(Plan& pl);
 int launch_pair_bank(const Plan& pl);
-void default_pair_config(const Plan& pl, Plan::GemmCfg& g);
-int pair_partials(const Plan& pl);
+void default_pair_compress(const Plan& pl, Plan::GemmCfg& g);
+void default_pair_expand(const Plan& pl, Plan::GemmCfg& g);
+int pair_partials(const Plan& pl, const Plan::GemmCfg& cfg);
 int launch_compress_pair(const Plan& pl, StageScope& sc, const void* in, float2* out);
 int launch_expand_pair(const Plan& pl, StageScope& sc);
 // Whether the staged compressing forms can address the readout-stage output

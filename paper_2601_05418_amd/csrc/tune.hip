@@ -123,12 +123,16 @@ int measure(Plan& pl, Store st, Choice* out, float* us_c, float* us_e) {
   // timed when another split keeps them
   bool any_staged = false;
   for (int ks : splits) any_staged = any_staged || (ks <= kMaxKsplit && compress_split_staged(pl, st, ks));
-  for (int v = 0; status == GPJC_OK && v < gemm_compress_variants(); ++v)
+  for (int v = 0; status == GPJC_OK && v < gemm_compress_variants(); ++v) {
+    unsigned timed = 0;  // splits that run (compress_partials): one that runs as another is not timed again
     for (int ks : splits) {
       if (status != GPJC_OK || ks > kMaxKsplit || (ks > 1 && kd / ks < 64)) continue;
       if (any_staged && !compress_split_staged(pl, st, ks)) continue;
       cfg.cvar = v;
       cfg.ksplit = ks;
+      const unsigned bit = 1u << compress_partials(pl, st);
+      if (timed & bit) continue;
+      timed |= bit;
       float us = 0.f;
       status = time_us(
           pl, ev.a, ev.b,
@@ -143,6 +147,7 @@ int measure(Plan& pl, Store st, Choice* out, float* us_c, float* us_e) {
         best.ksplit = ks;
       }
     }
+  }
   for (int v = 0; status == GPJC_OK && v < gemm_expand_variants(); ++v) {
     cfg.evar = v;
     float us = 0.f;

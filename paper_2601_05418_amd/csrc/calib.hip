@@ -209,6 +209,9 @@ __global__ __launch_bounds__(256) void k_gram_q(const double2* __restrict__ cw, 
 // Bound by FP64 issue and LDS reads (16 multiply-adds on 12 reads).  528 pairs,
 // 42 groups, P = 32, 224 rows: 3.8 ms; 7 ms with the PSF product formed for each
 // pair and three reads per element.
+// Pair groups lie along y and z, at most kPairsY along y (a grid has 65536 rows;
+// one-sample patches of 800 coils make 80100 groups).
+constexpr unsigned kPairsY = 32768;
 constexpr int kAD = 4;             // elements along a diagonal per thread
 constexpr int kAsmThreads = 320;   // at most; P = 32 has 8 x 35 threads' work
 template <int PB>
@@ -223,6 +226,8 @@ __global__ __launch_bounds__(kAsmThreads) void k_gram_assemble(const double2* __
   constexpr bool pad = PB > 1;
   constexpr int e3 = pad ? kAD - 1 : 0;
   const int ls = P + 2 * e3, lk = pad ? (P + kAD - 1) / kAD * kAD : P, lq = nd + e3, npair = nc * (nc + 1) / 2;
+  const int grp = blockIdx.z * gridDim.y + blockIdx.y;
+  if (grp * PB >= npair) return;
   extern __shared__ double2 sma[];
   double2* pj = sma;           // [ay][ls]     q_g(iy) psf[iy][t0 + j], from -e3
   double2* pk = pj + ay * ls;  // [ay][lk]     psf[iy][t0 + k]
@@ -231,7 +236,7 @@ __global__ __launch_bounds__(kAsmThreads) void k_gram_assemble(const double2* __
   int pn[PB], pm[PB];
 #pragma unroll
   for (int p = 0; p < PB; ++p) {
-    const int pair = min((int)blockIdx.y * PB + p, npair - 1);
+    const int pair = min(grp * PB + p, npair - 1);
     int n = 0, base = 0;
     while (base + nc - n <= pair) {
       base += nc - n;
@@ -294,7 +299,7 @@ __global__ __launch_bounds__(kAsmThreads) void k_gram_assemble(const double2* __
   double2* Hg = H + (size_t)g * nsp * nsp;
 #pragma unroll
   for (int p = 0; p < PB; ++p) {
-    if ((int)blockIdx.y * PB + p >= npair) break;
+    if (grp * PB + p >= npair) break;
 #pragma unroll
     for (int e = 0; e < kAD; ++e)
       if (k0 + e < P && j + e >= 0 && j + e < P)
@@ -571,7 +576,7 @@ static int calibrate_in(Plan& pl, Scratch& s, const uint8_t* roi, const float2* 
     const int qx = (int)std::min<size_t>(16, kGramLds / qrow - 1);
     // four coil pairs per work-group of the assembly, one where a staged row of
     // four would not fit (patches above 400); eight rows at a time leave room for
-    // four work-groups per CU at P = 32
+    // three work-groups per CU at P = 32 (43 KB each)
     const int pb = assemble_row(P, 4) <= kGramLds ? 4 : 1;
     const size_t arow = assemble_row(P, pb);
     const int ay = (int)std::min<size_t>(8, kGramLds / arow);
@@ -581,7 +586,8 @@ static int calibrate_in(Plan& pl, Scratch& s, const uint8_t* roi, const float2* 
     GPJC_HIP(hipGetLastError());
     const int items = (P + kAD - 1) / kAD * (P + kAD - 1), ntile = (items + kAsmThreads - 1) / kAsmThreads;
     const int threads = ((items + ntile - 1) / ntile + 63) / 64 * 64, npair = pl.nc * (pl.nc + 1) / 2;
-    const dim3 ga(G * ntile, (npair + pb - 1) / pb);
+    const unsigned groups = (npair + pb - 1) / pb, gy = std::min(groups, kPairsY);
+    const dim3 ga(G * ntile, gy, (groups + gy - 1) / gy);
     const size_t la = arow * ay;
     if (pb == 4)
       hipLaunchKernelGGL(k_gram_assemble<4>, ga, dim3(threads), la, st, Qg, pl.psf, qinv, t0s, H, pl.nc, P, pl.ny, pl.nt,

@@ -304,8 +304,10 @@ static int setup_plan(Plan& pl, const gpjc_geom* g, const gpjc_c64* d_coils, con
         }
     }
   }
+  int unequal = 0;
+  if (pl.scales) GPJC_HIP(hipMemcpyAsync(&unequal, pl.unequal, sizeof(int), hipMemcpyDeviceToHost, stream));
   GPJC_HIP(hipStreamSynchronize(stream));
-  return GPJC_OK;
+  return unequal ? scale_coils(pl) : GPJC_OK;
 }
 
 static bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }

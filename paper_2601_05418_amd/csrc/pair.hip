@@ -48,8 +48,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cmath>
-#include <vector>
 
 #include "devutil.h"
 #include "plan.h"
@@ -375,8 +373,9 @@ __global__ __launch_bounds__(64 * WM * pair_wk(WM)) void k_compress_pair(PairCom
 // its own maximum and split once, and its waves walk over tiles of 16 columns
 // (n, j), reading the bank's fragments from L2 one step ahead.  Columns lie on
 // the rows of the MFMA, permuted so that a lane's registers 0, 1 and 2, 3 are
-// neighbouring samples: each store instruction writes 64-byte segments of W
-// straight from the accumulators.
+// neighbouring samples, and neighbouring half-rows of lanes swap halves, so that a
+// store instruction writes whole 128-byte segments of W straight from the
+// accumulators.
 // ---------------------------------------------------------------------------
 struct PairExpand {
   const uint32_t* A;    // bank fragments [G][CT][KBk][hi, lo]
@@ -617,45 +616,113 @@ __global__ __launch_bounds__(256) void k_pair_bank(const double2* __restrict__ A
   }
 }
 
-// Set-up, one coil per work-group: mean and largest exponent of the coil's values
-// that are neither zero nor non-finite (both infinite if there is none).  (A mean:
-// one value of any size does not move it.  Sums of integers: no order matters.)
-__global__ __launch_bounds__(1024) void k_coil_size(const float2* __restrict__ coils, size_t npix,
-                                                    float2* __restrict__ size) {
-  __shared__ long long ss[16], sn[16];
-  __shared__ int sm[16];
-  const int tid = threadIdx.x;
-  const float2* c = coils + (size_t)blockIdx.x * npix;
-  long long s = 0, cnt = 0;
-  int m = -127;
-#pragma unroll 8
-  for (size_t i = tid; i < npix; i += 1024) {
-    const int e = (int)(__float_as_uint(fabsf(c[i].x) + fabsf(c[i].y)) >> 23);
-    const bool ok = e > 0 && e < 255;
-    s += ok ? e - 127 : 0;
-    cnt += ok;
-    m = max(m, ok ? e - 127 : m);
+// Set-up, rows y of one work-group: coilmax[y][x], rowp[y], and the row's scales
+// set to one (|re| + |im| bounds a modulus; fmaxf drops a NaN, and the row of W that
+// it reaches is NaN under any scale); with SIZES, over all rows, each coil's sum of
+// the exponents of its values that are neither zero nor non-finite, their number
+// and the largest.  (Integers: the order of the additions does not matter.)
+struct CoilSize {
+  long long sum;
+  int count, most;  // most: largest exponent + 128
+};
+constexpr int kMaxSizedCoils = 2048;
+template <bool SIZES>
+__global__ __launch_bounds__(256) void k_pair_setup(const float2* __restrict__ coils, const float2* __restrict__ psf,
+                                                    int nc, int nx, int ny, int nt, int B,
+                                                    float* __restrict__ coilmax, float* __restrict__ rowp,
+                                                    float* __restrict__ wscale, CoilSize* __restrict__ size) {
+  __shared__ float sh[4];
+  __shared__ int lsum[SIZES ? kMaxSizedCoils : 1], lcnt[SIZES ? kMaxSizedCoils : 1], lmax[SIZES ? kMaxSizedCoils : 1];
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (SIZES) {
+    for (int n = tid; n < nc; n += 256) lsum[n] = lcnt[n] = lmax[n] = 0;
+    __syncthreads();
   }
+  for (int y = blockIdx.x; y < ny; y += gridDim.x) {
+    for (int x0 = 0; x0 < nx; x0 += 256) {
+      const int x = x0 + tid;
+      float m = 0.f;
+      for (int n0 = 0; n0 < nc; n0 += 8) {  // eight coils' loads in flight
+        float v[8];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    s += __shfl_xor(s, off, 64);
-    cnt += __shfl_xor(cnt, off, 64);
-    m = max(m, __shfl_xor(m, off, 64));
+        for (int h = 0; h < 8; ++h) {
+          const float2 c = coils[((size_t)min(n0 + h, nc - 1) * ny + y) * nx + min(x, nx - 1)];
+          v[h] = x < nx && n0 + h < nc ? fabsf(c.x) + fabsf(c.y) : 0.f;
+        }
+#pragma unroll
+        for (int h = 0; h < 8; ++h) {
+          m = fmaxf(m, v[h]);
+          if (SIZES) {
+            const int e = (int)(__float_as_uint(v[h]) >> 23);
+            const bool ok = e > 0 && e < 255;
+            int s = ok ? e - 127 : 0, q = ok ? e + 1 : 0;
+            const int k = __popcll(__ballot(ok));
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+              s += __shfl_xor(s, off, 64);
+              q = max(q, __shfl_xor(q, off, 64));
+            }
+            if (lane == 0 && k) {
+              atomicAdd(&lsum[n0 + h], s);
+              atomicAdd(&lcnt[n0 + h], k);
+              atomicMax(&lmax[n0 + h], q);
+            }
+          }
+        }
+      }
+      if (x < nx) coilmax[(size_t)y * nx + x] = m;
+    }
+    float m = 0.f;
+    for (int t = tid; t < nt; t += 256) {
+      const float2 v = psf[(size_t)y * nt + t];
+      m = fmaxf(m, fabsf(v.x) + fabsf(v.y));
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    __syncthreads();
+    if (lane == 0) sh[tid >> 6] = m;
+    __syncthreads();
+    if (tid == 0) rowp[y] = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3])) * rsqrtf((float)nt);
+    for (int b = tid; b < B; b += 256) wscale[(size_t)b * ny + y] = 1.f;
   }
-  if ((tid & 63) == 0) {
-    ss[tid >> 6] = s;
-    sn[tid >> 6] = cnt;
-    sm[tid >> 6] = m;
+  if (SIZES) {
+    __syncthreads();
+    for (int n = tid; n < nc; n += 256)
+      if (lcnt[n]) {
+        atomicAdd(reinterpret_cast<unsigned long long*>(&size[n].sum), (unsigned long long)(long long)lsum[n]);
+        atomicAdd(&size[n].count, lcnt[n]);
+        atomicMax(&size[n].most, lmax[n]);
+      }
   }
+}
+
+// c[n] from the mean exponents, in steps of 2^16 (a pair has room for less), at most
+// 2^64 and no value above 2^100; *unequal is set if any is not one.  A mean: one
+// value of any size does not move it.  size NULL: c = 1 throughout.
+__global__ __launch_bounds__(256) void k_coil_scale(const CoilSize* __restrict__ size, int nc,
+                                                    float* __restrict__ cscale, int* __restrict__ unequal) {
+  __shared__ float sh[4];
+  const int tid = threadIdx.x;
+  auto mean = [&](int n) { return (float)((double)size[n].sum / (double)size[n].count); };
+  float most = -INFINITY;
+  if (size)
+    for (int n = tid; n < nc; n += 256)
+      if (size[n].count) most = fmaxf(most, mean(n));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off, 64));
+  if ((tid & 63) == 0) sh[tid >> 6] = most;
   __syncthreads();
-  if (tid) return;
-  s = cnt = 0;
-  for (int w = 0; w < 16; ++w) {
-    s += ss[w];
-    cnt += sn[w];
-    m = max(m, sm[w]);
+  most = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+  int any = 0;
+  for (int n = tid; n < nc; n += 256) {
+    int steps = 0;
+    if (size && size[n].count)
+      steps = min(min((int)((most - mean(n)) / 16.f), 4), max(0, (100 - (size[n].most - 128)) / 16));
+    cscale[n] = __uint_as_float((uint32_t)(127 + 16 * steps) << 23);
+    any |= steps;
   }
-  size[blockIdx.x] = cnt ? make_float2((float)((double)s / (double)cnt), (float)m) : make_float2(INFINITY, INFINITY);
+  any = __syncthreads_or(any);
+  if (tid == 0) *unequal = any != 0;
 }
 
 __global__ void k_scale_coils(const float2* __restrict__ coils, size_t npix, const float* __restrict__ cscale,
@@ -664,37 +731,6 @@ __global__ void k_scale_coils(const float2* __restrict__ coils, size_t npix, con
   const size_t base = (size_t)blockIdx.y * npix;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < npix; i += (size_t)gridDim.x * 256)
     out[base + i] = make_float2(coils[base + i].x * c, coils[base + i].y * c);
-}
-
-// Set-up, one row y per work-group: coilmax[y][x], rowp[y], and the row's scales
-// set to one.  |re| + |im| bounds a modulus.  (fmaxf drops a NaN; the row of W
-// that it reaches is NaN under any scale.)
-__global__ __launch_bounds__(256) void k_pair_setup(const float2* __restrict__ coils, const float2* __restrict__ psf,
-                                                    int nc, int nx, int ny, int nt, int B,
-                                                    float* __restrict__ coilmax, float* __restrict__ rowp,
-                                                    float* __restrict__ wscale) {
-  __shared__ float sh[4];
-  const int y = blockIdx.x, tid = threadIdx.x;
-  for (int x = tid; x < nx; x += 256) {
-    float m = 0.f;
-#pragma unroll 4
-    for (int n = 0; n < nc; ++n) {
-      const float2 c = coils[((size_t)n * ny + y) * nx + x];
-      m = fmaxf(m, fabsf(c.x) + fabsf(c.y));
-    }
-    coilmax[(size_t)y * nx + x] = m;
-  }
-  float m = 0.f;
-  for (int t = tid; t < nt; t += 256) {
-    const float2 v = psf[(size_t)y * nt + t];
-    m = fmaxf(m, fabsf(v.x) + fabsf(v.y));
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  if ((tid & 63) == 0) sh[tid >> 6] = m;
-  __syncthreads();
-  if (tid == 0) rowp[y] = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3])) * rsqrtf((float)nt);
-  for (int b = tid; b < B; b += 256) wscale[(size_t)b * ny + y] = 1.f;
 }
 
 int ceil_div(int n, int d) { return (n + d - 1) / d; }
@@ -768,9 +804,10 @@ size_t place_pair_scales(Plan& pl) {
   };
   take(&pl.wscale, (size_t)pl.B * pl.ny);
   take(&pl.cscale, pl.nc);
-  float* size = nullptr;
-  take(&size, 2 * (size_t)pl.nc);
-  pl.coilsize = reinterpret_cast<float2*>(size);
+  take(&pl.coilsize, sizeof(CoilSize) / sizeof(float) * (size_t)pl.nc);
+  float* flag = nullptr;
+  take(&flag, 1);
+  pl.unequal = reinterpret_cast<int*>(flag);
   take(&pl.coilmax, (size_t)pl.ny * pl.nx);
   take(&pl.rowp, pl.ny);
   take(&pl.ascale, (size_t)pl.G * pl.Kp);
@@ -796,40 +833,39 @@ bool pair_expand_ok(const Plan& pl) {
          (size_t)(16 / pl.P + 2) * pl.ny * pl.nt * 8 < kOOBPair;
 }
 
-// c[n] in steps of 2^16, at most 2^64 and no value of the map above 2^100: a pair
-// has room for less.  Coil maps within 2^16 of each other, which is all but a
-// set-up of very unequal gains, keep c = 1 and need no copy.
+// Coil maps within 2^16 of each other, which is all but a set-up of very unequal
+// gains, keep c = 1 and need no copy.  The others get one by scale_coils, once the
+// stream has run and *unequal is known.
 int setup_pair(Plan& pl) {
-  const size_t npix = (size_t)pl.ny * pl.nx;
-  std::vector<float2> size(pl.nc);
-  std::vector<float> c(pl.nc, 1.f);
-  hipLaunchKernelGGL(k_coil_size, dim3(pl.nc), dim3(1024), 0, pl.stream, pl.coils, npix, pl.coilsize);
-  GPJC_HIP(hipGetLastError());
-  GPJC_HIP(hipMemcpyAsync(size.data(), pl.coilsize, sizeof(float2) * pl.nc, hipMemcpyDeviceToHost, pl.stream));
-  GPJC_HIP(hipStreamSynchronize(pl.stream));
-  float most = -INFINITY;
-  for (const float2& e : size)
-    if (e.x < INFINITY) most = std::max(most, e.x);
-  bool any = false;
-  for (int n = 0; n < pl.nc; ++n)
-    if (size[n].x < INFINITY) {
-      const int steps = (int)std::min({(most - size[n].x) / 16.f, 4.f, std::max(0.f, (100.f - size[n].y) / 16.f)});
-      c[n] = std::ldexp(1.f, 16 * steps);
-      any = any || steps > 0;
-    }
-  GPJC_HIP(hipMemcpyAsync(pl.cscale, c.data(), sizeof(float) * pl.nc, hipMemcpyHostToDevice, pl.stream));
+  const bool sizes = pl.nc <= kMaxSizedCoils;
+  CoilSize* size = reinterpret_cast<CoilSize*>(pl.coilsize);
   pl.coils_pair = pl.coils;
-  if (any) {
-    float2* p = nullptr;
-    GPJC_HIP(hipMalloc(reinterpret_cast<void**>(&p), sizeof(float2) * pl.nc * npix));
-    pl.coils_pair = p;
-    hipLaunchKernelGGL(k_scale_coils, dim3((unsigned)std::min<size_t>((npix + 255) / 256, 1024), pl.nc), dim3(256), 0,
-                       pl.stream, pl.coils, npix, pl.cscale, p);
+  const dim3 grid(std::min(pl.ny, 1024));
+  if (sizes) {
+    GPJC_HIP(hipMemsetAsync(size, 0, sizeof(CoilSize) * pl.nc, pl.stream));
+    hipLaunchKernelGGL(k_pair_setup<true>, grid, dim3(256), 0, pl.stream, pl.coils, pl.psf, pl.nc, pl.nx, pl.ny, pl.nt,
+                       pl.B, pl.coilmax, pl.rowp, pl.wscale, size);
+  } else {
+    hipLaunchKernelGGL(k_pair_setup<false>, grid, dim3(256), 0, pl.stream, pl.coils, pl.psf, pl.nc, pl.nx, pl.ny,
+                       pl.nt, pl.B, pl.coilmax, pl.rowp, pl.wscale, size);
   }
-  hipLaunchKernelGGL(k_pair_setup, dim3(pl.ny), dim3(256), 0, pl.stream, pl.coils_pair, pl.psf, pl.nc, pl.nx, pl.ny,
-                     pl.nt, pl.B, pl.coilmax, pl.rowp, pl.wscale);
+  hipLaunchKernelGGL(k_coil_scale, dim3(1), dim3(256), 0, pl.stream, sizes ? size : nullptr, pl.nc, pl.cscale,
+                     pl.unequal);
   GPJC_HIP(hipGetLastError());
-  GPJC_HIP(hipStreamSynchronize(pl.stream));  // `c` is a host temporary
+  return GPJC_OK;
+}
+
+int scale_coils(Plan& pl) {
+  const size_t npix = (size_t)pl.ny * pl.nx;
+  float2* p = nullptr;
+  GPJC_HIP(hipMalloc(reinterpret_cast<void**>(&p), sizeof(float2) * pl.nc * npix));
+  pl.coils_pair = p;
+  hipLaunchKernelGGL(k_scale_coils, dim3((unsigned)std::min<size_t>((npix + 255) / 256, 1024), pl.nc), dim3(256), 0,
+                     pl.stream, pl.coils, npix, pl.cscale, p);
+  hipLaunchKernelGGL(k_pair_setup<false>, dim3(std::min(pl.ny, 1024)), dim3(256), 0, pl.stream, pl.coils_pair, pl.psf,
+                     pl.nc, pl.nx, pl.ny, pl.nt, pl.B, pl.coilmax, pl.rowp, pl.wscale, nullptr);
+  GPJC_HIP(hipGetLastError());
+  GPJC_HIP(hipStreamSynchronize(pl.stream));
   return GPJC_OK;
 }
 

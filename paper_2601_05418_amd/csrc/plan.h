@@ -122,7 +122,8 @@ struct Plan {
   float* wscale = nullptr;  // [B][ny] scale of W's rows, written by the readout forward
   float* cscale = nullptr;  // [nc] power of two that brings the coils' maps to about one size
   float2* coils_pair = nullptr;  // [nc][ny][nx] coil maps times cscale: coils itself where that is 1 throughout
-  float2* coilsize = nullptr;    // [nc] mean and largest exponent of a coil's map
+  float* coilsize = nullptr;     // [nc] exponents of the coils' maps (pair.hip: CoilSize)
+  int* unequal = nullptr;        // [1] whether any cscale is not 1
   float* coilmax = nullptr; // [ny][nx] largest coil value of every pixel, coils scaled by cscale
   float* rowp = nullptr;    // [ny] max|psf| / sqrt(nt) of every row
   float* ascale = nullptr;  // [G][Kp] power-of-two scale of the pairs of a bank row
@@ -224,6 +225,7 @@ size_t place_pair_scales(Plan& pl);          // sets the pointers into pl.scales
 size_t pair_compress_words(const Plan& pl);
 size_t pair_expand_words(const Plan& pl);
 int setup_pair(Plan& pl);
+int scale_coils(Plan& pl);  // where *unequal is set
 int launch_pair_bank(const Plan& pl);
 void default_pair_compress(const Plan& pl, Plan::GemmCfg& g);
 void default_pair_expand(const Plan& pl, Plan::GemmCfg& g);

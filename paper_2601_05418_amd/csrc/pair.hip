@@ -619,11 +619,11 @@ __global__ __launch_bounds__(256) void k_pair_bank(const double2* __restrict__ A
 // Set-up, rows y of one work-group: coilmax[y][x], rowp[y], and the row's scales
 // set to one (|re| + |im| bounds a modulus; fmaxf drops a NaN, and the row of W that
 // it reaches is NaN under any scale); with SIZES, over all rows, each coil's sum of
-// the exponents of its values that are neither zero nor non-finite, their number
-// and the largest.  (Integers: the order of the additions does not matter.)
+// the (biased) exponents of its values that are neither zero nor non-finite, and
+// their number.  (Integers: the order of the additions does not matter.  A wave
+// adds its 64 exponents bit by bit, by ballots, which wait for nothing.)
 struct CoilSize {
-  long long sum;
-  int count, most;  // most: largest exponent + 128
+  unsigned long long sum, count;
 };
 constexpr int kMaxSizedCoils = 2048;
 template <bool SIZES>
@@ -632,10 +632,10 @@ __global__ __launch_bounds__(256) void k_pair_setup(const float2* __restrict__ c
                                                     float* __restrict__ coilmax, float* __restrict__ rowp,
                                                     float* __restrict__ wscale, CoilSize* __restrict__ size) {
   __shared__ float sh[4];
-  __shared__ int lsum[SIZES ? kMaxSizedCoils : 1], lcnt[SIZES ? kMaxSizedCoils : 1], lmax[SIZES ? kMaxSizedCoils : 1];
+  __shared__ unsigned lsum[SIZES ? kMaxSizedCoils : 1], lcnt[SIZES ? kMaxSizedCoils : 1];
   const int tid = threadIdx.x, lane = tid & 63;
   if (SIZES) {
-    for (int n = tid; n < nc; n += 256) lsum[n] = lcnt[n] = lmax[n] = 0;
+    for (int n = tid; n < nc; n += 256) lsum[n] = lcnt[n] = 0;
     __syncthreads();
   }
   for (int y = blockIdx.x; y < ny; y += gridDim.x) {
@@ -654,18 +654,14 @@ __global__ __launch_bounds__(256) void k_pair_setup(const float2* __restrict__ c
           m = fmaxf(m, v[h]);
           if (SIZES) {
             const int e = (int)(__float_as_uint(v[h]) >> 23);
-            const bool ok = e > 0 && e < 255;
-            int s = ok ? e - 127 : 0, q = ok ? e + 1 : 0;
-            const int k = __popcll(__ballot(ok));
+            const int ok = e < 255 ? e : 0;
+            unsigned sum = 0;
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-              s += __shfl_xor(s, off, 64);
-              q = max(q, __shfl_xor(q, off, 64));
-            }
-            if (lane == 0 && k) {
-              atomicAdd(&lsum[n0 + h], s);
-              atomicAdd(&lcnt[n0 + h], k);
-              atomicMax(&lmax[n0 + h], q);
+            for (int b = 0; b < 8; ++b) sum += (unsigned)__popcll(__ballot((ok >> b) & 1)) << b;
+            const unsigned cnt = __popcll(__ballot(ok != 0));
+            if (lane == 0 && cnt) {
+              atomicAdd(&lsum[n0 + h], sum);
+              atomicAdd(&lcnt[n0 + h], cnt);
             }
           }
         }
@@ -689,16 +685,15 @@ __global__ __launch_bounds__(256) void k_pair_setup(const float2* __restrict__ c
     __syncthreads();
     for (int n = tid; n < nc; n += 256)
       if (lcnt[n]) {
-        atomicAdd(reinterpret_cast<unsigned long long*>(&size[n].sum), (unsigned long long)(long long)lsum[n]);
-        atomicAdd(&size[n].count, lcnt[n]);
-        atomicMax(&size[n].most, lmax[n]);
+        atomicAdd(&size[n].sum, (unsigned long long)lsum[n]);
+        atomicAdd(&size[n].count, (unsigned long long)lcnt[n]);
       }
   }
 }
 
 // c[n] from the mean exponents, in steps of 2^16 (a pair has room for less), at most
-// 2^64 and no value above 2^100; *unequal is set if any is not one.  A mean: one
-// value of any size does not move it.  size NULL: c = 1 throughout.
+// 2^64; *unequal is set if any is not one.  A mean: one value of any size does not
+// move it.  size NULL: c = 1 throughout.
 __global__ __launch_bounds__(256) void k_coil_scale(const CoilSize* __restrict__ size, int nc,
                                                     float* __restrict__ cscale, int* __restrict__ unequal) {
   __shared__ float sh[4];
@@ -716,13 +711,32 @@ __global__ __launch_bounds__(256) void k_coil_scale(const CoilSize* __restrict__
   int any = 0;
   for (int n = tid; n < nc; n += 256) {
     int steps = 0;
-    if (size && size[n].count)
-      steps = min(min((int)((most - mean(n)) / 16.f), 4), max(0, (100 - (size[n].most - 128)) / 16));
+    if (size && size[n].count) steps = min((int)((most - mean(n)) / 16.f), 4);
     cscale[n] = __uint_as_float((uint32_t)(127 + 16 * steps) << 23);
     any |= steps;
   }
   any = __syncthreads_or(any);
   if (tid == 0) *unequal = any != 0;
+}
+
+// No value of a scaled map above 2^100: one work-group per coil.
+__global__ __launch_bounds__(1024) void k_coil_limit(const float2* __restrict__ coils, size_t npix,
+                                                     float* __restrict__ cscale) {
+  __shared__ int most;
+  if (threadIdx.x == 0) most = 0;
+  __syncthreads();
+  int m = 0;
+  for (size_t i = threadIdx.x; i < npix; i += 1024) {
+    const float2 c = coils[(size_t)blockIdx.x * npix + i];
+    const int e = (int)(__float_as_uint(fabsf(c.x) + fabsf(c.y)) >> 23);
+    m = max(m, e < 255 ? e : 0);
+  }
+  atomicMax(&most, m);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int steps = ((int)(__float_as_uint(cscale[blockIdx.x]) >> 23) - 127) / 16;
+    cscale[blockIdx.x] = __uint_as_float((uint32_t)(127 + 16 * min(steps, max(0, (227 - most) / 16))) << 23);
+  }
 }
 
 __global__ void k_scale_coils(const float2* __restrict__ coils, size_t npix, const float* __restrict__ cscale,
@@ -860,6 +874,7 @@ int scale_coils(Plan& pl) {
   float2* p = nullptr;
   GPJC_HIP(hipMalloc(reinterpret_cast<void**>(&p), sizeof(float2) * pl.nc * npix));
   pl.coils_pair = p;
+  hipLaunchKernelGGL(k_coil_limit, dim3(pl.nc), dim3(1024), 0, pl.stream, pl.coils, npix, pl.cscale);
   hipLaunchKernelGGL(k_scale_coils, dim3((unsigned)std::min<size_t>((npix + 255) / 256, 1024), pl.nc), dim3(256), 0,
                      pl.stream, pl.coils, npix, pl.cscale, p);
   hipLaunchKernelGGL(k_pair_setup<false>, dim3(std::min(pl.ny, 1024)), dim3(256), 0, pl.stream, pl.coils_pair, pl.psf,

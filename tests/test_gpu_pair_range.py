@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import encoding as oe
 from paper_2601_05418_amd import gpjc, synth
 from tests import helpers as H
 
@@ -140,3 +141,20 @@ def test_images_and_rows(gpu_lib):
     for b in range(4):
         check(out[b], ops["fwd"](x[b]))
         check(nrm[b], ops["nrm"](x[b]))
+
+
+def test_more_coils_than_are_sized(gpu_lib):
+    """Above 2048 coils the maps are taken as they are."""
+    nc, n, k = 2100, 16, 3
+    rng = np.random.default_rng(6)
+    coils = H.round64(H.crandn(rng, (nc, n, n)))
+    psf = H.round64(np.exp(1j * rng.standard_normal((n, n))))
+    mask, groups = np.ones(n, bool), np.zeros(n, int)
+    bank = H.crandn(rng, (1, k, nc, 1)) / np.sqrt(nc)
+    plan = gpjc.Plan(n, n, nc, 1, coils, psf, mask, 1, groups, 1, k)
+    plan.set_compression(torch.as_tensor(bank).cuda())
+    x = H.round64(H.crandn(rng, (n, n)))
+    y = H.round64(H.crandn(rng, plan.data_shape()))
+    args = (coils, psf, mask, 1, bank, groups, 1)
+    check(host(plan.forward(dev(x[None])))[0], oe.forward(x, *args))
+    check(host(plan.adjoint(dev(y)))[0], oe.adjoint(y[0], *args))

@@ -53,11 +53,20 @@ typedef struct { double re, im; } gpjc_c128;
 
 /* Arithmetic of the group contraction and PSF product inside the operator.
  * FP32: FP32 storage and FP32 accuracy.  The group contractions run on the
- * FP16 MFMA, every FP32 operand split into a pair hi + lo of FP16 values under
- * a power-of-two scale (22-23 bits; the product lo lo, below 2^-24, is
- * dropped) with FP32 accumulation: closer to exact arithmetic than the FP32
- * MFMA, which rounds its accumulator 16 times as often.  The rest of the
- * operator, and gpjc_compress, are FP32 throughout.  BF16 / FP16 (compressed plans with
+ * FP16 MFMA, every FP32 operand split into a pair of FP16 values under a
+ * power-of-two scale with FP32 accumulation (the product of the low pieces,
+ * below 2^-24, is dropped).  The scales follow the image rows, the rows of the
+ * bank and, from 2^16 on, the gains of the coils, so the sizes of these cost
+ * nothing.  What is left to one scale: the coils' data of one image row (a pair
+ * is exact to 2^-24 down to about 2^-24 of the row's strongest coil, and to
+ * 2^-51 of it absolutely below), the entries of one bank row (to 2^-27 of the
+ * largest), and the Z of one patch in neighbouring rows.  Within that the
+ * contractions are closer to exact arithmetic than the FP32 MFMA, which rounds
+ * its accumulator 16 times as often; a channel that draws on data 2^-28 of
+ * their row alone is off by 3e-6, where BF16X6 keeps every element's 24 bits.
+ * The rest of the operator, gpjc_compress, and contractions that pairs do not
+ * serve (K above 512 expanding, patches of a few samples of very large volumes
+ * compressing) are FP32 throughout.  BF16 / FP16 (compressed plans with
  * patch_len % 4 == 0, else GPJC_E_UNSUPPORTED): the operands of both group
  * contractions are rounded to BF16 / FP16 (round to nearest even) and
  * contracted on MFMA with FP32 accumulation -- the compression matrices and

@@ -934,8 +934,8 @@ static int pair_resident(int wm, int nt) {
 }
 
 // Column tiles and split of the compressing form by the time they are
-// expected to take: a work-group needs about 1.5 us to fill and drain and 0.25 + 0.14
-// NT us (for WK = 2) per k-tile, 0.4 times as long again for each work-group that
+// expected to take: a work-group needs about 2 us to fill and drain and 0.15 + 0.18
+// NT us (for WK = 2) per k-tile, half as long again for each work-group that
 // shares the CU, the launch as many such rounds as its work-groups make, and every
 // split writes and reads back a partial of Z at about 5 TB/s.  No split where the
 // launch has four work-groups per CU without one: there it adds partials of Z and no
@@ -954,8 +954,8 @@ void default_pair_compress(const Plan& pl, Plan::GemmCfg& g) {
     const int res = pair_resident(wm, t), most = groups >= 1024 ? 1 : std::min(kMaxKsplit, ntile);
     for (int ks = 1; ks <= most; ++ks) {
       const long per_cu = (groups * ks + 255) / 256, rem = per_cu % res;
-      const double rounds = per_cu / res * (0.6 + 0.4 * res) + (rem ? 0.6 + 0.4 * rem : 0.0);
-      const double us = rounds * (ceil_div(ntile, ks) * (0.25 + 0.14 * t) * wk / 2 + 1.5) + zus * ks + 0.3 * (ks - 1);
+      const double rounds = per_cu / res * (0.5 + 0.5 * res) + (rem ? 0.5 + 0.5 * rem : 0.0);
+      const double us = rounds * (ceil_div(ntile, ks) * (0.15 + 0.18 * t) * wk / 2 + 2.0) + zus * ks + 0.3 * (ks - 1);
       if (us < best) {
         best = us;
         g.cvar = 8 - t;

@@ -966,6 +966,13 @@ void default_pair_compress(const Plan& pl, Plan::GemmCfg& g) {
 }
 void default_pair_expand(const Plan& pl, Plan::GemmCfg& g) { g.evar = 8 - pair_expand_tiles(pl); }
 
+// The variants below these run as they do: fewer column tiles than their number says.
+int pair_first_compress(const Plan& pl) { return 8 - pair_max_nt(pair_wm(pl.K)); }
+int pair_first_expand(const Plan& pl) {
+  const int kbk = pl.Kp / 16;
+  return 8 - std::min(kbk > kMaxGK ? 5 : 8, kExpandLds / (2048 * kbk));
+}
+
 // Partials of Z that a split leaves: 1 where the launch has four work-groups per CU
 // without one (a tuned choice of a smaller plan's bucket, or a caller's).
 int pair_partials(const Plan& pl, const Plan::GemmCfg& cfg) {

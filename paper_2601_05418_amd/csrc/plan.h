@@ -230,6 +230,8 @@ int launch_pair_bank(const Plan& pl);
 void default_pair_compress(const Plan& pl, Plan::GemmCfg& g);
 void default_pair_expand(const Plan& pl, Plan::GemmCfg& g);
 int pair_partials(const Plan& pl, const Plan::GemmCfg& cfg);
+int pair_first_compress(const Plan& pl);
+int pair_first_expand(const Plan& pl);
 int launch_compress_pair(const Plan& pl, StageScope& sc, const void* in, float2* out);
 int launch_expand_pair(const Plan& pl, StageScope& sc);
 // Whether the staged compressing forms can address the readout-stage output

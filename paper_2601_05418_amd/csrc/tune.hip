@@ -123,7 +123,10 @@ int measure(Plan& pl, Store st, Choice* out, float* us_c, float* us_e) {
   // timed when another split keeps them
   bool any_staged = false;
   for (int ks : splits) any_staged = any_staged || (ks <= kMaxKsplit && compress_split_staged(pl, st, ks));
-  for (int v = 0; status == GPJC_OK && v < gemm_compress_variants(); ++v) {
+  const bool pairs = st == Store::F32;
+  const int c0 = pairs && pair_compress_ok(pl) ? pair_first_compress(pl) : 0;
+  const int e0 = pairs && pair_expand_ok(pl) ? pair_first_expand(pl) : 0;
+  for (int v = c0; status == GPJC_OK && v < gemm_compress_variants(); ++v) {
     unsigned timed = 0;  // splits that run (compress_partials): one that runs as another is not timed again
     for (int ks : splits) {
       if (status != GPJC_OK || ks > kMaxKsplit || (ks > 1 && kd / ks < 64)) continue;
@@ -148,7 +151,7 @@ int measure(Plan& pl, Store st, Choice* out, float* us_c, float* us_e) {
       }
     }
   }
-  for (int v = 0; status == GPJC_OK && v < gemm_expand_variants(); ++v) {
+  for (int v = e0; status == GPJC_OK && v < gemm_expand_variants(); ++v) {
     cfg.evar = v;
     float us = 0.f;
     status = time_us(pl, ev.a, ev.b, [&] { return launch_group_expand(pl, st); }, &us);
